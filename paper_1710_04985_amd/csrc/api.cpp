@@ -22,7 +22,7 @@
 #include "column.hpp"
 #include "probe.hpp"
 #include "kernels.hpp"
-#include "tiles.hpp"
+#include "strips.hpp"
 
 using namespace sptrsv;
 
@@ -62,7 +62,7 @@ struct PlanState {
   int* a_depcnt = nullptr;
   int* a_jlev = nullptr;
   PushState push;
-  DevTiles tiles;                 // tiled copy (tiles.hpp), if the rows sit on a grid
+  DevStrips strips;               // strip-ordered copy (strips.hpp), if the rows sit on a grid
   void* vals_buf = nullptr;       // [noff + 2n] values: off-diagonals, diagonal, 1/diagonal
   // (group, epl, rows_fixed, rows_per_lane)
   std::map<std::tuple<int, int, int, int>, ChunkEntry> chunks;
@@ -98,7 +98,7 @@ struct Config {
   int stride = 1;  // static schedules, one right-hand side: elements between xp values
   int mrows = 0;   // static schedule, several right-hand sides: rows per lane group
                    // (1, 2, 4; 0 = by the number of right-hand sides)
-  int tile = 0;    // self-scheduled over tiles where the plan has them (same bits)
+  int strip = 0;   // self-scheduled over strips where the plan has them (same bits)
 };
 
 std::mutex g_tune_mu;
@@ -310,7 +310,7 @@ void free_plan(PlanState& ps) {
   dfree(ps.a_depcnt);
   dfree(ps.a_jlev);
   free_push(ps.push);
-  free_tiles(ps.tiles);
+  free_strips(ps.strips);
   ps.d = DevPlan();
   ps.vals_buf = nullptr;
   ps.a_level = ps.a_depcnt = ps.a_jlev = nullptr;
@@ -425,7 +425,7 @@ int read_status(sptrsv_handle_t h, hipStream_t s, bool clear) {
 }
 
 int install_device_plan(sptrsv_handle_t h, PlanState& ps, DeviceAnalysis& da, bool upper);
-void build_tile_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t s);
+void build_strip_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t s);
 
 // Builds the analysis of T^T: rows of T^T are the columns of T; each value is
 // taken from the forward plan's value buffer (so the caller's vals need not
@@ -451,7 +451,7 @@ int build_transpose(sptrsv_handle_t h, hipStream_t s) {
       free_device_analysis(da);
       free_plan(h->trn);
     }
-    if (!st) build_tile_state(h, h->trn, !h->upper, s);
+    if (!st) build_strip_state(h, h->trn, !h->upper, s);
     if (st != kErrNotSupported) return st;   // else the host route below decides
   }
   if (const int st = ensure_host_plan(h)) return st;
@@ -470,7 +470,7 @@ int build_transpose(sptrsv_handle_t h, hipStream_t s) {
   if (!st) st = gather(h, h->trn, h->fwd.vals_buf, s);
   if (!st && hipStreamSynchronize(s) != hipSuccess) st = kErrHip;
   if (st) free_plan(h->trn);   // a later call starts over instead of using half a plan
-  else build_tile_state(h, h->trn, !h->upper, s);
+  else build_strip_state(h, h->trn, !h->upper, s);
   return st;
 }
 
@@ -627,11 +627,16 @@ ChunkEntry* get_col_chunks(PlanState& ps, int group, int epl, int ncols, const C
 }
 
 int ensure_xp(sptrsv_handle_t h, int64_t elems);
-int tile_occupancy(sptrsv_handle_t h, const PlanState& ps);
+int strip_occupancy(sptrsv_handle_t h, const PlanState& ps);
 
-// Entries per lane of the default lane rule, the one the tiled copy is built
+// Values of the solution buffer a strip solve uses.
+int64_t strip_values(const PlanState& ps) {
+  return ps.strips.npub + static_cast<int64_t>(kDumpSlot) * ps.strips.nstrips;
+}
+
+// Entries per lane of the default lane rule, the one the strip-ordered copy is built
 // for.
-constexpr int kTileLaneEntries = 4;
+constexpr int kStripLaneEntries = 4;
 
 // Option bits of set_mask: options set explicitly, which the pattern-based
 // defaults of resolve() leave alone.
@@ -649,11 +654,11 @@ int widest_level(sptrsv_handle_t h) {
   return h->max_level;
 }
 
-// Whether the options leave room for the tiled form of the self-scheduled
+// Whether the options leave room for the strip form of the self-scheduled
 // solve: it computes the sums of the default lane rule, with one-wavefront
 // workgroups.
-bool tile_rule(sptrsv_handle_t h) {
-  return h->fwd.tiles.ntiles > 0 && h->group == 0 && h->epl == kTileLaneEntries && h->wg == 64 &&
+bool strip_rule(sptrsv_handle_t h) {
+  return h->fwd.strips.nstrips > 0 && h->group == 0 && h->epl == kStripLaneEntries && h->wg == 64 &&
          (h->algo == SPTRSV_ALGO_AUTO || h->algo == SPTRSV_ALGO_SELF);
 }
 
@@ -687,6 +692,9 @@ Config resolve(sptrsv_handle_t h) {
     if (!h->batched && one_lane && h->block_resident && n <= 65535 && p.noff <= 65535 &&
         lds <= h->lds_limit && widest_level(h) <= 64) {
       c.algo = SPTRSV_ALGO_BLOCK;
+      // (2-D 64x64, whole call: 54 us with the block kernel, 27 in strips)
+      c.strip = strip_rule(h) && !h->set_mask && c.poll == 1 && c.rpl == 1 &&
+                c.sync == SPTRSV_SYNC_VALUE;
       return c;
     }
     c.algo = SPTRSV_ALGO_SELF;
@@ -700,8 +708,7 @@ Config resolve(sptrsv_handle_t h) {
                    : SPTRSV_ASSIGN_XCD;
   if (!(h->set_mask & kSetGrid) && (long_rows || n > 8192 * nlev)) c.grid = 2 * h->num_cu;
   if (!(h->set_mask & kSetStride) && long_rows) c.stride = 32 / h->vb;
-  c.tile = tile_rule(h) && !(h->set_mask & (kSetGrid | kSetAssign | kSetStride)) && c.poll == 1 &&
-           c.rpl == 1;
+  c.strip = strip_rule(h) && !h->set_mask && c.poll == 1 && c.rpl == 1;
   return c;
 }
 
@@ -741,36 +748,36 @@ bool multi_by_columns(const PlanState& ps, const Config& c) {
 
 // Distinct offsets of the pattern, system by system (h->offsets; left empty
 // when some system has more than a grid's stencil would).  row_ptr, col: the
-// pattern in device memory.  Blocking; a failure only leaves the tiled form
+// pattern in device memory.  Blocking; a failure only leaves the strip form
 // unused.
 void find_offsets(sptrsv_handle_t h, const int* row_ptr, const int* col, hipStream_t s) {
   h->offsets.clear();
-  if (h->n == 0 || h->fwd.h.max_row_len > kTileMaxEntries) return;
+  if (h->n == 0 || h->fwd.h.max_row_len > kStripMaxEntries) return;
   std::vector<int> row0(1, 0);
   if (h->batched)
     for (int ni : h->sys_n) row0.push_back(row0.back() + ni);
   else
     row0.push_back(h->n);
   const int nsys = static_cast<int>(row0.size()) - 1;
-  const int words = nsys * (kTileTable + 1) + nsys + 1;   // tables, full flags, row0
+  const int words = nsys * (kStripTable + 1) + nsys + 1;   // tables, full flags, row0
   int err = kOk;
   int* buf = dalloc<int>(words, &err);
   if (!buf) return;
   std::vector<int> host(words, 0);
-  std::copy(row0.begin(), row0.end(), host.begin() + nsys * (kTileTable + 1));
-  int* full = buf + static_cast<int64_t>(nsys) * kTileTable;
+  std::copy(row0.begin(), row0.end(), host.begin() + nsys * (kStripTable + 1));
+  int* full = buf + static_cast<int64_t>(nsys) * kStripTable;
   if (hipMemcpyAsync(buf, host.data(), words * sizeof(int), hipMemcpyHostToDevice, s) == hipSuccess &&
-      launch_tile_offsets(h->n, row_ptr, col, nsys, full + nsys, buf, full, s) == hipSuccess &&
-      hipMemcpyAsync(host.data(), buf, static_cast<size_t>(nsys) * (kTileTable + 1) * sizeof(int),
+      launch_strip_offsets(h->n, row_ptr, col, nsys, full + nsys, buf, full, s) == hipSuccess &&
+      hipMemcpyAsync(host.data(), buf, static_cast<size_t>(nsys) * (kStripTable + 1) * sizeof(int),
                      hipMemcpyDeviceToHost, s) == hipSuccess &&
       hipStreamSynchronize(s) == hipSuccess) {
     h->offsets.resize(nsys);
     for (int k = 0; k < nsys; ++k) {
       std::vector<int>& o = h->offsets[k];
-      for (int q = 0; q < kTileTable; ++q)
-        if (host[k * kTileTable + q]) o.push_back(host[k * kTileTable + q]);
+      for (int q = 0; q < kStripTable; ++q)
+        if (host[k * kStripTable + q]) o.push_back(host[k * kStripTable + q]);
       std::sort(o.begin(), o.end());
-      if (host[nsys * kTileTable + k] || o.size() > kTileMaxOffsets) {
+      if (host[nsys * kStripTable + k] || o.size() > kStripMaxOffsets) {
         h->offsets.clear();
         break;
       }
@@ -779,19 +786,19 @@ void find_offsets(sptrsv_handle_t h, const int* row_ptr, const int* col, hipStre
   dfree(buf);
 }
 
-// The tiled copy of a plan (tiles.hpp), if its rows sit on a grid and memory
+// The strip-ordered copy of a plan (strips.hpp), if its rows sit on a grid and memory
 // allows; otherwise the plan keeps the row-wise schedules alone.  Blocking.
-void build_tile_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t s) {
-  if (h->offsets.empty() || ps.tiles.ntiles) return;
+void build_strip_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t s) {
+  if (h->offsets.empty() || ps.strips.nstrips) return;
   const int nsys = static_cast<int>(h->offsets.size());
   int err = kOk;
   unsigned char* lanes = nullptr;
-  if (ps.h.max_row_len > kTileLaneEntries) {
+  if (ps.h.max_row_len > kStripLaneEntries) {
     // rows of several lanes: their sums are split the same way here
-    ChunkEntry* ch = get_chunks(h, ps, 0, kTileLaneEntries, 0, 1, &err);
+    ChunkEntry* ch = get_chunks(h, ps, 0, kStripLaneEntries, 0, 1, &err);
     if (!ch) return;
     lanes = dalloc<unsigned char>(static_cast<size_t>(h->n), &err);
-    if (!lanes || launch_tile_lanes(ch->d, lanes, s) != hipSuccess) {
+    if (!lanes || launch_strip_lanes(ch->d, lanes, s) != hipSuccess) {
       dfree(lanes);
       return;
     }
@@ -804,33 +811,31 @@ void build_tile_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t 
     }
   }
   for (int attempt = 0; attempt < 2 && ps.d.row_pos; ++attempt) {
-    std::vector<TileGrid> grids(nsys);
-    int ext = 0, at = 0;
+    std::vector<StripGrid> grids(nsys);
+    int at = 0;
     bool ok = true, retry = false;
     for (int k = 0; k < nsys && ok; ++k) {
       const int nk = h->batched ? h->sys_n[k] : h->n;
-      int e = 0;
       if (nk > 0) {
-        ok = tile_infer(h->offsets[k], nk, upper, attempt, &grids[k], &e);
+        ok = strip_infer(h->offsets[k], nk, upper, attempt, &grids[k]);
         // systems with one reading keep it on the second attempt
         if (ok && attempt) retry = true;
-        if (!ok && attempt) ok = tile_infer(h->offsets[k], nk, upper, 0, &grids[k], &e);
+        if (!ok && attempt) ok = strip_infer(h->offsets[k], nk, upper, 0, &grids[k]);
       }
       grids[k].row0 = at;
       at += nk;
-      ext = std::max(ext, e);
     }
     if (!ok || (attempt && !retry)) break;
-    const int st = build_tiles(ps.d, grids, ext, ps.h.max_row_len, lanes, static_cast<int>(h->vb),
-                               s, ps.tiles);
+    const int st = build_strips(ps.d, grids, ps.h.max_row_len, lanes, static_cast<int>(h->vb),
+                               s, ps.strips);
     if (st == kErrNotSupported) continue;
     if (!st) {
-      const hipError_t e = h->dtype == SPTRSV_F64 ? launch_tile_gather<double>(ps.d, ps.tiles, s)
-                                                  : launch_tile_gather<float>(ps.d, ps.tiles, s);
-      if (e != hipSuccess || ensure_xp(h, ps.tiles.npos) || hipStreamSynchronize(s) != hipSuccess)
-        free_tiles(ps.tiles);
+      const hipError_t e = h->dtype == SPTRSV_F64 ? launch_strip_gather<double>(ps.d, ps.strips, s)
+                                                  : launch_strip_gather<float>(ps.d, ps.strips, s);
+      if (e != hipSuccess || ensure_xp(h, strip_values(ps)) || hipStreamSynchronize(s) != hipSuccess)
+        free_strips(ps.strips);
       else
-        (void)tile_occupancy(h, ps);
+        (void)strip_occupancy(h, ps);
     }
     break;
   }
@@ -915,12 +920,12 @@ int persistent_grid(sptrsv_handle_t h, int kind, int grid, int nchunks) {
   return std::max(1, std::min(g, need));
 }
 
-int tile_occupancy(sptrsv_handle_t h, const PlanState& ps) {
+int strip_occupancy(sptrsv_handle_t h, const PlanState& ps) {
   const auto key = std::make_pair(&ps == &h->trn ? 17 : 16, 64);
   auto it = h->occupancy.find(key);
   if (it != h->occupancy.end()) return it->second;
-  const int per_cu = h->dtype == SPTRSV_F64 ? tile_blocks_per_cu<double>(ps.tiles)
-                                            : tile_blocks_per_cu<float>(ps.tiles);
+  const int per_cu = h->dtype == SPTRSV_F64 ? strip_blocks_per_cu<double>(ps.strips)
+                                            : strip_blocks_per_cu<float>(ps.strips);
   h->occupancy[key] = per_cu;
   return per_cu;
 }
@@ -1042,12 +1047,12 @@ int regather_push(sptrsv_handle_t h, hipStream_t s) {
   return kOk;
 }
 
-// Re-gathers the tiled copies after a value update.
-int regather_tiles(sptrsv_handle_t h, hipStream_t s) {
+// Re-gathers the strip-ordered copies after a value update.
+int regather_strips(sptrsv_handle_t h, hipStream_t s) {
   for (PlanState* ps : {&h->fwd, &h->trn}) {
-    if (!ps->tiles.ntiles) continue;
-    const hipError_t e = h->dtype == SPTRSV_F64 ? launch_tile_gather<double>(ps->d, ps->tiles, s)
-                                                : launch_tile_gather<float>(ps->d, ps->tiles, s);
+    if (!ps->strips.nstrips) continue;
+    const hipError_t e = h->dtype == SPTRSV_F64 ? launch_strip_gather<double>(ps->d, ps->strips, s)
+                                                : launch_strip_gather<float>(ps->d, ps->strips, s);
     if (e != hipSuccess) return kErrHip;
   }
   return kOk;
@@ -1115,32 +1120,26 @@ int solve_column(sptrsv_handle_t h, PlanState& ps, const Config& c, const void* 
   return kOk;
 }
 
-// Tiled self-scheduled solve, one right-hand side.  The grid keeps the
-// residency margins of persistent_grid.
+// Strip-wise self-scheduled solve, one right-hand side.  Strips are claimed
+// from a ticket, so the grid may fill the GPU.
 template <typename T>
-int solve_tiled(sptrsv_handle_t h, PlanState& ps, const Config& c, const void* b, void* x,
+int solve_strips(sptrsv_handle_t h, PlanState& ps, const Config& c, const void* b, void* x,
                 void* xp, hipStream_t s, const SolveExt& ext) {
-  TileSolveArgs a;
-  a.tiles = &ps.tiles;
+  StripSolveArgs a;
+  a.strips = &ps.strips;
   a.scratch = h->scratch;
   a.b = b;
   a.x = x;
   a.xp = xp;
   a.spin_limit = h->spin_limit;
-  a.res_limit = h->res_limit;
   a.coop = h->coop;
-  const int cap = std::max(1, std::min(tile_occupancy(h, ps) / 2, 8)) * h->num_cu;
-  // untuned: about as many wavefronts as the DAG has tiles abreast; more of
-  // them only add polls ahead of the front (7-point 128^3, lower then upper:
-  // 330 us at 2 per CU, 379 at 8; 256 ILU(0) factors: 326 us at 2, 195 at 8)
-  const int abreast = ps.tiles.ntiles / std::max(1, ps.tiles.order);
-  const int want = h->tuned ? c.grid : (abreast > 3 * h->num_cu ? 8 : 2) * h->num_cu;
-  a.grid = std::max(1, std::min(std::min(want, cap), ps.tiles.ntiles));
-  if (launch_fill_sentinel<T>(static_cast<T*>(xp), ps.tiles.npos, h->scratch.arrive, s) != hipSuccess)
+  const int cap = strip_occupancy(h, ps) * h->num_cu;
+  a.grid = std::max(1, std::min(cap, ps.strips.nstrips));
+  if (launch_fill_sentinel<T>(static_cast<T*>(xp), ps.strips.npub, h->scratch.arrive, s) != hipSuccess)
     return kErrHip;
   hipEvent_t stop;
   timing_begin(h, s, &stop, ext.no_alloc);
-  if (launch_tile_solve<T>(a, s) != hipSuccess) return kErrHip;
+  if (launch_strip_solve<T>(a, s) != hipSuccess) return kErrHip;
   timing_end(s, stop);
   return kOk;
 }
@@ -1153,14 +1152,14 @@ int solve_impl(sptrsv_handle_t h, PlanState& ps, const Config& c_in, const void*
   if (n == 0 || nrhs == 0) return kOk;
   const bool multi = nrhs > 1;
   if (is_column(c_in.algo) && !multi) return solve_column<T>(h, ps, c_in, b, x, s, ext);
-  if (c_in.tile && !multi && ps.tiles.ntiles) {
-    // a fixed buffer too small for the tiles' positions leaves the row-wise form
+  if (c_in.strip && !multi && ps.strips.nstrips) {
+    // a fixed buffer too small for the published values leaves the row-wise form
     if (!ext.xp) {
-      if (const int st = ensure_xp(h, ps.tiles.npos)) return st;
-      return solve_tiled<T>(h, ps, c_in, b, x, h->xp, s, ext);
+      if (const int st = ensure_xp(h, strip_values(ps))) return st;
+      return solve_strips<T>(h, ps, c_in, b, x, h->xp, s, ext);
     }
-    if (ps.tiles.npos * static_cast<int64_t>(h->vb) <= ext.xp_bytes)
-      return solve_tiled<T>(h, ps, c_in, b, x, ext.xp, s, ext);
+    if (strip_values(ps) * static_cast<int64_t>(h->vb) <= ext.xp_bytes)
+      return solve_strips<T>(h, ps, c_in, b, x, ext.xp, s, ext);
   }
   // several right-hand sides under a column-wise schedule: row-wise, self-scheduled
   Config c = c_in;
@@ -1430,7 +1429,8 @@ int solve_dispatch_ordered(sptrsv_handle_t h, bool transpose, const void* b, voi
     }
     return kOk;
   }
-  if (c.algo == SPTRSV_ALGO_BLOCK && nrhs == 1 && !h->blk[transpose ? 1 : 0].built) {
+  if (c.algo == SPTRSV_ALGO_BLOCK && nrhs == 1 && !(c.strip && ps.strips.nstrips) &&
+      !h->blk[transpose ? 1 : 0].built) {
     if (ext.no_alloc) return kErrNotSupported;
     const int st = build_block(h, transpose ? 1 : 0, s);
     if (st) return st;
@@ -1519,7 +1519,7 @@ int analyze_from_host(sptrsv_handle_t h, const int* row_ptr, const int* col_idx,
   if ((st = gather(h, h->fwd, vals, s))) return st;
   if ((st = read_status(h, s, true))) return st;
   find_offsets(h, row_ptr, col_idx, s);
-  build_tile_state(h, h->fwd, h->upper, s);
+  build_strip_state(h, h->fwd, h->upper, s);
   return kOk;
 }
 
@@ -1605,7 +1605,7 @@ int analyze_on_device(sptrsv_handle_t h, const int* row_ptr, const int* col_idx,
   if ((st = gather(h, h->fwd, vals, s))) return st;
   if ((st = read_status(h, s, true))) return st;
   find_offsets(h, row_ptr, col_idx, s);
-  build_tile_state(h, h->fwd, h->upper, s);
+  build_strip_state(h, h->fwd, h->upper, s);
   return kOk;
 }
 
@@ -1877,7 +1877,7 @@ int sptrsv_update_values(sptrsv_handle_t h, const void* vals, hipStream_t stream
   if (!st && h->blk[0].built) st = gather(h, h->blk[0].ps, h->fwd.vals_buf, stream);
   if (!st && h->blk[1].built) st = gather(h, h->blk[1].ps, h->trn.vals_buf, stream);
   if (!st) st = regather_push(h, stream);
-  if (!st) st = regather_tiles(h, stream);
+  if (!st) st = regather_strips(h, stream);
   h->last_stream = stream;
   const int st2 = order_end(h, stream, capturing);
   return st ? st : st2;
@@ -1904,7 +1904,7 @@ int sptrsv_update_values_batched(sptrsv_handle_t h, const void* const* vals, hip
   if (!st && h->blk[0].built) st = gather(h, h->blk[0].ps, h->fwd.vals_buf, stream);
   if (!st && h->blk[1].built) st = gather(h, h->blk[1].ps, h->trn.vals_buf, stream);
   if (!st) st = regather_push(h, stream);
-  if (!st) st = regather_tiles(h, stream);
+  if (!st) st = regather_strips(h, stream);
   h->last_stream = stream;
   const int st2 = order_end(h, stream, capturing);
   return st ? st : st2;
@@ -2102,12 +2102,11 @@ int sptrsv_tune(sptrsv_handle_t h, const void* b, void* x, hipStream_t stream) {
             cand.push_back(c);
           }
         }
-    if (tile_rule(h))
-      for (int grid : {2 * ncu, 4 * ncu, 8 * ncu}) {
-        Config c{SPTRSV_ALGO_SELF, grp, epl, SPTRSV_SYNC_VALUE, 1, grid, SPTRSV_ASSIGN_STATIC};
-        c.tile = 1;
-        cand.push_back(c);
-      }
+    if (strip_rule(h)) {
+      Config c{SPTRSV_ALGO_SELF, grp, epl, SPTRSV_SYNC_VALUE, 1, 0, SPTRSV_ASSIGN_TICKET};
+      c.strip = 1;
+      cand.push_back(c);
+    }
     for (int rpl : {1, 4})
       cand.push_back({SPTRSV_ALGO_SELF, grp, epl, SPTRSV_SYNC_VALUE, rpl, ncu, SPTRSV_ASSIGN_TICKET});
     cand.push_back({SPTRSV_ALGO_SELF, grp, epl, SPTRSV_SYNC_FLAG, 1, ncu, SPTRSV_ASSIGN_TICKET});

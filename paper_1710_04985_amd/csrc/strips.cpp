@@ -1,0 +1,177 @@
+// Host side of the strip schedule: the grid behind a set of offsets, and the
+// shape of the strips.
+#include "strip_grid.hpp"
+
+#include <algorithm>
+#include <cstring>
+
+namespace sptrsv {
+namespace {
+
+struct Off {
+  int a, b, c;   // the entry lies a, b, c grid steps back (lexicographically positive in c, b, a)
+};
+
+// Strides and entry steps from the distinct offsets.
+bool read_strides(const std::vector<int>& d, int n, int attempt, StripGrid& g,
+                  std::vector<Off>& offs) {
+  offs.clear();
+  g.sy = g.sz = std::max(1, n);
+  if (d.empty() || (d.size() == 1 && d[0] == 1)) {      // independent rows, or one chain
+    if (attempt) return false;
+    g.nx = n;
+    g.ny = g.nz = 1;
+    if (!d.empty()) offs.push_back({1, 0, 0});
+    return true;
+  }
+  size_t at = d[0] == 1 ? 1 : 0;
+  // the entries one line back: a run of at most three consecutive offsets
+  size_t end = at + 1;
+  while (end < d.size() && d[end] == d[end - 1] + 1) ++end;
+  const size_t m = end - at;
+  if (m > 3 || (attempt && m != 2)) return false;
+  const int sy = d[at + (m == 3 ? 1 : m == 2 ? attempt : 0)];
+  if (sy < 2) return false;
+  int sz = 0;
+  if (end < d.size()) {
+    // the entries one plane back, centred on the plane stride
+    sz = d[end + (d.size() - end) / 2];
+    if (sz % sy || sz < 2 * sy) return false;
+  }
+  for (int v : d) {
+    if (v == 1) {
+      offs.push_back({1, 0, 0});
+    } else if (v >= sy - 1 && v <= sy + 1) {
+      offs.push_back({v - sy, 1, 0});
+    } else {
+      bool ok = false;
+      for (int b = -1; b <= 1 && !ok && sz; ++b)
+        for (int a = -1; a <= 1 && !ok; ++a)
+          if (static_cast<int64_t>(sz) + static_cast<int64_t>(b) * sy + a == v) {
+            offs.push_back({a, b, 1});
+            ok = true;
+          }
+      if (!ok) return false;
+    }
+  }
+  g.sy = sy;
+  g.nx = sy;
+  if (sz) {
+    g.sz = sz;
+    g.ny = sz / sy;
+    g.nz = (n + sz - 1) / sz;
+  } else {
+    g.ny = (n + sy - 1) / sy;
+    g.sz = sy * g.ny;
+    g.nz = 1;
+  }
+  return true;
+}
+
+int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// Fills in the shape's tables (ghost lines, published lanes, farthest steps);
+// false if they do not fit.
+bool shape_tables(const std::vector<Off>& offs, StripGrid& g) {
+  const int TU = 1 << g.lu, TV = 1 << g.lv;
+  g.gu = g.gv = 0;
+  g.dmax = 1;
+  struct Back {
+    int u, v;
+  };
+  std::vector<Back> back;
+  for (const Off& o : offs) {
+    const int c1 = o.a + g.al * o.b + g.be * o.c, c2 = o.b + g.ga * o.c, c3 = o.c;
+    const int u = g.axis == 0 ? c2 : c1, v = g.axis == 2 ? c2 : c3;
+    g.gu = std::max(g.gu, u);
+    g.gv = std::max(g.gv, v);
+    g.dmax = std::max(g.dmax, c1 + c2 + c3);
+    back.push_back({u, v});
+  }
+  if (g.dmax > kStripMaxBack || (TU + g.gu) * (TV + g.gv) > 255) return false;
+  std::memset(g.ghost, 255, sizeof(g.ghost));
+  std::memset(g.pub, -1, sizeof(g.pub));
+  std::memset(g.gcol, 0, sizeof(g.gcol));
+  std::vector<char> need((TU + g.gu) * (TV + g.gv), 0);
+  for (int v = 0; v < TV; ++v)
+    for (int u = 0; u < TU; ++u)
+      for (const Back& k : back)
+        if (u < k.u || v < k.v) need[(u - k.u + g.gu) + (v - k.v + g.gv) * (TU + g.gu)] = 1;
+  g.nghost = 0;
+  for (size_t q = 0; q < need.size(); ++q)
+    if (need[q]) {
+      if (g.nghost == kMaxGhosts) return false;
+      g.gcol[g.nghost] = static_cast<unsigned char>(q);
+      g.ghost[q] = static_cast<unsigned char>(g.nghost++);
+    }
+  g.npub = 0;
+  for (int l = 0; l < TU * TV; ++l)
+    if ((l & (TU - 1)) >= TU - g.gu || (l >> g.lu) >= TV - g.gv) g.pub[l] = static_cast<signed char>(g.npub++);
+  return true;
+}
+
+}  // namespace
+
+bool strip_infer(const std::vector<int>& offsets, int n, bool upper, int attempt, StripGrid* out) {
+  StripGrid g;
+  std::vector<Off> offs;
+  if (offsets.size() > kStripMaxOffsets || n < 1 || n >= (1 << 30)) return false;
+  if (!read_strides(offsets, n, attempt, g, offs)) return false;
+  if (static_cast<int64_t>(g.sy) * g.ny > (1ll << 30)) return false;
+  g.n = n;
+  g.upper = upper ? 1 : 0;
+  for (const Off& o : offs) {
+    if (o.c == 0 && o.b == 1) g.al = std::max(g.al, -o.a);
+    if (o.c == 1) g.ga = std::max(g.ga, -o.b);
+  }
+  for (const Off& o : offs)
+    if (o.c == 1) g.be = std::max(g.be, -(o.a + g.al * o.b));
+  const int64_t ext[3] = {g.nx + static_cast<int64_t>(g.al) * (g.ny - 1) +
+                              static_cast<int64_t>(g.be) * (g.nz - 1),
+                          g.ny + static_cast<int64_t>(g.ga) * (g.nz - 1), g.nz};
+  if (ext[0] > (1 << 30) || ext[1] > (1 << 30)) return false;
+  // Shape: every shape walks the same chain of steps (one per level), and
+  // waits one hop, worth about ten steps, per strip that the chain crosses.
+  // What differs besides is the work on lanes without a row: counted here as
+  // steps of all strips over the wavefronts that share them.  Walking along x
+  // (axis 0) reads b and writes x in order, so the others have to gain a
+  // quarter.
+  StripGrid best;
+  double best_cost = 0;
+  bool found = false;
+  for (int axis = 0; axis < 3; ++axis) {
+    if ((axis == 1 && g.ny == 1) || (axis == 2 && g.nz == 1)) continue;
+    const int64_t eu = axis == 0 ? ext[1] : ext[0], ev = axis == 2 ? ext[1] : ext[2];
+    for (int lu = 0; lu <= 6; ++lu) {
+      g.axis = axis;
+      g.lu = lu;
+      g.lv = 6 - lu;
+      if (ev == 1 && g.lv > 0) continue;
+      const int64_t nbu = ceil_div(eu, 1 << g.lu), nbv = ceil_div(ev, 1 << g.lv);
+      if (nbu * nbv > static_cast<int64_t>(n) / 16 + 64 || !shape_tables(offs, g)) continue;
+      const int64_t len = axis == 0 ? g.nx : axis == 1 ? g.ny : g.nz;
+      const double steps = static_cast<double>(nbu * nbv) *
+                           static_cast<double>(len + std::min<int64_t>(eu, 1 << g.lu) +
+                                               std::min<int64_t>(ev, 1 << g.lv) - 2 + g.dmax);
+      double cost = static_cast<double>(ext[0] + ext[1] + ext[2]) +
+                    10.0 * static_cast<double>(nbu + nbv - 2) + steps / 512;
+      if (axis != 0) cost *= 1.25;
+      g.nbu = static_cast<int>(nbu);
+      g.nbv = static_cast<int>(nbv);
+      if (!found || cost < best_cost) {
+        found = true;
+        best_cost = cost;
+        best = g;
+      }
+    }
+  }
+  if (!found) return false;
+  best.stride = best.axis == 0   ? 1
+                : best.axis == 1 ? best.sy - best.al
+                                 : best.sz - best.ga * best.sy + best.al * best.ga - best.be;
+  if (upper) best.stride = -best.stride;
+  *out = best;
+  return true;
+}
+
+}  // namespace sptrsv

@@ -1,0 +1,113 @@
+// CPU model of the strip form's geometry and LDS ring, for patterns given as
+// CSR: walks every strip as the solve kernel does, with row numbers in place
+// of values, and checks that every entry reads its own dependency.
+#include <algorithm>
+#include <cstdint>
+#include <cstdlib>
+#include <set>
+#include <vector>
+
+#include "strip_grid.hpp"
+
+using namespace sptrsv;
+
+namespace {
+
+// `lead`: how many steps ahead of the solver the ghost values are brought in
+int walk(const StripGrid& g, const int* rp, const int* ci, int lead) {
+  const int TU = 1 << g.lu, TV = 1 << g.lv;
+  struct Strip {
+    int bu, bv, first, end;
+  };
+  std::vector<Strip> strips;
+  for (int bv = 0; bv < g.nbv; ++bv)
+    for (int bu = 0; bu < g.nbu; ++bu) {
+      int first = INT32_MAX, end = INT32_MIN;
+      for (int l = 0; l < 64; ++l) {
+        const int u = bu * TU + (l & (TU - 1)), v = bv * TV + (l >> g.lu);
+        int lo, hi;
+        strip_line(g, u, v, &lo, &hi);
+        if (hi > lo) {
+          first = std::min(first, lo + u + v);
+          end = std::max(end, hi + u + v);
+        }
+      }
+      if (end > first) strips.push_back({bu, bv, first - g.dmax, end});
+    }
+  std::stable_sort(strips.begin(), strips.end(),
+                   [](const Strip& a, const Strip& b) { return a.bu + a.bv < b.bu + b.bv; });
+  std::vector<char> solved(g.n, 0);
+  for (const Strip& s : strips) {
+    std::vector<int> ring(kRingSteps * kRingCols, -1);
+    std::vector<int> lo(64), hi(64), glo(64, 0), ghi(64, 0), gu(64), gv(64);
+    for (int l = 0; l < 64; ++l)
+      strip_line(g, s.bu * TU + (l & (TU - 1)), s.bv * TV + (l >> g.lu), &lo[l], &hi[l]);
+    for (int q = 0; q < g.nghost; ++q) {
+      const int W = TU + g.gu;
+      gu[q] = s.bu * TU + g.gcol[q] % W - g.gu;
+      gv[q] = s.bv * TV + g.gcol[q] / W - g.gv;
+      if (gu[q] < 0 || gv[q] < 0) continue;
+      strip_line(g, gu[q], gv[q], &glo[q], &ghi[q]);
+      if (ghi[q] > glo[q] && g.pub[(gu[q] & (TU - 1)) | ((gv[q] & (TV - 1)) << g.lu)] < 0) return 1;
+    }
+    int brought = 0;
+    for (int step = 0; step < s.end - s.first; ++step) {
+      for (; brought < step + lead; ++brought)
+        for (int q = 0; q < g.nghost; ++q) {
+          const int w = brought + s.first - gu[q] - gv[q];
+          if (w < glo[q] || w >= ghi[q]) continue;
+          const int r = strip_row(g, StripPoint{gu[q], gv[q], w});
+          if (r < 0 || !solved[r]) return 2;          // from an earlier strip, and solved
+          ring[(brought % kRingSteps) * kRingCols + 64 + q] = r;
+        }
+      std::vector<int> now(64, -1);
+      for (int l = 0; l < 64; ++l) {
+        const int u = s.bu * TU + (l & (TU - 1)), v = s.bv * TV + (l >> g.lu);
+        const int w = step + s.first - u - v;
+        if (w < lo[l] || w >= hi[l]) continue;
+        const int r = strip_row(g, StripPoint{u, v, w});
+        if (r < 0 || r != strip_row(g, StripPoint{u, v, lo[l]}) + (w - lo[l]) * g.stride) return 3;
+        for (int e = rp[r]; e < rp[r + 1]; ++e) {
+          if (ci[e] == r) continue;
+          const StripPoint t = strip_point(g, ci[e]);
+          const int back = step - (t.u + t.v + t.w - s.first);
+          const int du = t.u - s.bu * TU, dv = t.v - s.bv * TV;
+          if (back < 1 || back > g.dmax || du >= TU || dv >= TV || du < -g.gu || dv < -g.gv)
+            return 4;                                 // the library keeps such a pattern row-wise
+          int col = du >= 0 && dv >= 0 ? du | (dv << g.lu)
+                                       : g.ghost[(du + g.gu) + (dv + g.gv) * (TU + g.gu)];
+          if (du < 0 || dv < 0) {
+            if (col >= kMaxGhosts) return 5;
+            col += 64;
+          }
+          if (ring[((step - back) % kRingSteps) * kRingCols + col] != ci[e]) return 6;
+        }
+        now[l] = r;
+      }
+      for (int l = 0; l < 64; ++l)
+        if (now[l] >= 0) {
+          ring[(step % kRingSteps) * kRingCols + l] = now[l];
+          if (solved[now[l]]) return 7;
+          solved[now[l]] = 1;
+        }
+    }
+  }
+  for (char c : solved)
+    if (!c) return 8;
+  return 0;
+}
+
+}  // namespace
+
+// 0: every check held; > 0: the check that failed; -1: no grid
+extern "C" int check_strips(int n, const int* rp, const int* ci, int upper, int attempt) {
+  std::set<int> d;
+  for (int i = 0; i < n; ++i)
+    for (int e = rp[i]; e < rp[i + 1]; ++e)
+      if (ci[e] != i) d.insert(std::abs(ci[e] - i));
+  StripGrid g;
+  if (!strip_infer(std::vector<int>(d.begin(), d.end()), n, upper != 0, attempt, &g)) return -1;
+  if (g.nghost > kMaxGhosts || g.dmax > kStripMaxBack) return 9;
+  if (const int rc = walk(g, rp, ci, 0 + 1)) return rc;
+  return walk(g, rp, ci, kRingSteps - kStripMaxBack);
+}

@@ -1,0 +1,60 @@
+"""The strip form's grids, strips and LDS ring on the CPU: every row on one
+line, every entry at the ring place the kernel would read it from, for ghost
+values brought in as late and as early as the kernel may."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import workloads as W
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1710_04985_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def check(tmp_path_factory):
+    out = tmp_path_factory.mktemp("strips") / "strip_check.so"
+    subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-I", CSRC,
+                    os.path.join(ROOT, "tests", "cpp", "strip_check.cpp"),
+                    os.path.join(CSRC, "strips.cpp"), "-o", str(out)], check=True)
+    lib = ctypes.CDLL(str(out))
+
+    def run(T, attempt=0, cut=0):
+        n = T.n - cut                                   # a leading (lower) part: a cut last line
+        rp = np.ascontiguousarray(T.row_ptr[:n + 1], np.int32)
+        ci = np.ascontiguousarray(T.col_idx[:rp[-1]], np.int32)
+        p = lambda a: a.ctypes.data_as(ctypes.c_void_p)
+        return lib.check_strips(n, p(rp), p(ci), int(T.upper), attempt)
+    return run
+
+
+GRIDS = [((1, 1), 5), ((2, 3), 5), ((64, 64), 5), ((65, 63), 5), ((63, 130), 9), ((200, 7), 9),
+         ((5, 300), 9), ((9, 7, 5), 7), ((33, 20, 17), 7), ((70, 3, 40), 7), ((2, 2, 50), 7),
+         ((16, 16, 200), 7), ((12, 11, 13), 27), ((4, 33, 6), 27), ((40, 5, 9), 27), ((9, 8, 120), 27)]
+
+
+@pytest.mark.parametrize("upper", [False, True])
+@pytest.mark.parametrize("dims,points", GRIDS, ids=["x".join(map(str, g)) + "_%d" % p for g, p in GRIDS])
+def test_grids(check, dims, points, upper):
+    T = W.stencil_triangle(dims, points, upper=upper)
+    assert check(T) == 0
+    if not upper and T.n > 10:
+        assert check(T, cut=3) == 0
+
+
+def test_patterns_that_are_no_grid(check):
+    # more offsets than a stencil; offsets no strides explain; entries that
+    # run across the line ends of the grid their offsets suggest
+    assert check(W.powerlaw_lower(3000, 1, window=500)) == -1
+    i = np.arange(900)
+
+    def band(offsets):
+        cols = [[r - o for o in sorted(offsets, reverse=True) if r >= o] + [r] for r in i]
+        rp = np.concatenate([[0], np.cumsum([len(c) for c in cols])]).astype(np.int32)
+        return W.Triangle(900, rp, np.concatenate(cols).astype(np.int32), np.ones(rp[-1]))
+    assert check(band([2, 5, 7])) != 0
+    assert check(band([1, 30])) == 4
+    assert check(band([29, 30]), attempt=1) in (0, 4)
