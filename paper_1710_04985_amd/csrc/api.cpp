@@ -627,12 +627,7 @@ ChunkEntry* get_col_chunks(PlanState& ps, int group, int epl, int ncols, const C
 }
 
 int ensure_xp(sptrsv_handle_t h, int64_t elems);
-int strip_occupancy(sptrsv_handle_t h, const PlanState& ps);
-
-// Values of the solution buffer a strip solve uses.
-int64_t strip_values(const PlanState& ps) {
-  return ps.strips.npub + static_cast<int64_t>(kDumpSlot) * ps.strips.nstrips;
-}
+int strip_occupancy(sptrsv_handle_t h, const PlanState& ps, int nrhs);
 
 // Entries per lane of the default lane rule, the one the strip-ordered copy is built
 // for.
@@ -724,6 +719,9 @@ Config resolve_multi(sptrsv_handle_t h, int nrhs) {
   // becomes the self-scheduled solve here
   if (h->algo == SPTRSV_ALGO_AUTO && !h->tuned && c.algo == SPTRSV_ALGO_BLOCK)
     c.algo = SPTRSV_ALGO_SELF;
+  // strips take any number of columns (128^3, 16 columns: 983 us row-wise,
+  // 420 us in strips); rows per lane group set explicitly ask for the row-wise form
+  c.strip = c.strip && h->mrows == 0;
   // options left unset, by the column count (where sptrsv_tune_multi's picks
   // changed on 128^3 and ILU(0) 96^3): 2, 4, 8 wavefronts per CU from 2, 8,
   // 16 columns; XCD-regional lists up to 4 columns, round-robin beyond
@@ -832,10 +830,10 @@ void build_strip_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t
     if (!st) {
       const hipError_t e = h->dtype == SPTRSV_F64 ? launch_strip_gather<double>(ps.d, ps.strips, s)
                                                   : launch_strip_gather<float>(ps.d, ps.strips, s);
-      if (e != hipSuccess || ensure_xp(h, strip_values(ps)) || hipStreamSynchronize(s) != hipSuccess)
+      if (e != hipSuccess || ensure_xp(h, strip_values(ps.strips, 1)) || hipStreamSynchronize(s) != hipSuccess)
         free_strips(ps.strips);
       else
-        (void)strip_occupancy(h, ps);
+        (void)strip_occupancy(h, ps, 1);
     }
     break;
   }
@@ -920,12 +918,12 @@ int persistent_grid(sptrsv_handle_t h, int kind, int grid, int nchunks) {
   return std::max(1, std::min(g, need));
 }
 
-int strip_occupancy(sptrsv_handle_t h, const PlanState& ps) {
-  const auto key = std::make_pair(&ps == &h->trn ? 17 : 16, 64);
+int strip_occupancy(sptrsv_handle_t h, const PlanState& ps, int nrhs) {
+  const auto key = std::make_pair((&ps == &h->trn ? 18 : 16) + (nrhs > 1), 64);
   auto it = h->occupancy.find(key);
   if (it != h->occupancy.end()) return it->second;
-  const int per_cu = h->dtype == SPTRSV_F64 ? strip_blocks_per_cu<double>(ps.strips)
-                                            : strip_blocks_per_cu<float>(ps.strips);
+  const int per_cu = h->dtype == SPTRSV_F64 ? strip_blocks_per_cu<double>(ps.strips, nrhs)
+                                            : strip_blocks_per_cu<float>(ps.strips, nrhs);
   h->occupancy[key] = per_cu;
   return per_cu;
 }
@@ -1120,22 +1118,24 @@ int solve_column(sptrsv_handle_t h, PlanState& ps, const Config& c, const void* 
   return kOk;
 }
 
-// Strip-wise self-scheduled solve, one right-hand side.  Strips are claimed
-// from a ticket, so the grid may fill the GPU.
+// Strip-wise self-scheduled solve.  Strips are claimed from a ticket, so the
+// grid may fill the GPU.
 template <typename T>
-int solve_strips(sptrsv_handle_t h, PlanState& ps, const Config& c, const void* b, void* x,
-                void* xp, hipStream_t s, const SolveExt& ext) {
+int solve_strips(sptrsv_handle_t h, PlanState& ps, const void* b, void* x, int nrhs, int ld,
+                 void* xp, hipStream_t s, const SolveExt& ext) {
   StripSolveArgs a;
   a.strips = &ps.strips;
   a.scratch = h->scratch;
   a.b = b;
   a.x = x;
   a.xp = xp;
+  a.nrhs = nrhs;
+  a.ld = ld;
   a.spin_limit = h->spin_limit;
   a.coop = h->coop;
-  const int cap = strip_occupancy(h, ps) * h->num_cu;
-  a.grid = std::max(1, std::min(cap, ps.strips.nstrips));
-  if (launch_fill_sentinel<T>(static_cast<T*>(xp), ps.strips.npub, h->scratch.arrive, s) != hipSuccess)
+  const int64_t tasks = static_cast<int64_t>(ps.strips.nstrips) * nrhs;
+  a.grid = static_cast<int>(std::min<int64_t>(strip_occupancy(h, ps, nrhs) * h->num_cu, tasks));
+  if (launch_fill_sentinel<T>(static_cast<T*>(xp), ps.strips.npub * nrhs, h->scratch.arrive, s) != hipSuccess)
     return kErrHip;
   hipEvent_t stop;
   timing_begin(h, s, &stop, ext.no_alloc);
@@ -1152,14 +1152,17 @@ int solve_impl(sptrsv_handle_t h, PlanState& ps, const Config& c_in, const void*
   if (n == 0 || nrhs == 0) return kOk;
   const bool multi = nrhs > 1;
   if (is_column(c_in.algo) && !multi) return solve_column<T>(h, ps, c_in, b, x, s, ext);
-  if (c_in.strip && !multi && ps.strips.nstrips) {
+  const int64_t tasks = static_cast<int64_t>(ps.strips.nstrips) * nrhs;
+  if (c_in.strip && tasks > 0 && tasks < INT32_MAX / kDumpSlot && !(multi && ext.no_alloc)) {
     // a fixed buffer too small for the published values leaves the row-wise form
-    if (!ext.xp) {
-      if (const int st = ensure_xp(h, strip_values(ps))) return st;
-      return solve_strips<T>(h, ps, c_in, b, x, h->xp, s, ext);
+    const int64_t need = strip_values(ps.strips, nrhs);
+    void* xp = ext.xp;
+    if (!xp) {
+      if (const int st = ensure_xp(h, need)) return st;
+      xp = h->xp;
     }
-    if (strip_values(ps) * static_cast<int64_t>(h->vb) <= ext.xp_bytes)
-      return solve_strips<T>(h, ps, c_in, b, x, ext.xp, s, ext);
+    if (!ext.xp || need * static_cast<int64_t>(h->vb) <= ext.xp_bytes)
+      return solve_strips<T>(h, ps, b, x, nrhs, ld, xp, s, ext);
   }
   // several right-hand sides under a column-wise schedule: row-wise, self-scheduled
   Config c = c_in;
@@ -2197,6 +2200,11 @@ int sptrsv_tune_multi(sptrsv_handle_t h, int32_t nrhs, int32_t ld, const void* B
   std::vector<Config> cand;
   const bool self_ok = h->algo == SPTRSV_ALGO_AUTO || h->algo == SPTRSV_ALGO_SELF ||
                        is_column(h->algo);
+  if (self_ok && strip_rule(h)) {
+    Config c{SPTRSV_ALGO_SELF, 0, 4, SPTRSV_SYNC_VALUE, 1, 0, SPTRSV_ASSIGN_TICKET};
+    c.strip = 1;
+    cand.push_back(c);
+  }
   if (self_ok)
     for (int grid : {ncu / 2, ncu, 2 * ncu, 4 * ncu, 8 * ncu})
       for (int as : {SPTRSV_ASSIGN_STATIC, SPTRSV_ASSIGN_XCD})

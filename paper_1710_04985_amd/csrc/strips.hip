@@ -309,6 +309,8 @@ k_strip_gather(DevStrips d, const T* __restrict__ off_val, const T* __restrict__
 
 template <typename T> struct SArgs {
   int nstrips;
+  int nrhs;
+  int64_t ld;        // elements between the columns of b and x
   int64_t npub;
   const StripInfo* info;
   const StripLane* lane;
@@ -407,6 +409,13 @@ template <int N, int I = 0, typename F> __device__ __forceinline__ void unroll(F
 // every other schedule.  All loads go to addresses clamped to the line's own
 // run instead of under a mask, so that the number in flight is fixed and
 // waiting for one step's never waits for a later step's.
+//
+// Several right-hand sides: a task is one column of one strip, since a strip
+// holds up its neighbours by its steps' latency, which more columns per task
+// lengthen, while other columns' strips fill the other compute units.  Whole
+// solves, us, 128^3 triangle, 16 columns, 1 / 2 / 3 / 4 columns per task:
+// 422 / 540 / 513 / 592 (row-wise: 983); ILU(0) 96^3, FP32, 3 columns:
+// 76 / 92 / 138 / 135 (332).
 constexpr int kStripThreads = 256;
 constexpr int kBlock = 8;                    // steps that wavefronts 2 and 3 take at once
 constexpr int kBCols = 65;                   // row of the b ring, padded against bank conflicts
@@ -431,8 +440,13 @@ __global__ void __launch_bounds__(kStripThreads) k_strip(SArgs<T> a) {
   for (;;) {
     if (threadIdx.x == 0) cnt.strip = atomicAdd(a.ticket, 1);
     __syncthreads();
-    const int p = wave_uniform(cnt.strip);
-    if (p >= a.nstrips) return;                        // the whole workgroup
+    const int task = wave_uniform(cnt.strip);
+    if (task >= a.nstrips * a.nrhs) return;            // the whole workgroup
+    // several right-hand sides: the columns of a strip follow one another
+    const int p = task / a.nrhs, column = task - p * a.nrhs;
+    const T* const b = a.b + column * a.ld;
+    T* const x = a.x + column * a.ld;
+    T* const xp = a.xp + column * a.npub;
     const StripInfo inf = a.info[p];
     const StripLane* lanes = a.lane + static_cast<int64_t>(p) * 64;
     const int steps = wave_uniform(inf.steps), stride = wave_uniform(inf.stride),
@@ -451,7 +465,8 @@ __global__ void __launch_bounds__(kStripThreads) k_strip(SArgs<T> a) {
       const char* tail = a.tail + rec0 * (NT * 256);
       // lanes that nobody reads publish into a line of the strip's own, so
       // that the store is unconditional and counted like the loads
-      T* pub = a.xp + (l.pub >= 0 ? inf.pub0 + l.pub : a.npub + p * static_cast<int64_t>(kDumpSlot));
+      T* pub = l.pub >= 0 ? xp + inf.pub0 + l.pub
+                          : a.xp + a.npub * a.nrhs + task * static_cast<int64_t>(kDumpSlot);
       const int64_t pub_step = l.pub >= 0 ? npub : 0;
       unsigned w[D][NW];
       auto fetch = [&](auto k, int s) {
@@ -543,7 +558,7 @@ __global__ void __launch_bounds__(kStripThreads) k_strip(SArgs<T> a) {
         const StripLane l = lanes[lane & ((1 << lg) - 1)];
         const int j = lane >> lg, col = 64 + (lane & ((1 << lg) - 1));
         const int glo = l.glo, ghi = l.glo + (l.glen > 0 ? l.glen - 1 : 0);
-        const T* gp = a.xp + l.gpos;
+        const T* gp = xp + l.gpos;
         int next = 0, done = 0, idle = 0;     // first step not brought in yet
         bool lost = false;
         auto issue = [&](T (&v)[2], int base) {
@@ -626,7 +641,7 @@ __global__ void __launch_bounds__(kStripThreads) k_strip(SArgs<T> a) {
           for (int i = 0; i < kBlock; ++i) {
             const T xi = xout[(i * L + lane / kBlock) * kXCols + j];
             if (static_cast<unsigned>(s0 + j - lo[i]) < static_cast<unsigned>(n[i]))
-              a.x[row0[i] + static_cast<int64_t>(s0 + j) * stride] = xi;
+              x[row0[i] + static_cast<int64_t>(s0 + j) * stride] = xi;
           }
         }
         write_counter(&cnt.stored, INT32_MAX);
@@ -637,7 +652,7 @@ __global__ void __launch_bounds__(kStripThreads) k_strip(SArgs<T> a) {
 #pragma unroll
           for (int i = 0; i < kBlock; ++i) {
             const int sc = min(max(s0 + j, lo[i]), lo[i] + max(n[i], 1) - 1);
-            v[k][i] = a.b[row0[i] + static_cast<int64_t>(sc) * stride];
+            v[k][i] = b[row0[i] + static_cast<int64_t>(sc) * stride];
           }
         };
         unroll<P>([&](auto k) {
@@ -660,14 +675,19 @@ __global__ void __launch_bounds__(kStripThreads) k_strip(SArgs<T> a) {
   }
 }
 
-template <typename T> const void* strip_fn(const DevStrips& t) {
+// The kernel for a copy.  Several right-hand sides are computed as the
+// one-lane solve computes each (one partial sum).
+template <typename T> const void* strip_fn(const DevStrips& t, int nrhs) {
+  const int acc = nrhs > 1 ? 1 : t.acc;
 #define SPTRSV_STRIP(E, A, D) \
-  if (t.entries == E && t.acc == A) return reinterpret_cast<const void*>(k_strip<T, E, A, D>)
+  if (t.entries == E && acc == A) return reinterpret_cast<const void*>(k_strip<T, E, A, D>)
   SPTRSV_STRIP(2, 1, 16);
   SPTRSV_STRIP(3, 1, 16);
   SPTRSV_STRIP(4, 1, 16);
   SPTRSV_STRIP(13, 4, 4);
   SPTRSV_STRIP(15, 4, 4);
+  SPTRSV_STRIP(13, 1, 4);
+  SPTRSV_STRIP(15, 1, 4);
 #undef SPTRSV_STRIP
   return nullptr;
 }
@@ -868,6 +888,8 @@ template <typename T> hipError_t launch_strip_solve(const StripSolveArgs& sa, hi
   if (t.nstrips == 0) return hipSuccess;
   SArgs<T> a;
   a.nstrips = t.nstrips;
+  a.nrhs = sa.nrhs;
+  a.ld = sa.ld;
   a.npub = t.npub;
   a.info = t.info;
   a.lane = t.lane;
@@ -879,15 +901,15 @@ template <typename T> hipError_t launch_strip_solve(const StripSolveArgs& sa, hi
   a.status = sa.scratch.status;
   a.ticket = sa.scratch.arrive;
   a.spin_limit = sa.spin_limit;
-  const void* fn = strip_fn<T>(t);
+  const void* fn = strip_fn<T>(t, sa.nrhs);
   if (!fn) return hipErrorInvalidValue;
   void* args[] = {&a};
   if (sa.coop) return hipLaunchCooperativeKernel(fn, dim3(sa.grid), dim3(kStripThreads), args, 0, s);
   return hipLaunchKernel(fn, dim3(sa.grid), dim3(kStripThreads), args, 0, s);
 }
 
-template <typename T> int strip_blocks_per_cu(const DevStrips& t) {
-  const void* fn = strip_fn<T>(t);
+template <typename T> int strip_blocks_per_cu(const DevStrips& t, int nrhs) {
+  const void* fn = strip_fn<T>(t, nrhs);
   int nb = 0;
   if (!fn || hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, kStripThreads, 0) != hipSuccess) return 1;
   return nb > 0 ? nb : 1;
@@ -896,7 +918,7 @@ template <typename T> int strip_blocks_per_cu(const DevStrips& t) {
 #define SPTRSV_INSTANTIATE(T)                                                                 \
   template hipError_t launch_strip_gather<T>(const DevPlan&, const DevStrips&, hipStream_t);  \
   template hipError_t launch_strip_solve<T>(const StripSolveArgs&, hipStream_t);              \
-  template int strip_blocks_per_cu<T>(const DevStrips&);
+  template int strip_blocks_per_cu<T>(const DevStrips&, int);
 
 SPTRSV_INSTANTIATE(double)
 SPTRSV_INSTANTIATE(float)

@@ -89,18 +89,25 @@ hipError_t launch_strip_lanes(const DevChunks& c, unsigned char* lanes_lg, hipSt
 template <typename T> hipError_t launch_strip_gather(const DevPlan& p, const DevStrips& t,
                                                      hipStream_t s);
 
+// values of the solution buffer a solve uses; the first npub * nrhs of them are
+// filled with the sentinel before it
+inline int64_t strip_values(const DevStrips& t, int nrhs) {
+  return (t.npub + static_cast<int64_t>(kDumpSlot) * t.nstrips) * nrhs;
+}
+
 struct StripSolveArgs {
   const DevStrips* strips;
   DevScratch scratch;
   const void* b;
   void* x;
-  void* xp;          // [npub] published values, filled with the sentinel, and kDumpSlot
-                     // more per strip
+  void* xp;          // [strip_values]
+  int nrhs = 1;
+  int64_t ld = 0;    // elements between the columns of b and x
   int spin_limit = 1 << 22;
   int coop = 0;
   int grid = 1;      // four-wavefront workgroups
 };
 template <typename T> hipError_t launch_strip_solve(const StripSolveArgs& a, hipStream_t s);
-template <typename T> int strip_blocks_per_cu(const DevStrips& t);
+template <typename T> int strip_blocks_per_cu(const DevStrips& t, int nrhs);
 
 }  // namespace sptrsv

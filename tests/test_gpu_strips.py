@@ -201,3 +201,30 @@ def test_watchdog_and_residency(sp, coop):
     for _ in range(3):
         assert bits_equal(h.solve(b), ref)
     h.status()
+
+
+@pytest.mark.parametrize("nrhs", [2, 3, 16, 33])
+@pytest.mark.parametrize("dims,points", [((65, 40), 5), ((40, 33), 9), ((17, 9, 20), 7), ((9, 8, 10), 27)])
+def test_several_right_hand_sides(sp, dims, points, nrhs):
+    """Every column equals the one-lane-per-row solve bit for bit, plain and
+    transposed, with a column stride beyond n and in place."""
+    T = _varied(W.stencil_triangle(dims, points), 6)
+    for dt in (torch.float64, torch.float32):
+        d = dev_tri(T, dt)
+        wide = torch.zeros(nrhs, T.n + 7, dtype=dt, device="cuda:0")
+        for r in range(nrhs):
+            wide[r, :T.n] = dev(W.uniform_vector(T.n, 40 + r), dt)
+        B = wide[:, :T.n]
+        h = sp.Handle(*d).configure(algo=2)
+        one = sp.Handle(*d).configure(algo=1, group=1)
+        for tr in (False, True):
+            X = h.solve_multi(B, transpose=tr)
+            h.status()
+            for r in range(nrhs):
+                b = B[r].contiguous()
+                assert bits_equal(X[r].contiguous(), one.solve_t(b) if tr else one.solve(b)), (tr, r)
+        ref = h.solve_multi(B)
+        h.solve_multi(B, out=B)
+        h.status()
+        assert bits_equal(B.contiguous(), ref.contiguous())
+        assert not wide[:, T.n:].any()                 # nothing written past the columns
