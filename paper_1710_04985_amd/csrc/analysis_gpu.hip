@@ -9,6 +9,7 @@
 
 #include "analysis.hpp"
 #include "analysis_gpu.hpp"
+#include "device_common.hpp"
 
 namespace sptrsv {
 namespace {
@@ -16,6 +17,19 @@ namespace {
 enum : int { kFlagBad = 1, kFlagUnsorted = 2, kFlagTimeout = 4 };
 
 __device__ __forceinline__ int bitlen(unsigned v) { return v ? 32 - __builtin_clz(v) : 0; }
+
+// Raises *out to the largest v of the workgroup (256 threads, all of them):
+// one atomic per workgroup at most, and none that would change nothing.
+__device__ __forceinline__ void block_max(int v, int* out) {
+  __shared__ int wave[4];
+  for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
+  if ((threadIdx.x & 63) == 0) wave[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    v = max(max(wave[0], wave[1]), max(wave[2], wave[3]));
+    if (v > __hip_atomic_load(out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(out, v);
+  }
+}
 
 // One row per thread: bounds, column range and side, strictly increasing
 // columns, one diagonal (unless unit), dependency count.  Any irregularity
@@ -52,13 +66,49 @@ __global__ void __launch_bounds__(256) k_check(int n, int64_t nnz, const int* __
   }
   if (blockIdx.x == 0 && threadIdx.x == 0 && (rp[0] != 0 || rp[n] != nnz)) f |= kFlagBad;
   if (f) atomicOr(flags, f);
-  if (ml) atomicMax(maxlen, ml);
+  block_max(ml, maxlen);
 }
 
 __global__ void __launch_bounds__(256) k_fill_int(int* p, int64_t count, int v) {
   const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
   for (int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; t < count; t += stride)
     p[t] = v;
+}
+
+// Levels of rows on grids without gaps: each row is given the level that its
+// place in the grid calls for, and checked against its dependencies, which
+// are given theirs the same way.  The recurrence has one solution, so levels
+// that satisfy it at every row are the levels; otherwise *differ is set and
+// nothing else here counts.  Bound by the pattern's bytes (128^3 7-point:
+// 30 us; the sweep k_levels 2550 us, a hop per level).
+__global__ void __launch_bounds__(256)
+k_grid_levels(int n, const int* __restrict__ rp, const int* __restrict__ col,
+              const StripGrid* __restrict__ grids, int nsys, int* __restrict__ level, int* differ,
+              int* maxlev) {
+  const int stride = gridDim.x * blockDim.x;
+  int top = -1;
+  bool bad = false;
+  for (int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; t < n; t += stride) {
+    const int i = static_cast<int>(t);
+    int lo = 0, hi = nsys - 1;             // the last system with row0 <= i
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (grids[mid].row0 <= i) lo = mid;
+      else hi = mid - 1;
+    }
+    const StripGrid& g = grids[lo];
+    const int want = strip_level(g, i - g.row0);
+    int got = 0;
+    for (int e = rp[i], e1 = rp[i + 1]; e < e1; ++e) {
+      const int j = col[e];
+      if (j != i) got = max(got, strip_level(g, j - g.row0) + 1);
+    }
+    bad |= got != want;
+    level[i] = want;
+    top = max(top, want);
+  }
+  if (bad) __hip_atomic_store(differ, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  block_max(top, maxlev);
 }
 
 // Levels of Sec. 4.1 (0-based), computed without global synchronisation: the
@@ -238,6 +288,10 @@ __global__ void __launch_bounds__(256) k_keys(int n, const int* __restrict__ lev
   }
 }
 
+// Workgroups of the kernels that add up over all rows: each ends with an atomic
+// on one word, about 10 ns apart.
+constexpr int kCheckBlocks = 1024;
+
 // inverse permutation, row length per position, level pointers
 __global__ void __launch_bounds__(256) k_positions(int n, int nlev, const int* __restrict__ pos_row,
                                                    const int* __restrict__ level,
@@ -305,7 +359,7 @@ template <typename T> int dmalloc(T** p, int64_t count) {
 
 struct Temps {
   int* flags = nullptr;
-  int* counters = nullptr;   // [0] max row length, [1] max level, [2] chunk ticket
+  int* counters = nullptr;   // [0] max row length, [1] max level, [2] chunk ticket, [3] grid levels differ
   unsigned long long* key = nullptr;
   unsigned long long* key_s = nullptr;
   int* rows = nullptr;
@@ -315,12 +369,14 @@ struct Temps {
   int* pos_of = nullptr;
   int* cnt = nullptr;
   int* ilev = nullptr;
+  StripGrid* grids = nullptr;
   void* tmp = nullptr;
   ~Temps() {
     for (void* p : {static_cast<void*>(flags), static_cast<void*>(counters), static_cast<void*>(key),
                     static_cast<void*>(key_s), static_cast<void*>(rows), static_cast<void*>(lkey),
                     static_cast<void*>(lkey_s), static_cast<void*>(rows2), static_cast<void*>(pos_of),
-                    static_cast<void*>(cnt), static_cast<void*>(ilev), tmp})
+                    static_cast<void*>(cnt), static_cast<void*>(ilev),
+                    static_cast<void*>(grids), tmp})
       if (p) (void)hipFree(p);
   }
 };
@@ -452,20 +508,22 @@ void free_device_analysis(DeviceAnalysis& a) {
   } while (0)
 
 int device_analysis(int n, int64_t nnz, const int* row_ptr, const int* col, bool upper,
-                    bool unit_diag, int num_cu, hipStream_t s, DeviceAnalysis& out) {
+                    bool unit_diag, int num_cu,
+                    const std::vector<std::vector<StripGrid>>& guesses, hipStream_t s,
+                    DeviceAnalysis& out) {
   out = DeviceAnalysis();
   if (n < 1 || nnz < 0 || nnz > INT32_MAX || n > (1 << 30)) return kErrNotSupported;
   out.n = n;
   Temps tp;
   DALLOC(tp.flags, 1);
-  DALLOC(tp.counters, 3);
+  DALLOC(tp.counters, 4);
   DALLOC(out.depcnt, n);
   DALLOC(out.level, n);
-  int zero2[3] = {0, -1, 0};
+  int zero2[4] = {0, -1, 0, 0};
   int zero = 0;
   DCHK(hipMemcpyAsync(tp.flags, &zero, sizeof(int), hipMemcpyHostToDevice, s));
-  DCHK(hipMemcpyAsync(tp.counters, zero2, 3 * sizeof(int), hipMemcpyHostToDevice, s));
-  k_check<<<blocks(n), 256, 0, s>>>(n, nnz, row_ptr, col, upper, unit_diag, out.depcnt, tp.flags,
+  DCHK(hipMemcpyAsync(tp.counters, zero2, 4 * sizeof(int), hipMemcpyHostToDevice, s));
+  k_check<<<std::min(blocks(n), kCheckBlocks), 256, 0, s>>>(n, nnz, row_ptr, col, upper, unit_diag, out.depcnt, tp.flags,
                                      tp.counters);
   DCHK(hipGetLastError());
   int flags = 0, max_len = 0;
@@ -477,10 +535,24 @@ int device_analysis(int n, int64_t nnz, const int* row_ptr, const int* col, bool
     return kErrNotSupported;
   }
 
-  // levels
-  k_fill_int<<<blocks(n), 256, 0, s>>>(out.level, n, -1);
-  DCHK(hipGetLastError());
-  {
+  // levels: from the grid, if a guess of it holds, else by the sweep
+  int counters[4] = {0, -1, 0, 1};
+  for (const std::vector<StripGrid>& g : guesses) {
+    if (!tp.grids) DALLOC(tp.grids, static_cast<int64_t>(g.size()));
+    DCHK(hipMemcpyAsync(tp.grids, g.data(), g.size() * sizeof(StripGrid), hipMemcpyHostToDevice, s));
+    DCHK(hipMemcpyAsync(tp.counters + 1, zero2 + 1, 3 * sizeof(int), hipMemcpyHostToDevice, s));
+    k_grid_levels<<<std::min(blocks(n), kCheckBlocks), 256, 0, s>>>(
+        n, row_ptr, col, tp.grids, static_cast<int>(g.size()), out.level, tp.counters + 3,
+        tp.counters + 1);
+    DCHK(hipGetLastError());
+    DCHK(hipMemcpyAsync(counters, tp.counters, sizeof(counters), hipMemcpyDeviceToHost, s));
+    DCHK(hipStreamSynchronize(s));
+    if (!counters[3]) break;
+  }
+  if (counters[3]) {
+    DCHK(hipMemcpyAsync(tp.counters + 1, zero2 + 1, 3 * sizeof(int), hipMemcpyHostToDevice, s));
+    k_fill_int<<<blocks(n), 256, 0, s>>>(out.level, n, -1);
+    DCHK(hipGetLastError());
     int per_cu = 0;
     DCHK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_levels, 64, 0));
     const int nch = (n + 63) / 64;
@@ -495,14 +567,13 @@ int device_analysis(int n, int64_t nnz, const int* row_ptr, const int* col, bool
     k_levels<<<grid, 64, 0, s>>>(n, row_ptr, col, upper ? 1 : 0, out.level, tp.flags,
                                  tp.counters + 1, tp.counters + 2, 1 << 24);
     DCHK(hipGetLastError());
-  }
-  int counters[3];
-  DCHK(hipMemcpyAsync(counters, tp.counters, 3 * sizeof(int), hipMemcpyDeviceToHost, s));
-  DCHK(hipMemcpyAsync(&flags, tp.flags, sizeof(int), hipMemcpyDeviceToHost, s));
-  DCHK(hipStreamSynchronize(s));
-  if (flags & kFlagTimeout) {
-    free_device_analysis(out);
-    return kErrTimeout;
+    DCHK(hipMemcpyAsync(counters, tp.counters, sizeof(counters), hipMemcpyDeviceToHost, s));
+    DCHK(hipMemcpyAsync(&flags, tp.flags, sizeof(int), hipMemcpyDeviceToHost, s));
+    DCHK(hipStreamSynchronize(s));
+    if (flags & kFlagTimeout) {
+      free_device_analysis(out);
+      return kErrTimeout;
+    }
   }
   out.max_row_len = counters[0];
   out.nlev = counters[1] + 1;

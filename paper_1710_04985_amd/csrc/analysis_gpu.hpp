@@ -9,6 +9,8 @@
 #include <cstdint>
 #include <vector>
 
+#include "strip_grid.hpp"
+
 namespace sptrsv {
 
 // Device arrays of one analysed triangle (owned by the caller after success;
@@ -37,9 +39,12 @@ struct DeviceAnalysis {
 // nnz beyond its limits): the caller then runs the host analysis, which also
 // produces the exact validation error.  Other errors: kErrHip, kErrOom,
 // kErrTimeout (level kernel spin limit; cannot happen on a valid pattern).
-// Blocking: synchronises `stream`.
+// Blocking: synchronises `stream`.  guesses: readings of the pattern as grids, one per
+// system each (may be empty); levels that a grid explains take one pass.
 int device_analysis(int n, int64_t nnz, const int* row_ptr, const int* col, bool upper,
-                    bool unit_diag, int num_cu, hipStream_t stream, DeviceAnalysis& out);
+                    bool unit_diag, int num_cu,
+                    const std::vector<std::vector<StripGrid>>& guesses, hipStream_t stream,
+                    DeviceAnalysis& out);
 
 void free_device_analysis(DeviceAnalysis& a);
 

@@ -425,6 +425,7 @@ int read_status(sptrsv_handle_t h, hipStream_t s, bool clear) {
 }
 
 int install_device_plan(sptrsv_handle_t h, PlanState& ps, DeviceAnalysis& da, bool upper);
+std::vector<std::vector<StripGrid>> grid_guesses(sptrsv_handle_t h, bool upper);
 void build_strip_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t s);
 
 // Builds the analysis of T^T: rows of T^T are the columns of T; each value is
@@ -439,7 +440,8 @@ int build_transpose(sptrsv_handle_t h, hipStream_t s) {
     int *rT = nullptr, *cT = nullptr, *sT = nullptr;
     int st = device_transpose(n, h->nnz, h->rp_dev, h->col_dev, s, &rT, &cT, &sT);
     DeviceAnalysis da;
-    if (!st) st = device_analysis(n, h->nnz, rT, cT, !h->upper, h->unit, h->num_cu, s, da);
+    if (!st) st = device_analysis(n, h->nnz, rT, cT, !h->upper, h->unit, h->num_cu,
+                                   grid_guesses(h, !h->upper), s, da);
     if (!st)
       st = device_value_sources(n, h->fwd.d.noff, h->fwd.d.off_src, h->fwd.d.diag_src, h->nnz, sT,
                                 da, s);
@@ -750,7 +752,7 @@ bool multi_by_columns(const PlanState& ps, const Config& c) {
 // unused.
 void find_offsets(sptrsv_handle_t h, const int* row_ptr, const int* col, hipStream_t s) {
   h->offsets.clear();
-  if (h->n == 0 || h->fwd.h.max_row_len > kStripMaxEntries) return;
+  if (h->n == 0) return;
   std::vector<int> row0(1, 0);
   if (h->batched)
     for (int ni : h->sys_n) row0.push_back(row0.back() + ni);
@@ -765,7 +767,7 @@ void find_offsets(sptrsv_handle_t h, const int* row_ptr, const int* col, hipStre
   std::copy(row0.begin(), row0.end(), host.begin() + nsys * (kStripTable + 1));
   int* full = buf + static_cast<int64_t>(nsys) * kStripTable;
   if (hipMemcpyAsync(buf, host.data(), words * sizeof(int), hipMemcpyHostToDevice, s) == hipSuccess &&
-      launch_strip_offsets(h->n, row_ptr, col, nsys, full + nsys, buf, full, s) == hipSuccess &&
+      launch_strip_offsets(h->n, h->nnz, row_ptr, col, nsys, full + nsys, buf, full, s) == hipSuccess &&
       hipMemcpyAsync(host.data(), buf, static_cast<size_t>(nsys) * (kStripTable + 1) * sizeof(int),
                      hipMemcpyDeviceToHost, s) == hipSuccess &&
       hipStreamSynchronize(s) == hipSuccess) {
@@ -784,11 +786,38 @@ void find_offsets(sptrsv_handle_t h, const int* row_ptr, const int* col, hipStre
   dfree(buf);
 }
 
+// Reading `attempt` (0, 1) of the offsets as grids, one per system; false: none.
+bool infer_grids(sptrsv_handle_t h, bool upper, int attempt, std::vector<StripGrid>& grids) {
+  const int nsys = static_cast<int>(h->offsets.size());
+  grids.assign(nsys, StripGrid());
+  int at = 0;
+  bool any = nsys > 0 && attempt == 0;
+  for (int k = 0; k < nsys; ++k) {
+    const int nk = h->batched ? h->sys_n[k] : h->n;
+    if (nk > 0) {
+      // systems with one reading keep it on the second attempt
+      if (strip_infer(h->offsets[k], nk, upper, attempt, &grids[k])) any = true;
+      else if (!attempt || !strip_infer(h->offsets[k], nk, upper, 0, &grids[k])) return false;
+    }
+    grids[k].row0 = at;
+    at += nk;
+  }
+  return any;
+}
+
+std::vector<std::vector<StripGrid>> grid_guesses(sptrsv_handle_t h, bool upper) {
+  std::vector<std::vector<StripGrid>> all;
+  for (int attempt = 0; attempt < 2; ++attempt) {
+    std::vector<StripGrid> g;
+    if (infer_grids(h, upper, attempt, g)) all.push_back(std::move(g));
+  }
+  return all;
+}
+
 // The strip-ordered copy of a plan (strips.hpp), if its rows sit on a grid and memory
 // allows; otherwise the plan keeps the row-wise schedules alone.  Blocking.
 void build_strip_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t s) {
   if (h->offsets.empty() || ps.strips.nstrips) return;
-  const int nsys = static_cast<int>(h->offsets.size());
   int err = kOk;
   unsigned char* lanes = nullptr;
   if (ps.h.max_row_len > kStripLaneEntries) {
@@ -809,21 +838,8 @@ void build_strip_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t
     }
   }
   for (int attempt = 0; attempt < 2 && ps.d.row_pos; ++attempt) {
-    std::vector<StripGrid> grids(nsys);
-    int at = 0;
-    bool ok = true, retry = false;
-    for (int k = 0; k < nsys && ok; ++k) {
-      const int nk = h->batched ? h->sys_n[k] : h->n;
-      if (nk > 0) {
-        ok = strip_infer(h->offsets[k], nk, upper, attempt, &grids[k]);
-        // systems with one reading keep it on the second attempt
-        if (ok && attempt) retry = true;
-        if (!ok && attempt) ok = strip_infer(h->offsets[k], nk, upper, 0, &grids[k]);
-      }
-      grids[k].row0 = at;
-      at += nk;
-    }
-    if (!ok || (attempt && !retry)) break;
+    std::vector<StripGrid> grids;
+    if (!infer_grids(h, upper, attempt, grids)) break;
     const int st = build_strips(ps.d, grids, ps.h.max_row_len, lanes, static_cast<int>(h->vb),
                                s, ps.strips);
     if (st == kErrNotSupported) continue;
@@ -1580,8 +1596,10 @@ int analyze_on_device(sptrsv_handle_t h, const int* row_ptr, const int* col_idx,
   if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, h->device) == hipSuccess &&
       ncu > 0)
     h->num_cu = ncu;
+  find_offsets(h, row_ptr, col_idx, s);
   DeviceAnalysis da;
-  int st = device_analysis(h->n, h->nnz, row_ptr, col_idx, h->upper, h->unit, h->num_cu, s, da);
+  int st = device_analysis(h->n, h->nnz, row_ptr, col_idx, h->upper, h->unit, h->num_cu,
+                           grid_guesses(h, h->upper), s, da);
   if (st) return st;
   if ((st = install_device_plan(h, h->fwd, da, h->upper))) {
     free_device_analysis(da);
@@ -1607,7 +1625,6 @@ int analyze_on_device(sptrsv_handle_t h, const int* row_ptr, const int* col_idx,
   if ((st = init_handle_common(h, s))) return st;
   if ((st = gather(h, h->fwd, vals, s))) return st;
   if ((st = read_status(h, s, true))) return st;
-  find_offsets(h, row_ptr, col_idx, s);
   build_strip_state(h, h->fwd, h->upper, s);
   return kOk;
 }

@@ -35,6 +35,7 @@ struct StripGrid {
   int sy = 1, sz = 1;
   int nx = 1, ny = 1, nz = 1;
   int al = 0, be = 0, ga = 0;
+  int wx = 0, wy = 0, wz = 0;   // the level of (x, y, z) in a grid without gaps
   int upper = 0;
   int axis = 0, lu = 6, lv = 0;
   int nbu = 1, nbv = 1;      // strips along the two lane coordinates
@@ -50,6 +51,17 @@ struct StripGrid {
   unsigned char gcol[64];    // its inverse: the index above of ghost g
   signed char pub[64];       // place of a lane among the published ones, -1 = not published
 };
+
+// wx x + wy y + wz z of a row (relative to row0): its level, if every row of the grid
+// has all the entries that fit
+SPTRSV_HD int strip_level(const StripGrid& g, int r) {
+  const int z = r / g.sz;
+  const int q = r - z * g.sz;
+  const int y = q / g.sy;
+  const int x = q - y * g.sy;
+  return g.upper ? g.wx * (g.nx - 1 - x) + g.wy * (g.ny - 1 - y) + g.wz * (g.nz - 1 - z)
+                 : g.wx * x + g.wy * y + g.wz * z;
+}
 
 struct StripPoint {
   int u, v, w;   // lane coordinates and the coordinate along the lines

@@ -124,6 +124,13 @@ bool strip_infer(const std::vector<int>& offsets, int n, bool upper, int attempt
     if (o.c == 0 && o.b == 1) g.al = std::max(g.al, -o.a);
     if (o.c == 1) g.ga = std::max(g.ga, -o.b);
   }
+  // every entry lies at least one level below its row
+  for (const Off& o : offs)
+    if (o.c == 0 && o.b == 0) g.wx = 1;
+  for (const Off& o : offs)
+    if (o.c == 0 && o.b == 1) g.wy = std::max(g.wy, 1 - g.wx * o.a);
+  for (const Off& o : offs)
+    if (o.c == 1) g.wz = std::max(g.wz, 1 - g.wx * o.a - g.wy * o.b);
   for (const Off& o : offs)
     if (o.c == 1) g.be = std::max(g.be, -(o.a + g.al * o.b));
   const int64_t ext[3] = {g.nx + static_cast<int64_t>(g.al) * (g.ny - 1) +

@@ -49,7 +49,7 @@ __device__ __forceinline__ bool table_add(int* table, int d, bool agent) {
 constexpr int kOffsetRows = 4096;
 
 __global__ void __launch_bounds__(256)
-k_strip_offsets(int n, const int* __restrict__ rp, const int* __restrict__ col, int nsys,
+k_strip_offsets(int n, int64_t nnz, const int* __restrict__ rp, const int* __restrict__ col, int nsys,
                const int* __restrict__ row0, int* table, int* full) {
   __shared__ int tab[kStripTable];
   __shared__ int over;
@@ -60,14 +60,17 @@ k_strip_offsets(int n, const int* __restrict__ rp, const int* __restrict__ col, 
     if (threadIdx.x < kStripTable) tab[threadIdx.x] = 0;
     if (threadIdx.x == 0) over = 0;
     __syncthreads();
-    for (int i = a + threadIdx.x; i < b && !over; i += 256)
-      for (int e = rp[i], e1 = rp[i + 1]; e < e1; ++e) {
+    for (int i = a + threadIdx.x; i < b && !over; i += 256) {
+      int e = rp[i], e1 = rp[i + 1];
+      if (e < 0 || e1 > nnz) e1 = e;        // not a valid pattern: the checks refuse it
+      for (; e < e1; ++e) {
         const int d = abs(col[e] - i);
         if (d != 0 && !table_add(tab, d, false)) {
           over = 1;
           break;
         }
       }
+    }
     __syncthreads();
     if (threadIdx.x < kStripTable) {
       const int d = tab[threadIdx.x];
@@ -715,11 +718,11 @@ struct DevFree {
 
 }  // namespace
 
-hipError_t launch_strip_offsets(int n, const int* row_ptr, const int* col, int nsys,
+hipError_t launch_strip_offsets(int n, int64_t nnz, const int* row_ptr, const int* col, int nsys,
                                 const int* sys_row0, int* table, int* full, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  k_strip_offsets<<<blocks(n, kOffsetRows), 256, 0, s>>>(n, row_ptr, col, nsys, sys_row0, table,
-                                                         full);
+  k_strip_offsets<<<blocks(n, kOffsetRows), 256, 0, s>>>(n, nnz, row_ptr, col, nsys, sys_row0,
+                                                         table, full);
   return hipGetLastError();
 }
 

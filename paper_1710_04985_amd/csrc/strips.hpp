@@ -69,9 +69,11 @@ struct DevStrips {
 
 // Distinct offsets of every system: table[s * kStripTable ..], 0 = empty;
 // full[s] != 0: more than the table holds.  Rows of the systems are
-// sys_row0[0 .. nsys].  row_ptr / col: CSR of the whole triangle.
-hipError_t launch_strip_offsets(int n, const int* row_ptr, const int* col, int nsys,
-                                const int* sys_row0, int* table, int* full, hipStream_t s);
+// sys_row0[0 .. nsys].  row_ptr / col: CSR of the whole triangle, which need not have
+// been checked yet (what is read stays in bounds).
+hipError_t launch_strip_offsets(int n, int64_t nnz, const int* row_ptr, const int* col,
+                                int nsys, const int* sys_row0, int* table, int* full,
+                                hipStream_t s);
 
 // Builds the strip-ordered copy of plan p (values excluded) for the given
 // grids.  Returns kOk, kErrNotSupported (some entry does not fit the grids),

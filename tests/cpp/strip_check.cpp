@@ -97,17 +97,35 @@ int walk(const StripGrid& g, const int* rp, const int* ci, int lead) {
   return 0;
 }
 
-}  // namespace
-
-// 0: every check held; > 0: the check that failed; -1: no grid
-extern "C" int check_strips(int n, const int* rp, const int* ci, int upper, int attempt) {
+bool infer(int n, const int* rp, const int* ci, int upper, int attempt, StripGrid* g) {
   std::set<int> d;
   for (int i = 0; i < n; ++i)
     for (int e = rp[i]; e < rp[i + 1]; ++e)
       if (ci[e] != i) d.insert(std::abs(ci[e] - i));
+  return strip_infer(std::vector<int>(d.begin(), d.end()), n, upper != 0, attempt, g);
+}
+
+}  // namespace
+
+// 0: every check held; > 0: the check that failed; -1: no grid
+extern "C" int check_strips(int n, const int* rp, const int* ci, int upper, int attempt) {
   StripGrid g;
-  if (!strip_infer(std::vector<int>(d.begin(), d.end()), n, upper != 0, attempt, &g)) return -1;
+  if (!infer(n, rp, ci, upper, attempt, &g)) return -1;
   if (g.nghost > kMaxGhosts || g.dmax > kStripMaxBack) return 9;
   if (const int rc = walk(g, rp, ci, 0 + 1)) return rc;
   return walk(g, rp, ci, kRingSteps - kStripMaxBack);
+}
+
+// rows whose level in the grid is not one above the highest of their entries'
+extern "C" int check_levels(int n, const int* rp, const int* ci, int upper, int attempt) {
+  StripGrid g;
+  if (!infer(n, rp, ci, upper, attempt, &g)) return -1;
+  int differ = 0;
+  for (int i = 0; i < n; ++i) {
+    int top = 0;
+    for (int e = rp[i]; e < rp[i + 1]; ++e)
+      if (ci[e] != i) top = std::max(top, strip_level(g, ci[e]) + 1);
+    differ += top != strip_level(g, i);
+  }
+  return differ;
 }

@@ -228,3 +228,23 @@ def test_several_right_hand_sides(sp, dims, points, nrhs):
         h.status()
         assert bits_equal(B.contiguous(), ref.contiguous())
         assert not wide[:, T.n:].any()                 # nothing written past the columns
+
+
+@pytest.mark.parametrize("upper", [False, True])
+def test_levels_of_device_setup(sp, upper):
+    """Levels read off the grid, or found by the sweep where rows lack entries
+    or wrap around the lines, equal the host's; also of a batch."""
+    tris = [W.stencil_triangle(d, p, upper=upper) for d, p in GRIDS]
+    tris += [_dropped(t, 7) for t in tris[4:]] + [t for t in PATTERNS if t.upper == upper]
+    uplo = "U" if upper else "L"
+    for T in tris:
+        devh, hosth = (sp.Handle(*dev_tri(T), uplo=uplo, setup=s) for s in ("device", "host"))
+        for tr in (False, True):
+            for a, b in zip(devh.export_analysis(tr), hosth.export_analysis(tr)):
+                assert np.array_equal(a, b)
+    for part in (tris[:12], tris[:20]):
+        d = [dev_tri(t) for t in part]
+        devh, hosth = (sp.BatchedHandle([a[0] for a in d], [a[1] for a in d], [a[2] for a in d],
+                                        uplo=uplo, setup=s) for s in ("device", "host"))
+        for a, b in zip(devh.export_analysis(), hosth.export_analysis()):
+            assert np.array_equal(a, b)

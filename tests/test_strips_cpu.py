@@ -22,12 +22,13 @@ def check(tmp_path_factory):
                     os.path.join(CSRC, "strips.cpp"), "-o", str(out)], check=True)
     lib = ctypes.CDLL(str(out))
 
-    def run(T, attempt=0, cut=0):
+    def run(T, attempt=0, cut=0, fn=lib.check_strips):
         n = T.n - cut                                   # a leading (lower) part: a cut last line
         rp = np.ascontiguousarray(T.row_ptr[:n + 1], np.int32)
         ci = np.ascontiguousarray(T.col_idx[:rp[-1]], np.int32)
         p = lambda a: a.ctypes.data_as(ctypes.c_void_p)
-        return lib.check_strips(n, p(rp), p(ci), int(T.upper), attempt)
+        return fn(n, p(rp), p(ci), int(T.upper), attempt)
+    run.levels = lambda T, **o: run(T, fn=lib.check_levels, **o)
     return run
 
 
@@ -41,6 +42,7 @@ GRIDS = [((1, 1), 5), ((2, 3), 5), ((64, 64), 5), ((65, 63), 5), ((63, 130), 9),
 def test_grids(check, dims, points, upper):
     T = W.stencil_triangle(dims, points, upper=upper)
     assert check(T) == 0
+    assert check.levels(T) == 0
     if not upper and T.n > 10:
         assert check(T, cut=3) == 0
 
