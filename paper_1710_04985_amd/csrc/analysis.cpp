@@ -223,26 +223,39 @@ void build_chunks(const HostPlan& p, int group, int entries_per_lane, int rows_f
     fixed_lg = 0;
     while ((64 >> fixed_lg) > rows_fixed) ++fixed_lg;
   }
+  // rows_fixed: rows_per_lane rows in each of the 64 >> lg lane groups
+  auto capacity = [&](int lg) {
+    return rows_fixed > 0 ? (64 >> lg) * rows_per_lane : lg == 0 ? 64 * rows_per_lane : 64 >> lg;
+  };
+  if (rows_fixed > 0 || group > 0 || p.off_ptr.empty()) {
+    // every row gets the same lanes
+    const int cap = capacity(fixed_lg);
+    int64_t total = 0;
+    for (int m = 0; m < p.nlev; ++m) total += (p.pos_ilev[m + 1] - p.pos_ilev[m] + cap - 1) / cap;
+    t.start.reserve(total);
+    t.meta.reserve(total);
+    for (int m = 0; m < p.nlev; ++m) {
+      t.level_chunk[m] = static_cast<int>(t.start.size());
+      for (int k = p.pos_ilev[m]; k < p.pos_ilev[m + 1]; k += cap) {
+        t.start.push_back(k);
+        t.meta.push_back(std::min(cap, p.pos_ilev[m + 1] - k) | (fixed_lg << 16));
+      }
+    }
+    t.level_chunk[p.nlev] = static_cast<int>(t.start.size());
+    if (!t.start.empty()) t.max_lg = fixed_lg;
+    return;
+  }
   for (int m = 0; m < p.nlev; ++m) {
     t.level_chunk[m] = static_cast<int>(t.start.size());
     int k = p.pos_ilev[m];
     const int end = p.pos_ilev[m + 1];
     while (k < end) {
-      int lg;
-      if (rows_fixed > 0 || group > 0) lg = fixed_lg;
-      else lg = lanes_for(p.off_ptr[k + 1] - p.off_ptr[k]);
-      // rows_fixed: rows_per_lane rows in each of the 64 >> lg lane groups
-      const int cap = rows_fixed > 0 ? (64 >> lg) * rows_per_lane
-                      : lg == 0      ? 64 * rows_per_lane
-                                     : 64 >> lg;
+      const int lg = lanes_for(p.off_ptr[k + 1] - p.off_ptr[k]);
+      const int cap = capacity(lg);
       int cnt = 1;
-      while (cnt < cap && k + cnt < end) {
-        if (rows_fixed <= 0 && group <= 0) {
-          const int len = p.off_ptr[k + cnt + 1] - p.off_ptr[k + cnt];
-          if (lanes_for(len) > lg) break;
-        }
+      while (cnt < cap && k + cnt < end &&
+             lanes_for(p.off_ptr[k + cnt + 1] - p.off_ptr[k + cnt]) <= lg)
         ++cnt;
-      }
       t.start.push_back(k);
       t.meta.push_back(cnt | (lg << 16));
       t.max_lg = std::max(t.max_lg, lg);

@@ -99,7 +99,8 @@ struct ChunkTable {
 };
 
 // group > 0: every row gets G = group lanes (a power of two <= 64).
-// group == 0: G = smallest power of two with ceil(len / G) <= entries_per_lane.
+// group == 0: G = smallest power of two with ceil(len / G) <= entries_per_lane;
+// a plan without off_ptr has no row longer than entries_per_lane.
 // rows_fixed > 0 overrides both: G = 64 / rows_fixed lanes per row and
 // count <= rows_fixed * rows_per_lane (multi-RHS kernels, where the lanes of
 // a row split right-hand sides, not entries, and each lane group may own

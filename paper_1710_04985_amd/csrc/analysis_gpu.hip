@@ -10,6 +10,7 @@
 #include "analysis.hpp"
 #include "analysis_gpu.hpp"
 #include "device_common.hpp"
+#include "devmem.hpp"
 
 namespace sptrsv {
 namespace {
@@ -274,17 +275,17 @@ k_levels(int n, const int* __restrict__ rp, const int* __restrict__ col, int upp
 }
 
 // sort keys: (level, bit length of the dependency count), values: row
+constexpr int kClassBits = 5;
+
+template <typename K>
 __global__ void __launch_bounds__(256) k_keys(int n, const int* __restrict__ level,
-                                              const int* __restrict__ depcnt,
-                                              unsigned long long* __restrict__ key, int* __restrict__ rows,
-                                              unsigned* __restrict__ lkey, int* __restrict__ rows2) {
+                                              const int* __restrict__ depcnt, K* __restrict__ key,
+                                              int* __restrict__ rows) {
   const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
   for (int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; t < n; t += stride) {
     const int i = static_cast<int>(t);
-    key[i] = (static_cast<unsigned long long>(level[i]) << 5) | bitlen(static_cast<unsigned>(depcnt[i]));
+    key[i] = (static_cast<K>(level[i]) << kClassBits) | bitlen(static_cast<unsigned>(depcnt[i]));
     rows[i] = i;
-    lkey[i] = static_cast<unsigned>(level[i]);
-    rows2[i] = i;
   }
 }
 
@@ -351,33 +352,18 @@ inline int blocks(int64_t work) {
 
 template <typename T> int dmalloc(T** p, int64_t count) {
   *p = nullptr;
-  if (hipMalloc(reinterpret_cast<void**>(p), static_cast<size_t>(count > 0 ? count : 1) * sizeof(T)) !=
-      hipSuccess)
+  if (dev_alloc(reinterpret_cast<void**>(p), count * static_cast<int64_t>(sizeof(T))) != hipSuccess)
     return kErrOom;
   return kOk;
 }
 
 struct Temps {
-  int* flags = nullptr;
-  int* counters = nullptr;   // [0] max row length, [1] max level, [2] chunk ticket, [3] grid levels differ
-  unsigned long long* key = nullptr;
-  unsigned long long* key_s = nullptr;
-  int* rows = nullptr;
-  unsigned* lkey = nullptr;
-  unsigned* lkey_s = nullptr;
-  int* rows2 = nullptr;
-  int* pos_of = nullptr;
-  int* cnt = nullptr;
-  int* ilev = nullptr;
+  int* flags = nullptr;      // and the counters behind it
   StripGrid* grids = nullptr;
-  void* tmp = nullptr;
+  char* work = nullptr;      // only if the caller's spare part is too small
   ~Temps() {
-    for (void* p : {static_cast<void*>(flags), static_cast<void*>(counters), static_cast<void*>(key),
-                    static_cast<void*>(key_s), static_cast<void*>(rows), static_cast<void*>(lkey),
-                    static_cast<void*>(lkey_s), static_cast<void*>(rows2), static_cast<void*>(pos_of),
-                    static_cast<void*>(cnt), static_cast<void*>(ilev),
-                    static_cast<void*>(grids), tmp})
-      if (p) (void)hipFree(p);
+    for (void* p : {static_cast<void*>(flags), static_cast<void*>(grids), static_cast<void*>(work)})
+      dev_free(p);
   }
 };
 
@@ -486,9 +472,7 @@ __global__ void __launch_bounds__(256) k_concat(const SysDesc* __restrict__ sys,
 }  // namespace
 
 void free_device_analysis(DeviceAnalysis& a) {
-  for (int* p : {a.level, a.depcnt, a.jlev, a.pos_row, a.off_ptr, a.off_col, a.off_pos, a.off_src,
-                 a.diag_src})
-    if (p) (void)hipFree(p);
+  dev_free(a.mem.base);
   a = DeviceAnalysis();
 }
 
@@ -507,50 +491,98 @@ void free_device_analysis(DeviceAnalysis& a) {
     }                                               \
   } while (0)
 
+namespace {
+
+// Rows ordered by (level, class) into pos_row and by level into jlev, both
+// stably: radix sorts of the same keys with and without the class bits.
+// work == nullptr: only sets *bytes.
+template <typename K>
+hipError_t sort_rows(int n, int lev_bits, DeviceAnalysis& out, char* work, int64_t* bytes,
+                     hipStream_t s) {
+  const int64_t kb = block_bytes(static_cast<int64_t>(n) * sizeof(K));
+  K* key = reinterpret_cast<K*>(work);
+  K* key_s = reinterpret_cast<K*>(work + kb);
+  int* rows = reinterpret_cast<int*>(work + 2 * kb);
+  const int64_t rb = block_bytes(static_cast<int64_t>(n) * sizeof(int));
+  void* tmp = work ? work + 2 * kb + rb : nullptr;
+  const unsigned un = static_cast<unsigned>(n);
+  const int end = kClassBits + lev_bits;
+  size_t b1 = 0, b2 = 0;
+  if (work) {
+    k_keys<K><<<blocks(n), 256, 0, s>>>(n, out.level, out.depcnt, key, rows);
+    if (const hipError_t e = hipGetLastError()) return e;
+    b1 = b2 = static_cast<size_t>(*bytes - (2 * kb + rb));
+  }
+  hipError_t e = rocprim::radix_sort_pairs(tmp, b1, key, key_s, rows, out.pos_row, un, 0, end, s);
+  if (e == hipSuccess)
+    e = rocprim::radix_sort_pairs(tmp, b2, key, key_s, rows, out.jlev, un, kClassBits, end, s);
+  if (!work) *bytes = 2 * kb + rb + block_bytes(static_cast<int64_t>(std::max(b1, b2)));
+  return e;
+}
+
+}  // namespace
+
 int device_analysis(int n, int64_t nnz, const int* row_ptr, const int* col, bool upper,
                     bool unit_diag, int num_cu,
-                    const std::vector<std::vector<StripGrid>>& guesses, hipStream_t s,
-                    DeviceAnalysis& out) {
+                    const std::vector<std::vector<StripGrid>>& guesses, int64_t spare,
+                    hipStream_t s, DeviceAnalysis& out) {
   out = DeviceAnalysis();
   if (n < 1 || nnz < 0 || nnz > INT32_MAX || n > (1 << 30)) return kErrNotSupported;
   out.n = n;
   Temps tp;
-  DALLOC(tp.flags, 1);
-  DALLOC(tp.counters, 4);
-  DALLOC(out.depcnt, n);
-  DALLOC(out.level, n);
-  int zero2[4] = {0, -1, 0, 0};
-  int zero = 0;
-  DCHK(hipMemcpyAsync(tp.flags, &zero, sizeof(int), hipMemcpyHostToDevice, s));
-  DCHK(hipMemcpyAsync(tp.counters, zero2, 4 * sizeof(int), hipMemcpyHostToDevice, s));
-  k_check<<<std::min(blocks(n), kCheckBlocks), 256, 0, s>>>(n, nnz, row_ptr, col, upper, unit_diag, out.depcnt, tp.flags,
-                                     tp.counters);
+  {
+    // off-diagonals: all entries but the diagonal's (a unit triangle may store any part of it)
+    const int64_t noff = unit_diag ? nnz : std::max<int64_t>(0, nnz - n);
+    const int64_t nb = block_bytes((static_cast<int64_t>(n) + 1) * sizeof(int));
+    const int64_t ob = block_bytes(std::max<int64_t>(1, noff) * sizeof(int));
+    out.mem.bytes = 7 * nb + 3 * ob + block_bytes(spare);
+    if (dev_alloc(reinterpret_cast<void**>(&out.mem.base), out.mem.bytes) != hipSuccess) {
+      out.mem = DevBlock();
+      return kErrOom;
+    }
+    char* at = out.mem.base;
+    for (int** p : {&out.level, &out.depcnt, &out.jlev, &out.pos_row, &out.row_pos, &out.diag_src,
+                    &out.off_ptr}) {
+      *p = reinterpret_cast<int*>(at);
+      at += nb;
+    }
+    for (int** p : {&out.off_col, &out.off_pos, &out.off_src}) {
+      *p = reinterpret_cast<int*>(at);
+      at += ob;
+    }
+    out.spare = at;
+  }
+  // [0] flags, [1] max row length, [2] max level, [3] chunk ticket, [4] grid levels differ
+  DALLOC(tp.flags, 5);
+  const int init[5] = {0, 0, -1, 0, 0};
+  int got[5] = {0, 0, -1, 0, 1};
+  DCHK(hipMemcpyAsync(tp.flags, init, sizeof(init), hipMemcpyHostToDevice, s));
+  k_check<<<std::min(blocks(n), kCheckBlocks), 256, 0, s>>>(n, nnz, row_ptr, col, upper, unit_diag,
+                                                            out.depcnt, tp.flags, tp.flags + 1);
   DCHK(hipGetLastError());
-  int flags = 0, max_len = 0;
-  DCHK(hipMemcpyAsync(&flags, tp.flags, sizeof(int), hipMemcpyDeviceToHost, s));
-  DCHK(hipMemcpyAsync(&max_len, tp.counters, sizeof(int), hipMemcpyDeviceToHost, s));
+  DCHK(hipMemcpyAsync(got, tp.flags, 2 * sizeof(int), hipMemcpyDeviceToHost, s));
   DCHK(hipStreamSynchronize(s));
-  if (flags) {
+  if (got[0]) {
     free_device_analysis(out);
     return kErrNotSupported;
   }
+  const int max_len = got[1];
 
   // levels: from the grid, if a guess of it holds, else by the sweep
-  int counters[4] = {0, -1, 0, 1};
   for (const std::vector<StripGrid>& g : guesses) {
     if (!tp.grids) DALLOC(tp.grids, static_cast<int64_t>(g.size()));
     DCHK(hipMemcpyAsync(tp.grids, g.data(), g.size() * sizeof(StripGrid), hipMemcpyHostToDevice, s));
-    DCHK(hipMemcpyAsync(tp.counters + 1, zero2 + 1, 3 * sizeof(int), hipMemcpyHostToDevice, s));
+    DCHK(hipMemcpyAsync(tp.flags + 2, init + 2, 3 * sizeof(int), hipMemcpyHostToDevice, s));
     k_grid_levels<<<std::min(blocks(n), kCheckBlocks), 256, 0, s>>>(
-        n, row_ptr, col, tp.grids, static_cast<int>(g.size()), out.level, tp.counters + 3,
-        tp.counters + 1);
+        n, row_ptr, col, tp.grids, static_cast<int>(g.size()), out.level, tp.flags + 4,
+        tp.flags + 2);
     DCHK(hipGetLastError());
-    DCHK(hipMemcpyAsync(counters, tp.counters, sizeof(counters), hipMemcpyDeviceToHost, s));
+    DCHK(hipMemcpyAsync(got, tp.flags, sizeof(got), hipMemcpyDeviceToHost, s));
     DCHK(hipStreamSynchronize(s));
-    if (!counters[3]) break;
+    if (!got[4]) break;
   }
-  if (counters[3]) {
-    DCHK(hipMemcpyAsync(tp.counters + 1, zero2 + 1, 3 * sizeof(int), hipMemcpyHostToDevice, s));
+  if (got[4]) {
+    DCHK(hipMemcpyAsync(tp.flags + 2, init + 2, 3 * sizeof(int), hipMemcpyHostToDevice, s));
     k_fill_int<<<blocks(n), 256, 0, s>>>(out.level, n, -1);
     DCHK(hipGetLastError());
     int per_cu = 0;
@@ -565,80 +597,61 @@ int device_analysis(int n, int64_t nnz, const int* row_ptr, const int* col, bool
     const int waves_per_cu = max_len > 16 ? std::min(4, std::max(1, per_cu)) : std::max(1, per_cu);
     const int grid = std::max(1, std::min(nch, waves_per_cu * num_cu));
     k_levels<<<grid, 64, 0, s>>>(n, row_ptr, col, upper ? 1 : 0, out.level, tp.flags,
-                                 tp.counters + 1, tp.counters + 2, 1 << 24);
+                                 tp.flags + 2, tp.flags + 3, 1 << 24);
     DCHK(hipGetLastError());
-    DCHK(hipMemcpyAsync(counters, tp.counters, sizeof(counters), hipMemcpyDeviceToHost, s));
-    DCHK(hipMemcpyAsync(&flags, tp.flags, sizeof(int), hipMemcpyDeviceToHost, s));
+    DCHK(hipMemcpyAsync(got, tp.flags, sizeof(got), hipMemcpyDeviceToHost, s));
     DCHK(hipStreamSynchronize(s));
-    if (flags & kFlagTimeout) {
+    if (got[0] & kFlagTimeout) {
       free_device_analysis(out);
       return kErrTimeout;
     }
   }
-  out.max_row_len = counters[0];
-  out.nlev = counters[1] + 1;
+  out.max_row_len = max_len;
+  out.nlev = got[2] + 1;
   const int nlev = out.nlev;
   int lev_bits = 1;
   while (lev_bits < 31 && (1ll << lev_bits) < nlev) ++lev_bits;
 
-  // stable radix sorts: positions by (level, length class); jlev by level
-  DALLOC(tp.key, n);
-  DALLOC(tp.key_s, n);
-  DALLOC(tp.rows, n);
-  DALLOC(tp.lkey, n);
-  DALLOC(tp.lkey_s, n);
-  DALLOC(tp.rows2, n);
-  DALLOC(out.pos_row, n);
-  DALLOC(out.jlev, n);
-  k_keys<<<blocks(n), 256, 0, s>>>(n, out.level, out.depcnt, tp.key, tp.rows, tp.lkey, tp.rows2);
-  DCHK(hipGetLastError());
-  size_t b1 = 0, b2 = 0, b3 = 0;
-  DCHK(rocprim::radix_sort_pairs(nullptr, b1, tp.key, tp.key_s, tp.rows, out.pos_row,
-                                 static_cast<unsigned>(n), 0, 5 + lev_bits, s));
-  DCHK(rocprim::radix_sort_pairs(nullptr, b2, tp.lkey, tp.lkey_s, tp.rows2, out.jlev,
-                                 static_cast<unsigned>(n), 0, lev_bits, s));
-  DALLOC(tp.cnt, static_cast<int64_t>(n) + 1);
-  DALLOC(out.off_ptr, static_cast<int64_t>(n) + 1);
-  DCHK(rocprim::exclusive_scan(nullptr, b3, tp.cnt, out.off_ptr, 0, static_cast<size_t>(n) + 1,
-                               rocprim::plus<int>(), s));
-  size_t tb = std::max(b1, std::max(b2, b3));
-  if (hipMalloc(&tp.tmp, tb > 0 ? tb : 1) != hipSuccess) {
-    free_device_analysis(out);
-    return kErrOom;
+  // work space: row lengths by position, level pointers, sort and scan buffers
+  const bool wide = kClassBits + lev_bits > 32;
+  const int64_t cb = block_bytes((static_cast<int64_t>(n) + 1) * sizeof(int));
+  const int64_t lb = block_bytes((static_cast<int64_t>(nlev) + 1) * sizeof(int));
+  int64_t sort_bytes = 0;
+  size_t scan_bytes = 0;
+  DCHK(wide ? sort_rows<unsigned long long>(n, lev_bits, out, nullptr, &sort_bytes, s)
+            : sort_rows<unsigned>(n, lev_bits, out, nullptr, &sort_bytes, s));
+  DCHK(rocprim::exclusive_scan(nullptr, scan_bytes, static_cast<int*>(nullptr), out.off_ptr, 0,
+                               static_cast<size_t>(n) + 1, rocprim::plus<int>(), s));
+  const int64_t need = cb + lb + std::max(sort_bytes, static_cast<int64_t>(scan_bytes));
+  char* work = out.spare;
+  if (need > spare) {
+    DALLOC(tp.work, need);
+    work = tp.work;
   }
-  DCHK(rocprim::radix_sort_pairs(tp.tmp, b1, tp.key, tp.key_s, tp.rows, out.pos_row,
-                                 static_cast<unsigned>(n), 0, 5 + lev_bits, s));
-  DCHK(rocprim::radix_sort_pairs(tp.tmp, b2, tp.lkey, tp.lkey_s, tp.rows2, out.jlev,
-                                 static_cast<unsigned>(n), 0, lev_bits, s));
+  int* cnt = reinterpret_cast<int*>(work);
+  int* ilev = reinterpret_cast<int*>(work + cb);
+  char* tmp = work + cb + lb;
+  DCHK(wide ? sort_rows<unsigned long long>(n, lev_bits, out, tmp, &sort_bytes, s)
+            : sort_rows<unsigned>(n, lev_bits, out, tmp, &sort_bytes, s));
 
   // inverse permutation, row lengths, level pointers, CSR pointers
-  DALLOC(tp.pos_of, n);
-  DALLOC(tp.ilev, static_cast<int64_t>(nlev) + 1);
   k_positions<<<blocks(static_cast<int64_t>(n) + 1), 256, 0, s>>>(n, nlev, out.pos_row, out.level,
-                                                                   out.depcnt, tp.pos_of, tp.cnt,
-                                                                   tp.ilev);
+                                                                   out.depcnt, out.row_pos, cnt, ilev);
   DCHK(hipGetLastError());
-  DCHK(rocprim::exclusive_scan(tp.tmp, b3, tp.cnt, out.off_ptr, 0, static_cast<size_t>(n) + 1,
+  DCHK(rocprim::exclusive_scan(tmp, scan_bytes, cnt, out.off_ptr, 0, static_cast<size_t>(n) + 1,
                                rocprim::plus<int>(), s));
-  out.off_ptr_h.resize(static_cast<size_t>(n) + 1);
-  out.ilev.resize(static_cast<size_t>(nlev) + 1);
-  DCHK(hipMemcpyAsync(out.off_ptr_h.data(), out.off_ptr, (static_cast<size_t>(n) + 1) * sizeof(int),
-                      hipMemcpyDeviceToHost, s));
-  DCHK(hipMemcpyAsync(out.ilev.data(), tp.ilev, (static_cast<size_t>(nlev) + 1) * sizeof(int),
-                      hipMemcpyDeviceToHost, s));
-  DCHK(hipStreamSynchronize(s));
-  out.noff = out.off_ptr_h[n];
-
   // the level-ordered copy of the off-diagonal pattern
-  DALLOC(out.off_col, out.noff);
-  DALLOC(out.off_pos, out.noff);
-  DALLOC(out.off_src, out.noff);
-  DALLOC(out.diag_src, n);
-  k_offdiag<<<blocks(n), 256, 0, s>>>(n, unit_diag, row_ptr, col, out.pos_row, tp.pos_of,
+  k_offdiag<<<blocks(n), 256, 0, s>>>(n, unit_diag, row_ptr, col, out.pos_row, out.row_pos,
                                        out.off_ptr, out.off_col, out.off_pos, out.off_src,
                                        out.diag_src);
   DCHK(hipGetLastError());
+  out.ilev.resize(static_cast<size_t>(nlev) + 1);
+  int noff = 0;
+  DCHK(hipMemcpyAsync(out.ilev.data(), ilev, (static_cast<size_t>(nlev) + 1) * sizeof(int),
+                      hipMemcpyDeviceToHost, s));
+  DCHK(hipMemcpyAsync(&noff, out.off_ptr + n, sizeof(int), hipMemcpyDeviceToHost, s));
   DCHK(hipStreamSynchronize(s));
+  out.noff = noff;
   return kOk;
 }
 
@@ -656,7 +669,7 @@ int device_transpose(int n, int64_t nnz, const int* row_ptr, const int* col, hip
   auto cleanup = [&]() {
     for (void* p : {static_cast<void*>(keys), static_cast<void*>(keys_s), static_cast<void*>(vals),
                     static_cast<void*>(row_of), tmp})
-      if (p) (void)hipFree(p);
+      dev_free(p);
   };
   if (dmalloc(&keys_s, nnz) || dmalloc(&vals, nnz) || dmalloc(&row_of, nnz) ||
       dmalloc(rpT, static_cast<int64_t>(n) + 1) || dmalloc(colT, nnz) || dmalloc(srcT, nnz)) {
@@ -676,7 +689,7 @@ int device_transpose(int n, int64_t nnz, const int* row_ptr, const int* col, hip
       size_t tb = 0;
       if (rocprim::radix_sort_pairs(nullptr, tb, keys, keys_s, vals, *srcT,
                                     static_cast<unsigned>(nnz), 0, col_bits, s) != hipSuccess ||
-          hipMalloc(&tmp, tb > 0 ? tb : 1) != hipSuccess ||
+          dev_alloc(&tmp, static_cast<int64_t>(tb)) != hipSuccess ||
           rocprim::radix_sort_pairs(tmp, tb, keys, keys_s, vals, *srcT, static_cast<unsigned>(nnz),
                                     0, col_bits, s) != hipSuccess)
         st = kErrHip;
@@ -692,7 +705,7 @@ int device_transpose(int n, int64_t nnz, const int* row_ptr, const int* col, hip
   if (st) {
     for (int** p : {rpT, colT, srcT})
       if (*p) {
-        (void)hipFree(*p);
+        dev_free(*p);
         *p = nullptr;
       }
   }
@@ -709,7 +722,7 @@ int device_value_sources(int n, int64_t noff_f, const int* off_src_f, const int*
   k_compose_src<<<blocks(tot_t), 256, 0, s>>>(n, t.noff, srcT, loc, t.off_src, t.diag_src);
   int st = kOk;
   if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) st = kErrHip;
-  (void)hipFree(loc);
+  dev_free(loc);
   return st;
 }
 
@@ -749,8 +762,8 @@ int device_concat(const std::vector<ConcatSystem>& systems, int vb, int* rp_cat,
     const int last = static_cast<int>(eoff);
     if (hipMemcpy(rp_cat + roff, &last, sizeof(int), hipMemcpyHostToDevice) != hipSuccess) st = kErrHip;
   }
-  if (dsys) (void)hipFree(dsys);
-  if (flags) (void)hipFree(flags);
+  dev_free(dsys);
+  dev_free(flags);
   if (!st && f) st = kErrNotSupported;
   return st;
 }

@@ -13,9 +13,22 @@
 
 namespace sptrsv {
 
-// Device arrays of one analysed triangle (owned by the caller after success;
-// free with free_device_analysis).  Same meaning as the HostPlan fields.
+// One allocation that holds many arrays.
+struct DevBlock {
+  char* base = nullptr;
+  int64_t bytes = 0;
+  bool holds(const void* p) const {
+    return p >= static_cast<const void*>(base) && p < static_cast<const void*>(base + bytes);
+  }
+};
+inline int64_t block_bytes(int64_t bytes) { return (bytes + 255) / 256 * 256; }
+
+// Device arrays of one analysed triangle, all in mem (owned by the caller
+// after success; free with free_device_analysis).  Same meaning as the
+// HostPlan fields.
 struct DeviceAnalysis {
+  DevBlock mem;
+  char* spare = nullptr;    // the caller's part of mem, uninitialised
   int n = 0;
   int nlev = 0;
   int64_t noff = 0;
@@ -24,13 +37,13 @@ struct DeviceAnalysis {
   int* depcnt = nullptr;    // [n]
   int* jlev = nullptr;      // [n] rows by (level, row)
   int* pos_row = nullptr;   // [n]
+  int* row_pos = nullptr;   // [n] its inverse
   int* off_ptr = nullptr;   // [n+1]
   int* off_col = nullptr;   // [noff]
   int* off_pos = nullptr;   // [noff]
   int* off_src = nullptr;   // [noff]
   int* diag_src = nullptr;  // [n]
   std::vector<int> ilev;    // host: level pointers [nlev+1]
-  std::vector<int> off_ptr_h;   // host copy of off_ptr
 };
 
 // Analyses the triangle (row_ptr, col) held in device memory.  Returns kOk,
@@ -40,18 +53,19 @@ struct DeviceAnalysis {
 // produces the exact validation error.  Other errors: kErrHip, kErrOom,
 // kErrTimeout (level kernel spin limit; cannot happen on a valid pattern).
 // Blocking: synchronises `stream`.  guesses: readings of the pattern as grids, one per
-// system each (may be empty); levels that a grid explains take one pass.
+// system each (may be empty); levels that a grid explains take one pass.  spare: bytes to set aside
+// for the caller, used as work space here.
 int device_analysis(int n, int64_t nnz, const int* row_ptr, const int* col, bool upper,
                     bool unit_diag, int num_cu,
-                    const std::vector<std::vector<StripGrid>>& guesses, hipStream_t stream,
-                    DeviceAnalysis& out);
+                    const std::vector<std::vector<StripGrid>>& guesses, int64_t spare,
+                    hipStream_t stream, DeviceAnalysis& out);
 
 void free_device_analysis(DeviceAnalysis& a);
 
 // Pattern of T^T in CSR, on the device: rows of T^T are the columns of T,
 // each with its columns (rows of T) strictly increasing; srcT[t] is the entry
 // of T that entry t of T^T came from.  The three arrays are allocated here
-// (hipFree them).  Blocking.
+// (dev_free them).  Blocking.
 int device_transpose(int n, int64_t nnz, const int* row_ptr, const int* col, hipStream_t stream,
                      int** rpT, int** colT, int** srcT);
 

@@ -20,6 +20,7 @@
 #include "analysis_gpu.hpp"
 #include "api_internal.hpp"
 #include "column.hpp"
+#include "devmem.hpp"
 #include "probe.hpp"
 #include "kernels.hpp"
 #include "strips.hpp"
@@ -54,9 +55,11 @@ struct PlanState {
   bool built = false;
   HostPlan h;
   DevPlan d;
-  // analysed on the device: the host plan holds only nlev, ilev, pos_ilev
-  // and off_ptr until something needs the rest (ensure_plan_host), which is
-  // then downloaded from d and the analysis arrays below
+  // analysed on the device: the host plan holds only nlev, ilev and pos_ilev
+  // until something needs off_ptr (get_chunks) or the rest too
+  // (ensure_plan_host), downloaded then from d and the analysis arrays below;
+  // the device arrays are parts of mem
+  DevBlock mem;
   bool host_complete = true;
   int* a_level = nullptr;
   int* a_depcnt = nullptr;
@@ -123,7 +126,7 @@ struct DevBuffer {
   DevBuffer(const DevBuffer&) = delete;
   DevBuffer& operator=(const DevBuffer&) = delete;
   ~DevBuffer() {
-    if (p) (void)hipFree(p);   // hipFree waits for the device before freeing
+    dev_free(p);   // waits for the device
   }
 };
 
@@ -225,16 +228,14 @@ namespace {
 template <typename T> T* dalloc(size_t count, int* err) {
   if (count == 0) count = 1;
   void* p = nullptr;
-  if (hipMalloc(&p, count * sizeof(T)) != hipSuccess) {
+  if (dev_alloc(&p, static_cast<int64_t>(count * sizeof(T))) != hipSuccess) {
     *err = kErrOom;
     return nullptr;
   }
   return static_cast<T*>(p);
 }
 
-void dfree(void* p) {
-  if (p) (void)hipFree(p);
-}
+void dfree(void* p) { dev_free(p); }
 
 void free_entry(ChunkEntry& e) {
   dfree(e.d.start);
@@ -296,19 +297,23 @@ void free_push(PushState& p) {
   p = PushState();
 }
 
+// Frees an array of plan ps, unless it is a part of the plan's one block.
+void dfree_of(const PlanState& ps, void* p) {
+  if (!ps.mem.holds(p)) dfree(p);
+}
+
 void free_plan(PlanState& ps) {
   free_chunks(ps);
-  dfree(ps.d.off_ptr);
-  dfree(ps.d.off_col);
-  dfree(ps.d.off_pos);
-  dfree(ps.d.off_src);
-  dfree(ps.d.diag_src);
-  dfree(ps.d.pos_row);
-  dfree(ps.d.row_pos);
-  dfree(ps.vals_buf);
-  dfree(ps.a_level);
-  dfree(ps.a_depcnt);
-  dfree(ps.a_jlev);
+  dfree_of(ps, ps.d.off_ptr);
+  dfree_of(ps, ps.d.off_col);
+  dfree_of(ps, ps.d.off_pos);
+  dfree_of(ps, ps.d.off_src);
+  dfree_of(ps, ps.d.diag_src);
+  dfree_of(ps, ps.d.pos_row);
+  dfree_of(ps, ps.d.row_pos);
+  dfree_of(ps, ps.vals_buf);
+  dfree(ps.mem.base);
+  ps.mem = DevBlock();
   free_push(ps.push);
   free_strips(ps.strips);
   ps.d = DevPlan();
@@ -351,10 +356,24 @@ int upload_plan(PlanState& ps, size_t vb, hipStream_t s) {
   return kOk;
 }
 
+// The row pointers of a plan analysed on the device (downloaded once).
+int ensure_off_ptr(PlanState& ps) {
+  if (ps.host_complete || !ps.h.off_ptr.empty()) return kOk;
+  const size_t count = static_cast<size_t>(ps.h.n) + 1;
+  ps.h.off_ptr.resize(count);
+  if (hipMemcpy(ps.h.off_ptr.data(), ps.d.off_ptr, count * sizeof(int), hipMemcpyDeviceToHost) !=
+      hipSuccess) {
+    ps.h.off_ptr.clear();
+    return kErrHip;
+  }
+  return kOk;
+}
+
 // Completes the host plan of a plan analysed on the device: every plan
 // array is downloaded once (blocking).
 int ensure_plan_host(PlanState& ps) {
   if (ps.host_complete) return kOk;
+  if (const int st = ensure_off_ptr(ps)) return st;
   const size_t n = static_cast<size_t>(ps.h.n);
   HostPlan& p = ps.h;
   const DevPlan& d = ps.d;
@@ -424,7 +443,8 @@ int read_status(sptrsv_handle_t h, hipStream_t s, bool clear) {
   return kOk;
 }
 
-int install_device_plan(sptrsv_handle_t h, PlanState& ps, DeviceAnalysis& da, bool upper);
+void install_device_plan(sptrsv_handle_t h, PlanState& ps, DeviceAnalysis& da, bool upper);
+int64_t values_bytes(sptrsv_handle_t h);
 std::vector<std::vector<StripGrid>> grid_guesses(sptrsv_handle_t h, bool upper);
 void build_strip_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t s);
 
@@ -441,13 +461,15 @@ int build_transpose(sptrsv_handle_t h, hipStream_t s) {
     int st = device_transpose(n, h->nnz, h->rp_dev, h->col_dev, s, &rT, &cT, &sT);
     DeviceAnalysis da;
     if (!st) st = device_analysis(n, h->nnz, rT, cT, !h->upper, h->unit, h->num_cu,
-                                   grid_guesses(h, !h->upper), s, da);
+                                   grid_guesses(h, !h->upper), values_bytes(h), s, da);
     if (!st)
       st = device_value_sources(n, h->fwd.d.noff, h->fwd.d.off_src, h->fwd.d.diag_src, h->nnz, sT,
                                 da, s);
     for (int* q : {rT, cT, sT}) dfree(q);
-    if (!st) st = install_device_plan(h, h->trn, da, !h->upper);
-    if (!st) st = gather(h, h->trn, h->fwd.vals_buf, s);
+    if (!st) {
+      install_device_plan(h, h->trn, da, !h->upper);
+      st = gather(h, h->trn, h->fwd.vals_buf, s);
+    }
     if (!st && hipStreamSynchronize(s) != hipSuccess) st = kErrHip;
     if (st) {
       free_device_analysis(da);
@@ -521,6 +543,8 @@ ChunkEntry* get_chunks(sptrsv_handle_t h, PlanState& ps, int group, int epl, int
     *err = kErrNotSupported;
     return nullptr;
   }
+  if (group == 0 && rows_fixed == 0 && ps.h.max_row_len > epl && (*err = ensure_off_ptr(ps)))
+    return nullptr;
   ChunkTable t;
   build_chunks(ps.h, group, epl, rows_fixed, rpl, t);
   ChunkEntry e;
@@ -846,7 +870,9 @@ void build_strip_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t
     if (!st) {
       const hipError_t e = h->dtype == SPTRSV_F64 ? launch_strip_gather<double>(ps.d, ps.strips, s)
                                                   : launch_strip_gather<float>(ps.d, ps.strips, s);
-      if (e != hipSuccess || ensure_xp(h, strip_values(ps.strips, 1)) || hipStreamSynchronize(s) != hipSuccess)
+      if (e != hipSuccess || 
+          ensure_xp(h, std::max<int64_t>(h->n, strip_values(ps.strips, 1))) ||
+          hipStreamSynchronize(s) != hipSuccess)
         free_strips(ps.strips);
       else
         (void)strip_occupancy(h, ps, 1);
@@ -870,7 +896,7 @@ int ensure_xp(sptrsv_handle_t h, int64_t elems) {
   if (h->xp_elems >= elems) return kOk;
   if (h->xp_buf && h->order_ev && h->order_pending) HIPCHK(hipEventSynchronize(h->order_ev));
   auto nb = std::make_shared<DevBuffer>();
-  if (hipMalloc(&nb->p, static_cast<size_t>(elems > 0 ? elems : 1) * h->vb) != hipSuccess)
+  if (dev_alloc(&nb->p, elems * static_cast<int64_t>(h->vb)) != hipSuccess)
     return kErrOom;
   h->xp_buf = std::move(nb);   // frees the old buffer unless a graph holds it
   h->xp = h->xp_buf->p;
@@ -886,7 +912,7 @@ int ensure_multi(sptrsv_handle_t h, PlanState& ps, int64_t elems, hipStream_t s)
     dfree(h->bp);
     h->bp = nullptr;
     h->bp_elems = 0;
-    if (hipMalloc(&h->bp, static_cast<size_t>(elems > 0 ? elems : 1) * h->vb) != hipSuccess)
+    if (dev_alloc(&h->bp, elems * static_cast<int64_t>(h->vb)) != hipSuccess)
       return kErrOom;
     h->bp_elems = elems;
   }
@@ -1516,10 +1542,9 @@ int init_handle_common(sptrsv_handle_t h, hipStream_t s) {
   h->scratch.ticket = dalloc<int>(1, &err);
   h->scratch.status = dalloc<int>(1, &err);
   h->scratch.epoch = dalloc<unsigned>(1, &err);
-  h->scratch.flags = dalloc<unsigned>(h->n, &err);
+  if (!h->scratch.flags) h->scratch.flags = dalloc<unsigned>(h->n, &err);
   h->scratch.arrive = dalloc<int>(1, &err);
   if (err) return err;
-  if ((err = ensure_xp(h, h->n))) return err;
   HIPCHK(hipEventCreateWithFlags(&h->order_ev, hipEventDisableTiming));
   HIPCHK(launch_init_scratch(h->scratch, h->n, s));
   return kOk;
@@ -1536,16 +1561,22 @@ int analyze_from_host(sptrsv_handle_t h, const int* row_ptr, const int* col_idx,
   if ((st = init_handle_common(h, s))) return st;
   if ((st = upload_plan(h->fwd, h->vb, s))) return st;
   if ((st = gather(h, h->fwd, vals, s))) return st;
-  if ((st = read_status(h, s, true))) return st;
   find_offsets(h, row_ptr, col_idx, s);
   build_strip_state(h, h->fwd, h->upper, s);
-  return kOk;
+  if ((st = ensure_xp(h, h->n))) return st;
+  return read_status(h, s, true);
+}
+
+// Bytes of a plan's value buffer, whatever part of the diagonal is stored.
+int64_t values_bytes(sptrsv_handle_t h) {
+  const int64_t noff = h->unit ? h->nnz : std::max<int64_t>(0, h->nnz - h->n);
+  return block_bytes((noff + 2 * static_cast<int64_t>(h->n)) * static_cast<int64_t>(h->vb));
 }
 
 // Takes over the arrays of a device analysis as plan ps (the host plan keeps
-// nlev, ilev and off_ptr; the rest is downloaded only if the host needs it)
-// and allocates its value buffer.
-int install_device_plan(sptrsv_handle_t h, PlanState& ps, DeviceAnalysis& da, bool upper) {
+// nlev and ilev; the rest is downloaded only if the host needs it); its
+// spare part begins with the value buffer.
+void install_device_plan(sptrsv_handle_t h, PlanState& ps, DeviceAnalysis& da, bool upper) {
   HostPlan& p = ps.h;
   p = HostPlan();
   p.n = h->n;
@@ -1556,7 +1587,6 @@ int install_device_plan(sptrsv_handle_t h, PlanState& ps, DeviceAnalysis& da, bo
   p.unit_diag = h->unit;
   p.ilev = std::move(da.ilev);
   p.pos_ilev = p.ilev;
-  p.off_ptr = std::move(da.off_ptr_h);
   p.max_row_len = da.max_row_len;
   DevPlan& d = ps.d;
   d = DevPlan();
@@ -1569,25 +1599,23 @@ int install_device_plan(sptrsv_handle_t h, PlanState& ps, DeviceAnalysis& da, bo
   d.off_src = da.off_src;
   d.diag_src = da.diag_src;
   d.pos_row = da.pos_row;
+  d.row_pos = da.row_pos;
+  ps.mem = da.mem;
   ps.a_level = da.level;
   ps.a_depcnt = da.depcnt;
   ps.a_jlev = da.jlev;
   ps.host_complete = false;
+  ps.vals_buf = da.spare;
   da = DeviceAnalysis();        // the plan owns the arrays now
-  int err = kOk;
-  ps.vals_buf =
-      dalloc<char>((static_cast<size_t>(d.noff) + 2 * static_cast<size_t>(h->n)) * h->vb, &err);
-  if (!ps.vals_buf) return err;
   d.off_val = ps.vals_buf;
   d.diag = static_cast<char*>(ps.vals_buf) + static_cast<size_t>(d.noff) * h->vb;
   d.dinv = static_cast<char*>(d.diag) + static_cast<size_t>(h->n) * h->vb;
   ps.built = true;
-  return kOk;
 }
 
 // Setup on the device (levels, level-ordered layout) from the caller's device
-// pattern; the plan stays on the device, only nlev, ilev and off_ptr come to
-// the host (for the chunk tables).  Returns kErrNotSupported for a pattern
+// pattern; the plan stays on the device, only nlev and ilev come to the
+// host (for the chunk tables; off_ptr too if rows of several lanes need it).  Returns kErrNotSupported for a pattern
 // the device route does not take; the caller then runs the host route.
 int analyze_on_device(sptrsv_handle_t h, const int* row_ptr, const int* col_idx, const void* vals,
                       hipStream_t s, bool copy_pattern = true) {
@@ -1598,14 +1626,15 @@ int analyze_on_device(sptrsv_handle_t h, const int* row_ptr, const int* col_idx,
     h->num_cu = ncu;
   find_offsets(h, row_ptr, col_idx, s);
   DeviceAnalysis da;
+  // behind the values: the flags of the flag schedules and the pattern
+  const int64_t vb = values_bytes(h), nb = block_bytes((static_cast<int64_t>(h->n) + 1) * 4);
   int st = device_analysis(h->n, h->nnz, row_ptr, col_idx, h->upper, h->unit, h->num_cu,
-                           grid_guesses(h, h->upper), s, da);
+                           grid_guesses(h, h->upper),
+                           vb + nb + (copy_pattern ? nb + block_bytes(h->nnz * 4) : 0), s, da);
   if (st) return st;
-  if ((st = install_device_plan(h, h->fwd, da, h->upper))) {
-    free_device_analysis(da);
-    return st;
-  }
-  int err = kOk;
+  char* spare = da.spare + vb;
+  install_device_plan(h, h->fwd, da, h->upper);
+  h->scratch.flags = reinterpret_cast<unsigned*>(spare);
   // the handle's own copy of the pattern, for what is built later (a
   // batched handle's concatenation already is its own)
   h->pattern_host = false;
@@ -1613,9 +1642,8 @@ int analyze_on_device(sptrsv_handle_t h, const int* row_ptr, const int* col_idx,
     h->rp_dev = const_cast<int*>(row_ptr);
     h->col_dev = const_cast<int*>(col_idx);
   } else {
-    h->rp_dev = dalloc<int>(static_cast<size_t>(h->n) + 1, &err);
-    h->col_dev = dalloc<int>(static_cast<size_t>(h->nnz), &err);
-    if (err) return err;
+    h->rp_dev = reinterpret_cast<int*>(spare + nb);
+    h->col_dev = reinterpret_cast<int*>(spare + 2 * nb);
     HIPCHK(hipMemcpyAsync(h->rp_dev, row_ptr, (static_cast<size_t>(h->n) + 1) * sizeof(int),
                           hipMemcpyDeviceToDevice, s));
     if (h->nnz > 0)
@@ -1624,9 +1652,9 @@ int analyze_on_device(sptrsv_handle_t h, const int* row_ptr, const int* col_idx,
   }
   if ((st = init_handle_common(h, s))) return st;
   if ((st = gather(h, h->fwd, vals, s))) return st;
-  if ((st = read_status(h, s, true))) return st;
   build_strip_state(h, h->fwd, h->upper, s);
-  return kOk;
+  if ((st = ensure_xp(h, h->n))) return st;
+  return read_status(h, s, true);
 }
 
 void free_block(BlockState& b) {
@@ -1640,6 +1668,9 @@ void free_block(BlockState& b) {
 void destroy_handle(sptrsv_handle_t h) {
   if (!h) return;
   if (h->order_ev) (void)hipEventDestroy(h->order_ev);
+  dfree_of(h->fwd, h->scratch.flags);
+  if (h->rp_dev != h->rp_cat) dfree_of(h->fwd, h->rp_dev);
+  if (h->col_dev != h->col_cat) dfree_of(h->fwd, h->col_dev);
   free_plan(h->fwd);
   free_plan(h->trn);
   free_block(h->blk[0]);
@@ -1647,7 +1678,6 @@ void destroy_handle(sptrsv_handle_t h) {
   dfree(h->scratch.ticket);
   dfree(h->scratch.status);
   dfree(h->scratch.epoch);
-  dfree(h->scratch.flags);
   dfree(h->scratch.arrive);
   h->xp_buf.reset();
   h->xp = nullptr;
@@ -1655,8 +1685,6 @@ void destroy_handle(sptrsv_handle_t h) {
   dfree(h->rp_cat);
   dfree(h->col_cat);
   dfree(h->vals_cat);
-  if (h->rp_dev != h->rp_cat) dfree(h->rp_dev);
-  if (h->col_dev != h->col_cat) dfree(h->col_dev);
   dfree(h->col_acc);
   dfree(h->col_cnt);
   for (auto& pr : h->ev_pool) {
@@ -2405,7 +2433,7 @@ const char* sptrsv_status_string(int status) {
 int sptrsv_destroy(sptrsv_handle_t h) {
   if (!h) return kErrInvalidArg;
   if (h->live_graphs > 0) return kErrBusy;   // their kernels use the handle's buffers
-  // the handle's own work first (hipFree also waits for the device)
+  // the handle's own work first (freeing also waits for the device)
   if (h->order_ev && h->order_pending) (void)hipEventSynchronize(h->order_ev);
   destroy_handle(h);
   return kOk;

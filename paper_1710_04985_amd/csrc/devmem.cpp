@@ -1,0 +1,126 @@
+// A store of freed device blocks, so that the setup of the next handle finds
+// its few large allocations at hand: the driver takes 40 to 200 us to give out
+// a block of this size and, depending on its state, 0.3 or 4 to 6 ms to take
+// one back (128^3 7-point: blocks of 131 and 267 MB).
+//
+// The store is bounded (kKeepBytes over all devices; the block freed longest
+// ago goes first), gives everything back when an allocation fails, and gives
+// back a block that kKeepFrees later ones have passed over.  A block enters it
+// only when its device is idle, so the next owner may use it on any stream.
+#include "devmem.hpp"
+
+#include <iterator>
+#include <list>
+#include <map>
+#include <mutex>
+
+namespace sptrsv {
+namespace {
+
+constexpr int64_t kLarge = 1 << 20;          // smaller ones cost the runtime about 1 us
+constexpr int64_t kKeepBytes = 1ll << 30;
+constexpr int64_t kKeepFrees = 64;
+
+struct Block {
+  void* p;
+  int64_t bytes;
+  int device;
+  int64_t freed;                             // count of frees when it was stored
+};
+
+struct Store {
+  std::mutex mu;
+  std::map<void*, Block> live;               // large blocks in use
+  std::list<Block> kept;                     // oldest first
+  int64_t kept_bytes = 0, frees = 0;
+
+  // Hands back the oldest blocks until `bytes` remain, and those passed over.
+  void trim(int64_t bytes) {
+    while (!kept.empty() && (kept_bytes > bytes || frees - kept.front().freed > kKeepFrees)) {
+      (void)hipFree(kept.front().p);
+      kept_bytes -= kept.front().bytes;
+      kept.pop_front();
+    }
+  }
+};
+
+// never destroyed: the runtime may be gone when static destructors run
+Store& store() {
+  static Store* s = new Store;
+  return *s;
+}
+
+}  // namespace
+
+hipError_t dev_alloc(void** p, int64_t bytes) {
+  *p = nullptr;
+  if (bytes < 1) bytes = 1;
+  if (bytes < kLarge) {
+    hipError_t e = hipMalloc(p, static_cast<size_t>(bytes));
+    if (e == hipSuccess) return e;
+    Store& s = store();
+    std::lock_guard<std::mutex> lock(s.mu);
+    if (s.kept.empty()) return e;
+    s.trim(0);
+    return hipMalloc(p, static_cast<size_t>(bytes));
+  }
+  int device = 0;
+  if (const hipError_t e = hipGetDevice(&device)) return e;
+  constexpr int64_t kUnit = 2 << 20;
+  bytes = (bytes + kUnit - 1) / kUnit * kUnit;
+  Store& s = store();
+  std::lock_guard<std::mutex> lock(s.mu);
+  // the smallest block that fits, if at most a quarter of it would lie idle
+  auto best = s.kept.end();
+  for (auto it = s.kept.begin(); it != s.kept.end(); ++it)
+    if (it->device == device && it->bytes >= bytes && it->bytes - bytes <= it->bytes / 4 &&
+        (best == s.kept.end() || it->bytes < best->bytes))
+      best = it;
+  if (best != s.kept.end()) {
+    *p = best->p;
+    s.kept_bytes -= best->bytes;
+    s.live[best->p] = *best;
+    s.kept.erase(best);
+    return hipSuccess;
+  }
+  hipError_t e = hipMalloc(p, static_cast<size_t>(bytes));
+  if (e != hipSuccess && !s.kept.empty()) {
+    s.trim(0);
+    e = hipMalloc(p, static_cast<size_t>(bytes));
+  }
+  if (e == hipSuccess) s.live[*p] = Block{*p, bytes, device, 0};
+  return e;
+}
+
+void dev_free(void* p) {
+  if (!p) return;
+  Store& s = store();
+  Block b{nullptr, 0, 0, 0};
+  {
+    std::lock_guard<std::mutex> lock(s.mu);
+    auto it = s.live.find(p);
+    if (it != s.live.end()) {
+      b = it->second;
+      s.live.erase(it);
+    }
+  }
+  bool idle = false;
+  if (b.p && b.bytes <= kKeepBytes) {
+    int device = 0;
+    idle = hipGetDevice(&device) == hipSuccess &&
+           (device == b.device || hipSetDevice(b.device) == hipSuccess);
+    idle = idle && hipDeviceSynchronize() == hipSuccess;
+    if (device != b.device) (void)hipSetDevice(device);
+  }
+  if (!idle) {
+    (void)hipFree(p);
+    return;
+  }
+  std::lock_guard<std::mutex> lock(s.mu);
+  b.freed = ++s.frees;
+  s.kept.push_back(b);
+  s.kept_bytes += b.bytes;
+  s.trim(kKeepBytes);
+}
+
+}  // namespace sptrsv

@@ -9,6 +9,7 @@
 
 #include "analysis.hpp"
 #include "device_common.hpp"
+#include "devmem.hpp"
 
 namespace sptrsv {
 namespace {
@@ -137,15 +138,15 @@ k_strip_boxes(const StripGrid* __restrict__ grids, int nsys, const int* __restri
   }
 }
 
-// entry slots the longest row needs
+// entry slots the row that needs most needs, with four partial sums
 __global__ void __launch_bounds__(256)
 k_strip_slots(int n, const int* __restrict__ off_ptr, const unsigned char* __restrict__ lanes_lg,
-              int acc, StripCount* cnt) {
+              StripCount* cnt) {
   int slots = 0;
   const int stride = gridDim.x * blockDim.x;
   for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += stride) {
-    const int len = off_ptr[k + 1] - off_ptr[k], lg = lanes_lg ? lanes_lg[k] : 0;
-    if (len > 0) slots = max(slots, lg > 2 ? kStripMaxEntries + 1 : entry_slot(len - 1, lg, acc) + 1);
+    const int len = off_ptr[k + 1] - off_ptr[k], lg = lanes_lg[k];
+    if (len > 0) slots = max(slots, lg > 2 ? kStripMaxEntries + 1 : entry_slot(len - 1, lg, 4) + 1);
   }
   for (int o = 32; o > 0; o >>= 1) slots = max(slots, __shfl_xor(slots, o, 64));
   if ((threadIdx.x & 63) == 0 && slots) atomicMax(&cnt->slots, slots);
@@ -703,13 +704,11 @@ inline int blocks(int64_t work, int per) {
 struct DevFree {
   std::vector<void*> p;
   ~DevFree() {
-    for (void* q : p)
-      if (q) (void)hipFree(q);
+    for (void* q : p) dev_free(q);
   }
   template <typename T> bool get(T** out, int64_t count) {
     void* q = nullptr;
-    if (hipMalloc(&q, static_cast<size_t>(count > 0 ? count : 1) * sizeof(T)) != hipSuccess)
-      return false;
+    if (dev_alloc(&q, count * static_cast<int64_t>(sizeof(T))) != hipSuccess) return false;
     p.push_back(q);
     *out = static_cast<T*>(q);
     return true;
@@ -742,7 +741,7 @@ template <typename T> hipError_t launch_strip_gather(const DevPlan& p, const Dev
 }
 
 void free_strips(DevStrips& t) {
-  if (t.mem) (void)hipFree(t.mem);
+  dev_free(t.mem);
   t = DevStrips();
 }
 
@@ -771,6 +770,7 @@ int build_strips(const DevPlan& p, const std::vector<StripGrid>& grids, int max_
       !f.get(&box_strip_d, nboxes) || !f.get(&boxes_d, nboxes) || !f.get(&cnt, 1))
     return kErrOom;
   StripCount c{0, 0, 0};
+  if (!lanes_lg) c.slots = max_len;   // an entry, a slot
   std::vector<int2> box(nboxes);
 #define TCHK(expr)                            \
   do {                                        \
@@ -779,8 +779,10 @@ int build_strips(const DevPlan& p, const std::vector<StripGrid>& grids, int max_
   TCHK(hipMemcpyAsync(grids_d, gh.data(), nsys * sizeof(StripGrid), hipMemcpyHostToDevice, s));
   TCHK(hipMemcpyAsync(box0_d, box0.data(), (nsys + 1) * sizeof(int), hipMemcpyHostToDevice, s));
   TCHK(hipMemcpyAsync(cnt, &c, sizeof(c), hipMemcpyHostToDevice, s));
-  k_strip_slots<<<std::min(blocks(p.n, 256), 1024), 256, 0, s>>>(p.n, p.off_ptr, lanes_lg, acc, cnt);
-  TCHK(hipGetLastError());
+  if (lanes_lg) {
+    k_strip_slots<<<std::min(blocks(p.n, 256), 1024), 256, 0, s>>>(p.n, p.off_ptr, lanes_lg, cnt);
+    TCHK(hipGetLastError());
+  }
   k_strip_boxes<<<static_cast<int>(nboxes), 64, 0, s>>>(grids_d, nsys, box0_d, box_d, cnt);
   TCHK(hipGetLastError());
   TCHK(hipMemcpyAsync(box.data(), box_d, nboxes * sizeof(int2), hipMemcpyDeviceToHost, s));
@@ -846,8 +848,7 @@ int build_strips(const DevPlan& p, const std::vector<StripGrid>& grids, int max_
                 b_src = up(t.nrec * E * 256), b_dsrc = up(t.nrec * 256),
                 b_lane = up(t.nstrips * 64ll * sizeof(StripLane)),
                 b_info = up(t.nstrips * static_cast<int64_t>(sizeof(StripInfo)));
-  if (hipMalloc(&t.mem, static_cast<size_t>(b_quad + b_tail + b_src + b_dsrc + b_lane + b_info)) !=
-      hipSuccess)
+  if (dev_alloc(&t.mem, b_quad + b_tail + b_src + b_dsrc + b_lane + b_info) != hipSuccess)
     return kErrOom;
   char* at = static_cast<char*>(t.mem);
   auto take = [&](int64_t b) {
