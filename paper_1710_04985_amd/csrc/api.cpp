@@ -697,7 +697,7 @@ bool strip_rule(sptrsv_handle_t h) {
 //  * rows longer than 64 entries, or levels of more than 8,192 rows on
 //    average, take two wavefronts per CU (power-law, batched ILU(0));
 //  * rows longer than 64 entries take 32-byte slots for the solution
-//    (power-law: 0.72 against 0.82 ms packed).
+//    (power-law 1M rows: 604 us against 709 packed).
 Config resolve(sptrsv_handle_t h) {
   if (h->tuned) return h->tuned_cfg;
   Config c{h->algo, h->group, h->epl, h->sync, h->rpl, h->grid, h->assign};
@@ -731,6 +731,18 @@ Config resolve(sptrsv_handle_t h) {
   if (!(h->set_mask & kSetStride) && long_rows) c.stride = 32 / h->vb;
   c.strip = strip_rule(h) && !h->set_mask && c.poll == 1 && c.rpl == 1;
   return c;
+}
+
+// Whether the static schedules publish each row of a chunk as soon as it is
+// ready: with overlapped polling, in triangles whose longer rows take several
+// lanes.  There most dependencies are ready before a chunk is reached and the
+// last ones come one at a time (row-wise, us per solve, whole chunks against
+// row by row: power-law 1M rows 738 / 604, its transpose in FP32 of 777,777
+// rows 602 / 444, 128^3 27-point 2198 / 1220); with rows of at most four
+// entries most of a lane's are missing together, and asking for all of them
+// at once is faster (128^3 7-point 375 / 694, 256 2-D ILU(0) factors 571 / 727).
+int publish_early(const PlanState& ps, const Config& c) {
+  return c.poll != 0 && c.group != 1 && ps.h.max_row_len > 4 ? 1 : 0;
 }
 
 // Schedule of a solve with nrhs > 1 right-hand sides: sptrsv_tune_multi's
@@ -1264,6 +1276,7 @@ int solve_impl(sptrsv_handle_t h, PlanState& ps, const Config& c_in, const void*
   a.ld = ld;
   a.spin_limit = h->spin_limit;
   a.poll = c.poll;
+  a.early = publish_early(ps, c);
   a.xp_stride = stride;
   a.res_limit = h->res_limit;
   a.coop = h->coop;
@@ -1423,6 +1436,7 @@ int solve_columns(sptrsv_handle_t h, PlanState& ps, const Config& c_in, const vo
   a.ld = ld;
   a.spin_limit = h->spin_limit;
   a.poll = c.poll;
+  a.early = publish_early(ps, c);
   a.xp_stride = c.stride;
   a.xp_col = col_elems;
   a.res_limit = h->res_limit;

@@ -152,6 +152,7 @@ template <typename T> struct KArgs {
   int* arrive;
   int res_limit;
   int spin_limit;
+  int early;         // publish_when_ready instead of whole chunks
   int poll;          // 1: overlapped polling of all slots, 0: single rounds of pending ones
   const int* chunk_col;   // column-batched tables: right-hand side of each chunk
   int64_t xp_col;         // elements between the columns of xp (column-batched)
@@ -435,6 +436,103 @@ template <typename T> struct StageD {   // first entries of the lane, raw
   int q;
 };
 
+// Stage D of a chunk whose rows have at most four entries a lane: waits for
+// the values still missing in xv, and publishes each row as soon as its own
+// have come instead of with the last row of the chunk.
+//
+// Bound by the hop from a row to the rows of the next level, about 1.3 us on
+// irregular triangles (0.7 at best, where one row has the wavefront): a round
+// of polls reads up to 64 scattered lines, and a chunk waits for some of the
+// last values of nearly every level, while a chain of rows waits for its own
+// only.  So a lane asks for one value at a time, the one of the earliest
+// position, so that the last to come is also the last asked for, and lanes
+// that wait for nothing stay out of the round.  Power-law triangle of 1M rows,
+// whole solve: 738 us with whole chunks and two overlapped rounds over all
+// slots; published by row 685; two single asks in flight 690, one 635;
+// earliest position first 611; idle lanes masked 604.  The caller's x is
+// written last: polls would wait for the stores' acknowledgement.
+template <typename T>
+__device__ __forceinline__ void publish_when_ready(const T* xq, int xs, const int (&j)[4],
+                                                   const T (&v)[4], T (&xv)[4], T bi, T dinv, int lg,
+                                                   bool live, int lane, T* slot, T* xo,
+                                                   int spin_limit, int* status) {
+  const int G = 1 << lg;
+  const unsigned long long mine = (G == 64 ? ~0ull : (1ull << G) - 1) << (lane & ~(G - 1));
+  const bool first = (lane & (G - 1)) == 0;
+  unsigned pend = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (j[q] >= 0 && is_sentinel(xv[q])) pend |= 1u << q;
+  bool left = live;                   // row not published yet
+  T xi = T(0);
+  auto publish_rows = [&]() -> bool { // false: none left
+    const bool now = left && (__ballot(pend == 0) & mine) == mine;
+    if (__any(now)) {
+      T sum = T(0);
+      // an entry that the row lacks adds -0 * 0 = -0, which changes nothing
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        sum = fma_t(j[q] >= 0 ? v[q] : -T(0), j[q] >= 0 ? xv[q] : T(0), sum);
+      sum = group_sum(sum, lg);
+      if (now) {
+        xi = canonical((bi - sum) * dinv);
+        if (first) store_agent(slot, xi);
+        left = false;
+      }
+    }
+    return __any(left);
+  };
+  // the missing value asked for next: the one of the earliest position, so that
+  // the last to come is also the last asked for
+  unsigned bit = 0;
+  const T* p = xq;
+  auto choose = [&]() {
+    int best = INT32_MAX;
+    bit = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (((pend >> q) & 1u) && j[q] < best) {
+        best = j[q];
+        bit = 1u << q;
+      }
+    p = xq + static_cast<int64_t>(bit ? best : 0) * xs;
+  };
+  // false: no row is left
+  auto take = [&](T got) -> bool {
+    const bool hit = bit != 0 && !is_sentinel(got);
+    if (!__any(hit)) return true;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (hit && bit == 1u << q) xv[q] = got;
+    if (hit) pend &= ~bit;
+    if (!publish_rows()) return false;
+    if (hit) choose();
+    return true;
+  };
+  if (publish_rows()) {
+    choose();
+    bool late = true;
+    for (int s = 1; s <= spin_limit; ++s) {
+      T got = T(0);
+      if (bit) got = load_agent(p);
+      if (!take(got)) {
+        late = false;
+        break;
+      }
+      if ((s & 63) == 63 && (load_status(status) & kStatusTimeout)) break;
+    }
+    if (late) {
+      raise_status(status, kStatusTimeout);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if ((pend >> q) & 1u) xv[q] = __builtin_nan("");
+      pend = 0;
+      (void)publish_rows();
+    }
+  }
+  if (live && first) *xo = xi;
+}
+
 template <typename T, int kStride, bool kCols>
 __global__ void __launch_bounds__(256)
 k_self_static(KArgs<T> a, const int* __restrict__ cstart, const int* __restrict__ cmeta,
@@ -524,24 +622,31 @@ k_self_static(KArgs<T> a, const int* __restrict__ cstart, const int* __restrict_
     // ---- D (finish): wait, accumulate, rest of the row, group sum, publish
     if (sd.c >= 0) {
       const int G = 1 << sd.lg;
-      T sum = T(0);
-      if (sd.k >= 0) {
-        wait_values<T, 4>(xq, xs, sd.j, xv, a.spin_limit, a.status, a.poll != 0);
+      const int64_t qo = kCols ? static_cast<int64_t>(sd.q) : 0;
+      T* const slot = a.xp + qo * a.xp_col + static_cast<int64_t>(sd.k >= 0 ? sd.k : 0) * xs;
+      T* const xo = a.x + qo * a.ld + sd.i;
+      if (a.early && !__any(sd.k >= 0 && sd.e + 4 * G < sd.e1)) {
+        publish_when_ready<T>(xq, xs, sd.j, sd.v, xv, sd.bi, sd.d, sd.lg, sd.k >= 0, lane, slot, xo,
+                              a.spin_limit, a.status);
+      } else {
+        T sum = T(0);
+        if (sd.k >= 0) {
+          wait_values<T, 4>(xq, xs, sd.j, xv, a.spin_limit, a.status, a.poll != 0);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          if (sd.j[q] < 0) continue;
-          sum = fma_t(sd.v[q], xv[q], sum);
+          for (int q = 0; q < 4; ++q) {
+            if (sd.j[q] < 0) continue;
+            sum = fma_t(sd.v[q], xv[q], sum);
+          }
+          if (sd.e + 4 * G < sd.e1)
+            sum = row_dot<T, true>(a.off_pos, a.off_val, sd.e + 4 * G, sd.e1, G, xq, xs,
+                                   a.spin_limit, a.status, a.poll != 0, sum);
         }
-        if (sd.e + 4 * G < sd.e1)
-          sum = row_dot<T, true>(a.off_pos, a.off_val, sd.e + 4 * G, sd.e1, G, xq, xs,
-                                 a.spin_limit, a.status, a.poll != 0, sum);
-      }
-      sum = group_sum(sum, sd.lg);
-      if (sd.k >= 0 && (lane & (G - 1)) == 0) {
-        const T xi = canonical((sd.bi - sum) * sd.d);
-        const int64_t qo = kCols ? static_cast<int64_t>(sd.q) : 0;
-        store_agent(a.xp + qo * a.xp_col + static_cast<int64_t>(sd.k) * xs, xi);
-        a.x[qo * a.ld + sd.i] = xi;
+        sum = group_sum(sum, sd.lg);
+        if (sd.k >= 0 && (lane & (G - 1)) == 0) {
+          const T xi = canonical((sd.bi - sum) * sd.d);
+          store_agent(slot, xi);
+          *xo = xi;
+        }
       }
     } else if (sc.c < 0 && sb.c < 0 && nb.c < 0) {
       return;                         // pipeline drained
@@ -1226,6 +1331,7 @@ template <typename T> KArgs<T> make_args(const SolveArgs& s) {
   a.arrive = s.scratch.arrive;
   a.res_limit = s.res_limit;
   a.spin_limit = s.spin_limit;
+  a.early = s.early;
   a.poll = s.poll;
   a.chunk_col = s.chunks ? s.chunks->col : nullptr;
   a.xp_col = s.xp_col;
