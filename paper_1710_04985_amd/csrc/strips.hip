@@ -381,13 +381,14 @@ template <int N, int I = 0, typename F> __device__ __forceinline__ void unroll(F
   }
 }
 
-// Bound by the chain of steps: one per level of the triangle, about 0.1 us each
-// (wavefront 0 issues some 33 instructions a step; the LDS round trip and the
-// row's FMAs take 42 ns of it), plus 1 to 2 us per strip that the chain
-// crosses.  us per triangle, this kernel against a wavefront per 64-row box of
-// the grid (waiting once per box) and against a hop per level: 128^3 7-point
-// 96 / 165 / 375, 1024^2 9-point 341 / 632 / 2503, 128^3 27-point 410 / 485 /
-// 2196, 256 2-D ILU(0) factors 114 / 190 / 561.
+// Bound by the chain of steps: one per level of the triangle, 0.08 to 0.1 us
+// each (wavefront 0 issues some 33 instructions a step; the LDS round trip and
+// the row's FMAs take 42 ns of it), plus 1 to 2 us per strip that the chain
+// crosses; with 13 entries a row by the 9 KB that a step loads, 0.2 us at the
+// 45 GB/s that one wavefront draws.  us per triangle, this kernel against a
+// wavefront per 64-row box of the grid (waiting once per box) and against a hop
+// per level: 128^3 7-point 95 / 165 / 375, 1024^2 9-point 329 / 632 / 2503,
+// 128^3 27-point 408 / 485 / 2196, 256 2-D ILU(0) factors 112 / 190 / 561.
 //
 // Workgroups claim strips from a ticket, in dependency order (by the sum of
 // the strips' lane coordinates): whatever a strip reads belongs to strips
@@ -405,7 +406,11 @@ template <int N, int I = 0, typename F> __device__ __forceinline__ void unroll(F
 //     several steps, and what has arrived goes into the ring (overlapping two
 //     rounds only adds traffic: 128^3 7-point 100 us against 96);
 //   2 stores results to the caller's x, eight steps at a time: a line's rows
-//     are then neighbours in memory, where one step's are 64 lines apart;
+//     are then neighbours in memory, where one step's are 64 lines apart (and
+//     it looks once per eight steps: 1024^2 9-point, whole solve of both
+//     triangles repeated, 735 us with a look per step, 691 so, 665 with the
+//     solver's own looks at wavefronts 2 and 3 read ahead; 740 where the
+//     records come from memory every time);
 //   3 loads b the same way, into LDS.
 // With A = 4 slot q adds to partial sum q mod 4, and the sums are added in the
 // order of the row-wise kernels' butterfly (rows that those kernels give fewer
@@ -470,12 +475,13 @@ __global__ void __launch_bounds__(kStripThreads) k_strip(SArgs<T> a) {
       // lanes that nobody reads publish into a line of the strip's own, so
       // that the store is unconditional and counted like the loads
       T* pub = l.pub >= 0 ? xp + inf.pub0 + l.pub
-                          : a.xp + a.npub * a.nrhs + task * static_cast<int64_t>(kDumpSlot);
+                          : a.xp + a.npub * a.nrhs + task * static_cast<int64_t>(kDumpSlot) +
+                                lane % kDumpSlot;
       const int64_t pub_step = l.pub >= 0 ? npub : 0;
       unsigned w[D][NW];
       auto fetch = [&](auto k, int s) {
         const int sc = min(max(s, rlo), rhi);
-        const unsigned oq = static_cast<unsigned>(sc) * (NQ * 1024u) + lane * 16u;
+        const unsigned oq = __umul24(sc, NQ * 1024) + lane * 16u;
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
           const uint4 v = *reinterpret_cast<const uint4*>(quad + oq + q * 1024);
@@ -485,7 +491,7 @@ __global__ void __launch_bounds__(kStripThreads) k_strip(SArgs<T> a) {
           w[k][4 * q + 3] = v.w;
         }
         if constexpr (NT > 0) {
-          const unsigned ot = (static_cast<unsigned>(sc) * 64u + lane) * (NT * 4u);
+          const unsigned ot = __umul24(sc, NT * 256) + lane * (NT * 4u);
           const auto v = *reinterpret_cast<const Words<NT>*>(tail + ot);
 #pragma unroll
           for (int q = 0; q < NT; ++q) w[k][4 * NQ + q] = v.w[q];
@@ -544,13 +550,22 @@ __global__ void __launch_bounds__(kStripThreads) k_strip(SArgs<T> a) {
       unroll<D - 1>([&](auto k) { fetch(k, k); });
       address(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
       constexpr int U = kRingSteps;
+      int bready = 0, stored = 0;
       for (int s = 0; s < steps; s += U)
         unroll<U>([&](auto k) {
           // every eight steps: their b is in place, and the rows that they
-          // overwrite have been taken over
-          if (k % kBlock == 0) {
-            wait_counter(&cnt.bready, s + k + kBlock, a.status);
-            wait_counter(&cnt.stored, s + k + kBlock - kRingSteps, a.status);
+          // overwrite have been taken over (both read a step early, so that the
+          // solver does not stand still for the LDS)
+          if constexpr (k % kBlock == 0) {
+            const int b_end = s + k + kBlock, x_end = b_end - kRingSteps;
+            if (__builtin_expect(wave_uniform(bready) < b_end, 0))
+              wait_counter(&cnt.bready, b_end, a.status);
+            if (__builtin_expect(wave_uniform(stored) < x_end, 0))
+              wait_counter(&cnt.stored, x_end, a.status);
+          }
+          if constexpr (k % kBlock == kBlock - 1) {
+            bready = __hip_atomic_load(&cnt.bready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            stored = __hip_atomic_load(&cnt.stored, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
           }
           step(k, s + k);
         });
@@ -636,10 +651,12 @@ __global__ void __launch_bounds__(kStripThreads) k_strip(SArgs<T> a) {
         int done = 0;
         for (int s0 = 0; s0 < steps; s0 += kBlock) {
           const int end = min(s0 + kBlock, steps);
-          for (int s = s0; s < end; ++s) {
-            if (__builtin_expect(done <= s, 0)) done = wait_counter(&cnt.done, s + 1, a.status);
-            xout[lane * kXCols + (s - s0)] = ring[(s & (kRingSteps - 1)) * kRingCols + lane];
-          }
+          if (done < end) done = wait_counter(&cnt.done, end, a.status);
+          T xs[kBlock];
+#pragma unroll
+          for (int q = 0; q < kBlock; ++q) xs[q] = ring[((s0 + q) & (kRingSteps - 1)) * kRingCols + lane];
+#pragma unroll
+          for (int q = 0; q < kBlock; ++q) xout[lane * kXCols + q] = xs[q];
           write_counter(&cnt.stored, end);
 #pragma unroll
           for (int i = 0; i < kBlock; ++i) {
