@@ -44,6 +44,14 @@ struct Store {
   }
 };
 
+// Waits for all work on the current device.  By a free, which does so, and not
+// by hipDeviceSynchronize: that breaks the graph capture of another stream also
+// where the capture allows calls like hipFree.
+bool wait_idle() {
+  void* p = nullptr;
+  return hipMalloc(&p, 1) == hipSuccess && hipFree(p) == hipSuccess;
+}
+
 // never destroyed: the runtime may be gone when static destructors run
 Store& store() {
   static Store* s = new Store;
@@ -109,7 +117,7 @@ void dev_free(void* p) {
     int device = 0;
     idle = hipGetDevice(&device) == hipSuccess &&
            (device == b.device || hipSetDevice(b.device) == hipSuccess);
-    idle = idle && hipDeviceSynchronize() == hipSuccess;
+    idle = idle && wait_idle();
     if (device != b.device) (void)hipSetDevice(device);
   }
   if (!idle) {

@@ -18,7 +18,7 @@ struct DevPlan {
   int* off_src = nullptr;   // [noff]
   int* diag_src = nullptr;  // [n]
   int* pos_row = nullptr;   // [n]
-  int* row_pos = nullptr;   // [n] inverse of pos_row (built on first multi-RHS solve)
+  int* row_pos = nullptr;   // [n] inverse of pos_row (device setup; else on first use)
   void* off_val = nullptr;  // [noff] T
   void* diag = nullptr;     // [n] T, the diagonal (source of other plans' values)
   void* dinv = nullptr;     // [n] T, 1 / diagonal (what the solves multiply by)

@@ -60,3 +60,24 @@ def test_reuse_from_threads_and_streams(sp):
     [t.start() for t in ts]
     [t.join() for t in ts]
     assert not wrong
+
+
+def test_handle_destroyed_beside_a_relaxed_capture(sp):
+    """Giving memory back leaves another stream's capture alone where the
+    capture allows calls like hipFree."""
+    T = W.laplacian_triangle((48, 48, 48))
+    d, b = dev_tri(T), dev(W.uniform_vector(T.n, 3))
+    h = sp.Handle(*d)
+    want = h.solve(b)
+    a = torch.arange(1000.0, device="cuda")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, capture_error_mode="relaxed"):
+        c = a * 2
+        del h
+        e = c + 1
+    for _ in range(3):
+        e.zero_()
+        g.replay()
+        assert torch.equal(e, a * 2 + 1)
+    assert bits_equal(sp.Handle(*d).solve(b), want)
