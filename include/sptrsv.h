@@ -45,6 +45,10 @@
  *     Under graph capture nothing is recorded or waited for: the capturing
  *     stream orders the graph, and the caller orders graph launches against
  *     other work on the handle.
+ *   - Device memory: blocks of 1 MiB and more that a call frees are kept
+ *     for the next handle, at most 1 GiB over all devices; all of it goes
+ *     back when an allocation fails, and a block that 64 later frees have
+ *     passed over goes back by itself.
  *   - n = 0 is valid and every solve on it is a no-op.
  *   - Dependencies are taken from the pattern (Sec. 4.4): an explicitly
  *     stored zero off-diagonal still counts as a dependency.
@@ -101,7 +105,17 @@ typedef enum {
                                XCD-regional static one; two wavefronts per CU for rows
                                of more than 64 entries or levels averaging more than
                                8,192 rows; 32-byte slots for rows of more than 64
-                               entries.  No rule changes the result bits. */
+                               entries.  Triangles whose rows sit on regular grids
+                               (found from the distinct offsets |i - j|, every entry
+                               checked; each system of a batched handle its own grid)
+                               are solved in strips of 64 grid lines instead, under
+                               AUTO and SELF, as long as no lane rule, grid,
+                               assignment, slot width, polling mode, rows per lane or
+                               workgroup size was set: no resident grid is needed, and
+                               sptrsv_get_schedule and sptrsv_get_info keep naming the
+                               row-wise (or block) schedule that takes over where the
+                               strips' buffer does not fit.  No rule changes the result
+                               bits. */
     SPTRSV_ALGO_LEVEL = 1,  /* level-scheduled: one launch per level (Sec. 4.1) */
     SPTRSV_ALGO_SELF = 2,   /* self-scheduled: one persistent launch (Sec. 4.2) */
     SPTRSV_ALGO_BLOCK = 3,  /* level-scheduled inside one workgroup per independent
@@ -311,7 +325,8 @@ int sptrsv_solve(sptrsv_handle_t h, const void *b, void *x, hipStream_t stream);
  * MiB) per GPU, held until the process ends, instead of the handle's
  * buffer, and the call allocates nothing (no hipMalloc, hipFree, event or
  * library allocation).  Needs n * slot stride * value bytes <= 64 MiB
- * (FP64 packed: up to 8,388,608 rows), else SPTRSV_ERR_TOO_LARGE.  The work
+ * (FP64 packed: up to 8,388,608 rows), else SPTRSV_ERR_TOO_LARGE (a solve in
+ * strips whose published values do not fit runs row-wise).  The work
  * tables of the handle's current schedule must already exist: the analysis
  * builds those of the default schedule and sptrsv_tune those of its choice
  * (as does any earlier sptrsv_solve or graph capture with that schedule);
@@ -385,7 +400,9 @@ int sptrsv_tune(sptrsv_handle_t h, const void *b, void *x, hipStream_t stream);
  * option excludes it) on the caller's B and X, and keeps the fastest for
  * this nrhs.  Without it, options left unset follow the column count: 2, 4
  * or 8 wavefronts per CU from 2, 8 or 16 columns, XCD-regional assignment up
- * to 4 columns and round-robin beyond, one row per lane group.  Does nothing
+ * to 4 columns and round-robin beyond, one row per lane group; triangles on
+ * grids are solved in strips, a column of a strip at a time (see
+ * SPTRSV_ALGO_AUTO), which is one of the candidates.  Does nothing
  * where sptrsv_solve_multi solves with the single-RHS schedule (long
  * rows).  B != X.
  * Blocking.  Changing a schedule option discards the choice. */
