@@ -384,11 +384,12 @@ template <int N, int I = 0, typename F> __device__ __forceinline__ void unroll(F
 // Bound by the chain of steps: one per level of the triangle, 0.08 to 0.1 us
 // each (wavefront 0 issues some 33 instructions a step; the LDS round trip and
 // the row's FMAs take 42 ns of it), plus 1 to 2 us per strip that the chain
-// crosses; with 13 entries a row by the 9 KB that a step loads, 0.2 us at the
-// 45 GB/s that one wavefront draws.  us per triangle, this kernel against a
+// crosses; with 13 entries a row by the 10 KB that a step loads: one wavefront
+// draws 30 GB/s with 8 loads in flight, 45 with 32, 64 with 56, so those rows'
+// records are loaded up to seven steps ahead (strip_fn).  us per triangle, this kernel against a
 // wavefront per 64-row box of the grid (waiting once per box) and against a hop
 // per level: 128^3 7-point 95 / 165 / 375, 1024^2 9-point 329 / 632 / 2503,
-// 128^3 27-point 408 / 485 / 2196, 256 2-D ILU(0) factors 112 / 190 / 561.
+// 128^3 27-point 378 / 485 / 2196, 256 2-D ILU(0) factors 112 / 190 / 561.
 //
 // Workgroups claim strips from a ticket, in dependency order (by the sum of
 // the strips' lane coordinates): whatever a strip reads belongs to strips
@@ -432,7 +433,7 @@ static_assert(kBlock == 8, "eight steps of eight cache lines to a wavefront");
 constexpr int kXCols = kBlock + 1;           // line of the store scratch, likewise
 
 template <typename T, int E, int A, int D>
-__global__ void __launch_bounds__(kStripThreads) k_strip(SArgs<T> a) {
+__global__ void __launch_bounds__(kStripThreads, 1) k_strip(SArgs<T> a) {
   constexpr int VW = sizeof(T) / 4;
   constexpr int CW = (E + 1) * VW;                     // first word of the ring addresses
   constexpr int NW = CW + (E + 1) / 2;
@@ -700,15 +701,28 @@ __global__ void __launch_bounds__(kStripThreads) k_strip(SArgs<T> a) {
 // one-lane solve computes each (one partial sum).
 template <typename T> const void* strip_fn(const DevStrips& t, int nrhs) {
   const int acc = nrhs > 1 ? 1 : t.acc;
-#define SPTRSV_STRIP(E, A, D) \
-  if (t.entries == E && acc == A) return reinterpret_cast<const void*>(k_strip<T, E, A, D>)
+  // Long records, loaded 7 steps ahead instead of 3: faster where they come
+  // from memory, but in FP64 the extra stages sit in accumulation registers, so
+  // a step has more to do (27-point, both triangles, us at 7 / 3 steps: FP64
+  // 20^3 105 / 94, 60x50x40 (27 MB of records) 221 / 201, 200x40x100 (170 MB)
+  // 516 / 546, 128^3 769 / 824; FP32 90 / 91, 183 / 190, 400 / 479, 576 / 688).
+  const bool far = sizeof(T) == 4 || t.nrec * t.words * 256 > (64 << 20);
+#define SPTRSV_STRIP(E, A, D)                                    \
+  if (t.entries == E && acc == A && (E <= 4 || far == (D == 8))) \
+  return reinterpret_cast<const void*>(k_strip<T, E, A, D>)
   SPTRSV_STRIP(2, 1, 16);
   SPTRSV_STRIP(3, 1, 16);
   SPTRSV_STRIP(4, 1, 16);
-  SPTRSV_STRIP(13, 4, 4);
-  SPTRSV_STRIP(15, 4, 4);
-  SPTRSV_STRIP(13, 1, 4);
-  SPTRSV_STRIP(15, 1, 4);
+  SPTRSV_STRIP(13, 4, 8);
+  SPTRSV_STRIP(15, 4, 8);
+  SPTRSV_STRIP(13, 1, 8);
+  SPTRSV_STRIP(15, 1, 8);
+  if constexpr (sizeof(T) == 8) {
+    SPTRSV_STRIP(13, 4, 4);
+    SPTRSV_STRIP(15, 4, 4);
+    SPTRSV_STRIP(13, 1, 4);
+    SPTRSV_STRIP(15, 1, 4);
+  }
 #undef SPTRSV_STRIP
   return nullptr;
 }

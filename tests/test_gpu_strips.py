@@ -248,3 +248,20 @@ def test_levels_of_device_setup(sp, upper):
                                         uplo=uplo, setup=s) for s in ("device", "host"))
         for a, b in zip(devh.export_analysis(), hosth.export_analysis()):
             assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("nrhs", [1, 3])
+def test_long_records_loaded_further_ahead(sp, nrhs):
+    """13 entries a row in FP64, on both sides of the 64 MB of records from
+    which they are loaded further ahead (about 20 and 110 MB)."""
+    for side in (45, 80):
+        T = _varied(W.stencil_triangle((side, side, side), 27), 6)
+        d = dev_tri(T)
+        b = torch.stack([dev(W.uniform_vector(T.n, 20 + q)) for q in range(nrhs)])
+        h = sp.Handle(*d, setup="device").configure(algo=2)
+        ref = sp.Handle(*d, setup="device").configure(algo=2, assign=0, **({"group": 1} if nrhs > 1 else {}))
+        for _ in range(2):
+            x = h.solve_multi(b) if nrhs > 1 else h.solve(b[0])[None]
+            h.status()
+            for q in range(nrhs):
+                assert bits_equal(x[q], ref.solve(b[q]))
