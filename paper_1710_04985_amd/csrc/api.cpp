@@ -713,7 +713,7 @@ Config resolve(sptrsv_handle_t h) {
     if (!h->batched && one_lane && h->block_resident && n <= 65535 && p.noff <= 65535 &&
         lds <= h->lds_limit && widest_level(h) <= 64) {
       c.algo = SPTRSV_ALGO_BLOCK;
-      // (2-D 64x64, whole call: 54 us with the block kernel, 27 in strips)
+      // (2-D 64x64, whole call: 54 us with the block kernel, 21 in strips)
       c.strip = strip_rule(h) && !h->set_mask && c.poll == 1 && c.rpl == 1 &&
                 c.sync == SPTRSV_SYNC_VALUE;
       return c;
