@@ -446,7 +446,7 @@ int read_status(sptrsv_handle_t h, hipStream_t s, bool clear) {
 void install_device_plan(sptrsv_handle_t h, PlanState& ps, DeviceAnalysis& da, bool upper);
 int64_t values_bytes(sptrsv_handle_t h);
 std::vector<std::vector<StripGrid>> grid_guesses(sptrsv_handle_t h, bool upper);
-void build_strip_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t s);
+int build_strip_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t s);
 
 // Builds the analysis of T^T: rows of T^T are the columns of T; each value is
 // taken from the forward plan's value buffer (so the caller's vals need not
@@ -471,11 +471,11 @@ int build_transpose(sptrsv_handle_t h, hipStream_t s) {
       st = gather(h, h->trn, h->fwd.vals_buf, s);
     }
     if (!st && hipStreamSynchronize(s) != hipSuccess) st = kErrHip;
+    if (!st) st = build_strip_state(h, h->trn, !h->upper, s);
     if (st) {
       free_device_analysis(da);
       free_plan(h->trn);
     }
-    if (!st) build_strip_state(h, h->trn, !h->upper, s);
     if (st != kErrNotSupported) return st;   // else the host route below decides
   }
   if (const int st = ensure_host_plan(h)) return st;
@@ -493,8 +493,8 @@ int build_transpose(sptrsv_handle_t h, hipStream_t s) {
   int st = upload_plan(h->trn, h->vb, s);
   if (!st) st = gather(h, h->trn, h->fwd.vals_buf, s);
   if (!st && hipStreamSynchronize(s) != hipSuccess) st = kErrHip;
+  if (!st) st = build_strip_state(h, h->trn, !h->upper, s);
   if (st) free_plan(h->trn);   // a later call starts over instead of using half a plan
-  else build_strip_state(h, h->trn, !h->upper, s);
   return st;
 }
 
@@ -784,11 +784,11 @@ bool multi_by_columns(const PlanState& ps, const Config& c) {
 
 // Distinct offsets of the pattern, system by system (h->offsets; left empty
 // when some system has more than a grid's stencil would).  row_ptr, col: the
-// pattern in device memory.  Blocking; a failure only leaves the strip form
-// unused.
-void find_offsets(sptrsv_handle_t h, const int* row_ptr, const int* col, hipStream_t s) {
+// pattern in device memory.  Blocking; without the memory for it the strip
+// form is left unused.
+int find_offsets(sptrsv_handle_t h, const int* row_ptr, const int* col, hipStream_t s) {
   h->offsets.clear();
-  if (h->n == 0) return;
+  if (h->n == 0) return kOk;
   std::vector<int> row0(1, 0);
   if (h->batched)
     for (int ni : h->sys_n) row0.push_back(row0.back() + ni);
@@ -798,15 +798,17 @@ void find_offsets(sptrsv_handle_t h, const int* row_ptr, const int* col, hipStre
   const int words = nsys * (kStripTable + 1) + nsys + 1;   // tables, full flags, row0
   int err = kOk;
   int* buf = dalloc<int>(words, &err);
-  if (!buf) return;
+  if (!buf) return kOk;
   std::vector<int> host(words, 0);
   std::copy(row0.begin(), row0.end(), host.begin() + nsys * (kStripTable + 1));
   int* full = buf + static_cast<int64_t>(nsys) * kStripTable;
+  err = kErrHip;
   if (hipMemcpyAsync(buf, host.data(), words * sizeof(int), hipMemcpyHostToDevice, s) == hipSuccess &&
       launch_strip_offsets(h->n, h->nnz, row_ptr, col, nsys, full + nsys, buf, full, s) == hipSuccess &&
       hipMemcpyAsync(host.data(), buf, static_cast<size_t>(nsys) * (kStripTable + 1) * sizeof(int),
                      hipMemcpyDeviceToHost, s) == hipSuccess &&
       hipStreamSynchronize(s) == hipSuccess) {
+    err = kOk;
     h->offsets.resize(nsys);
     for (int k = 0; k < nsys; ++k) {
       std::vector<int>& o = h->offsets[k];
@@ -820,6 +822,7 @@ void find_offsets(sptrsv_handle_t h, const int* row_ptr, const int* col, hipStre
     }
   }
   dfree(buf);
+  return err;
 }
 
 // Reading `attempt` (0, 1) of the offsets as grids, one per system; false: none.
@@ -852,46 +855,40 @@ std::vector<std::vector<StripGrid>> grid_guesses(sptrsv_handle_t h, bool upper) 
 
 // The strip-ordered copy of a plan (strips.hpp), if its rows sit on a grid and memory
 // allows; otherwise the plan keeps the row-wise schedules alone.  Blocking.
-void build_strip_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t s) {
-  if (h->offsets.empty() || ps.strips.nstrips) return;
-  int err = kOk;
+int build_strip_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t s) {
+  if (h->offsets.empty() || ps.strips.nstrips) return kOk;
+  int st = kOk;
   unsigned char* lanes = nullptr;
   if (ps.h.max_row_len > kStripLaneEntries) {
     // rows of several lanes: their sums are split the same way here
-    ChunkEntry* ch = get_chunks(h, ps, 0, kStripLaneEntries, 0, 1, &err);
-    if (!ch) return;
-    lanes = dalloc<unsigned char>(static_cast<size_t>(h->n), &err);
-    if (!lanes || launch_strip_lanes(ch->d, lanes, s) != hipSuccess) {
-      dfree(lanes);
-      return;
-    }
+    ChunkEntry* ch = get_chunks(h, ps, 0, kStripLaneEntries, 0, 1, &st);
+    if (ch) lanes = dalloc<unsigned char>(static_cast<size_t>(h->n), &st);
+    if (lanes && launch_strip_lanes(ch->d, lanes, s) != hipSuccess) st = kErrHip;
   }
-  if (!ps.d.row_pos) {
-    ps.d.row_pos = dalloc<int>(static_cast<size_t>(h->n), &err);
-    if (ps.d.row_pos && launch_row_pos(h->n, ps.d.pos_row, ps.d.row_pos, s) != hipSuccess) {
-      dfree(ps.d.row_pos);
-      ps.d.row_pos = nullptr;
-    }
+  if (!st && !ps.d.row_pos) {
+    ps.d.row_pos = dalloc<int>(static_cast<size_t>(h->n), &st);
+    if (ps.d.row_pos && launch_row_pos(h->n, ps.d.pos_row, ps.d.row_pos, s) != hipSuccess)
+      st = kErrHip;
   }
-  for (int attempt = 0; attempt < 2 && ps.d.row_pos; ++attempt) {
+  for (int attempt = 0; attempt < 2 && !st; ++attempt) {
     std::vector<StripGrid> grids;
     if (!infer_grids(h, upper, attempt, grids)) break;
-    const int st = build_strips(ps.d, grids, ps.h.max_row_len, lanes, static_cast<int>(h->vb),
-                               s, ps.strips);
-    if (st == kErrNotSupported) continue;
-    if (!st) {
-      const hipError_t e = h->dtype == SPTRSV_F64 ? launch_strip_gather<double>(ps.d, ps.strips, s)
-                                                  : launch_strip_gather<float>(ps.d, ps.strips, s);
-      if (e != hipSuccess || 
-          ensure_xp(h, std::max<int64_t>(h->n, strip_values(ps.strips, 1))) ||
-          hipStreamSynchronize(s) != hipSuccess)
-        free_strips(ps.strips);
-      else
-        (void)strip_occupancy(h, ps, 1);
+    st = build_strips(ps.d, grids, ps.h.max_row_len, lanes, static_cast<int>(h->vb), s, ps.strips);
+    if (st == kErrNotSupported) {
+      st = kOk;
+      continue;
     }
+    if (!st && (h->dtype == SPTRSV_F64 ? launch_strip_gather<double>(ps.d, ps.strips, s)
+                                       : launch_strip_gather<float>(ps.d, ps.strips, s)) != hipSuccess)
+      st = kErrHip;
+    if (!st) st = ensure_xp(h, std::max<int64_t>(h->n, strip_values(ps.strips, 1)));
+    if (!st && hipStreamSynchronize(s) != hipSuccess) st = kErrHip;
+    if (!st) (void)strip_occupancy(h, ps, 1);
     break;
   }
+  if (st) free_strips(ps.strips);
   dfree(lanes);
+  return st == kErrOom ? kOk : st;
 }
 
 uint64_t tune_key(sptrsv_handle_t h) {
@@ -1575,8 +1572,8 @@ int analyze_from_host(sptrsv_handle_t h, const int* row_ptr, const int* col_idx,
   if ((st = init_handle_common(h, s))) return st;
   if ((st = upload_plan(h->fwd, h->vb, s))) return st;
   if ((st = gather(h, h->fwd, vals, s))) return st;
-  find_offsets(h, row_ptr, col_idx, s);
-  build_strip_state(h, h->fwd, h->upper, s);
+  if ((st = find_offsets(h, row_ptr, col_idx, s))) return st;
+  if ((st = build_strip_state(h, h->fwd, h->upper, s))) return st;
   if ((st = ensure_xp(h, h->n))) return st;
   return read_status(h, s, true);
 }
@@ -1638,7 +1635,7 @@ int analyze_on_device(sptrsv_handle_t h, const int* row_ptr, const int* col_idx,
   if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, h->device) == hipSuccess &&
       ncu > 0)
     h->num_cu = ncu;
-  find_offsets(h, row_ptr, col_idx, s);
+  if (const int fs = find_offsets(h, row_ptr, col_idx, s)) return fs;
   DeviceAnalysis da;
   // behind the values: the flags of the flag schedules and the pattern
   const int64_t vb = values_bytes(h), nb = block_bytes((static_cast<int64_t>(h->n) + 1) * 4);
@@ -1666,7 +1663,7 @@ int analyze_on_device(sptrsv_handle_t h, const int* row_ptr, const int* col_idx,
   }
   if ((st = init_handle_common(h, s))) return st;
   if ((st = gather(h, h->fwd, vals, s))) return st;
-  build_strip_state(h, h->fwd, h->upper, s);
+  if ((st = build_strip_state(h, h->fwd, h->upper, s))) return st;
   if ((st = ensure_xp(h, h->n))) return st;
   return read_status(h, s, true);
 }

@@ -28,6 +28,14 @@ struct Block {
   int64_t freed;                             // count of frees when it was stored
 };
 
+// Every failure below is answered for here or by the status returned; the
+// runtime keeps it as the thread's last error all the same, until it is asked
+// for, and the check behind the next launch would take it for its own.
+hipError_t settled(hipError_t e) {
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e;
+}
+
 struct Store {
   std::mutex mu;
   std::map<void*, Block> live;               // large blocks in use
@@ -37,7 +45,7 @@ struct Store {
   // Hands back the oldest blocks until `bytes` remain, and those passed over.
   void trim(int64_t bytes) {
     while (!kept.empty() && (kept_bytes > bytes || frees - kept.front().freed > kKeepFrees)) {
-      (void)hipFree(kept.front().p);
+      (void)settled(hipFree(kept.front().p));
       kept_bytes -= kept.front().bytes;
       kept.pop_front();
     }
@@ -49,7 +57,7 @@ struct Store {
 // where the capture allows calls like hipFree.
 bool wait_idle() {
   void* p = nullptr;
-  return hipMalloc(&p, 1) == hipSuccess && hipFree(p) == hipSuccess;
+  return settled(hipMalloc(&p, 1)) == hipSuccess && settled(hipFree(p)) == hipSuccess;
 }
 
 // never destroyed: the runtime may be gone when static destructors run
@@ -64,16 +72,16 @@ hipError_t dev_alloc(void** p, int64_t bytes) {
   *p = nullptr;
   if (bytes < 1) bytes = 1;
   if (bytes < kLarge) {
-    hipError_t e = hipMalloc(p, static_cast<size_t>(bytes));
+    const hipError_t e = settled(hipMalloc(p, static_cast<size_t>(bytes)));
     if (e == hipSuccess) return e;
     Store& s = store();
     std::lock_guard<std::mutex> lock(s.mu);
     if (s.kept.empty()) return e;
     s.trim(0);
-    return hipMalloc(p, static_cast<size_t>(bytes));
+    return settled(hipMalloc(p, static_cast<size_t>(bytes)));
   }
   int device = 0;
-  if (const hipError_t e = hipGetDevice(&device)) return e;
+  if (const hipError_t e = settled(hipGetDevice(&device))) return e;
   constexpr int64_t kUnit = 2 << 20;
   bytes = (bytes + kUnit - 1) / kUnit * kUnit;
   Store& s = store();
@@ -91,10 +99,10 @@ hipError_t dev_alloc(void** p, int64_t bytes) {
     s.kept.erase(best);
     return hipSuccess;
   }
-  hipError_t e = hipMalloc(p, static_cast<size_t>(bytes));
+  hipError_t e = settled(hipMalloc(p, static_cast<size_t>(bytes)));
   if (e != hipSuccess && !s.kept.empty()) {
     s.trim(0);
-    e = hipMalloc(p, static_cast<size_t>(bytes));
+    e = settled(hipMalloc(p, static_cast<size_t>(bytes)));
   }
   if (e == hipSuccess) s.live[*p] = Block{*p, bytes, device, 0};
   return e;
@@ -121,7 +129,7 @@ void dev_free(void* p) {
     if (device != b.device) (void)hipSetDevice(device);
   }
   if (!idle) {
-    (void)hipFree(p);
+    (void)settled(hipFree(p));
     return;
   }
   std::lock_guard<std::mutex> lock(s.mu);

@@ -8,7 +8,8 @@
 namespace sptrsv {
 
 // Allocates `bytes` (at least one) on the current device; contents undefined.
-// Large blocks come from a store of freed ones where one fits.
+// Large blocks come from a store of freed ones where one fits.  A failure is
+// the returned status alone: it is not left behind as the thread's last error.
 hipError_t dev_alloc(void** p, int64_t bytes);
 
 // Returns memory of dev_alloc once the device that holds it is idle (as

@@ -1,0 +1,129 @@
+"""The library's host side on the CPU, over a stand-in HIP runtime (see
+cpp/host_model.cpp): which form a call takes, what it leaves allocated, and what
+error it leaves behind, also where allocations fail or a stream is capturing."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import workloads as W
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1710_04985_amd", "csrc")
+MB = 1 << 20
+OPT = {"algo": 0, "group": 1, "wg": 7, "assign": 9, "poll": 10, "multi_rows": 12}
+P, I32, I64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
+
+
+@pytest.fixture(scope="module")
+def built(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("model") / "host_model.so")
+    src = [os.path.join(CSRC, f) for f in ("api.cpp", "devmem.cpp", "analysis.cpp", "strips.cpp")]
+    subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-Wl,-Bsymbolic",
+                    "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-I", CSRC,
+                    "-I", os.path.join(ROOT, "include"), *src,
+                    os.path.join(ROOT, "tests", "cpp", "host_model.cpp"), "-o", out], check=True)
+    return out
+
+
+@pytest.fixture
+def m(built, tmp_path):
+    """A fresh copy, so that no state of the process-wide kind is shared."""
+    path = str(tmp_path / "m.so")
+    with open(built, "rb") as a, open(path, "wb") as b:
+        b.write(a.read())
+    lib = ctypes.CDLL(path)
+    for f in (lib.model_fail_from, lib.model_npub, lib.model_strip_bytes):
+        f.argtypes = [I64]
+    lib.model_alloc.argtypes, lib.model_alloc.restype = [I64], P
+    lib.model_free.argtypes = lib.model_is_live.argtypes = [P]
+    lib.model_live_bytes.restype = I64
+    lib.model_log.restype = ctypes.c_char_p
+    lib.log = lambda: lib.model_log().decode().split()
+    lib.model_fail_from(-1)
+    return lib
+
+
+class Model:
+    """A handle over the stand-in runtime."""
+
+    def __init__(self, m, T, nrhs=64):
+        self.m, self.n, self.T = m, T.n, T
+        self.rp = np.ascontiguousarray(T.row_ptr, np.int32)
+        self.ci = np.ascontiguousarray(T.col_idx, np.int32)
+        self.v = np.ascontiguousarray(T.vals, np.float64)
+        self.b = np.ones(T.n * nrhs)
+        self.x = np.zeros(T.n * nrhs)
+        self.h = P()
+        self.st = m.sptrsv_analyze_ex(I32(T.n), I32(T.nnz), self.p(self.rp), self.p(self.ci),
+                                      self.p(self.v), 0, int(T.upper), 0, 0, None,
+                                      ctypes.byref(self.h))
+
+    @staticmethod
+    def p(a):
+        return a.ctypes.data_as(P)
+
+    def set(self, **kw):
+        for k, v in kw.items():
+            assert self.m.sptrsv_set_option(self.h, OPT[k], I64(v)) == 0
+        return self
+
+    def solve(self, t=False):
+        f = self.m.sptrsv_solve_transpose if t else self.m.sptrsv_solve
+        return f(self.h, self.p(self.b), self.p(self.x), None)
+
+    def multi(self, nrhs, t=False):
+        return self.m.sptrsv_solve_multi(self.h, I32(nrhs), I32(self.n), self.p(self.b),
+                                         self.p(self.x), int(t), None)
+
+    def destroy(self):
+        assert self.m.sptrsv_destroy(self.h) == 0
+
+
+def test_allocation_that_succeeds_after_the_store_is_emptied(m):
+    a = m.model_alloc(4 * MB)
+    m.model_free(a)
+    assert m.model_live_bytes() == 4 * MB              # kept
+    m.model_fail_next(1)
+    b = m.model_alloc(8 * MB)
+    assert b and m.model_live_bytes() == 8 * MB        # the kept block went back
+    assert m.model_last_error() == 0
+    small = m.model_alloc(4 * MB)
+    m.model_free(small)
+    m.model_fail_next(1)
+    assert m.model_alloc(100) and m.model_last_error() == 0
+
+
+def test_failed_allocations_leave_no_error_behind(m):
+    m.model_fail_from(MB)
+    assert not m.model_alloc(16 * MB) and m.model_last_error() == 0
+    m.model_fail_from(1)
+    assert not m.model_alloc(10) and m.model_last_error() == 0
+    m.model_fail_from(-1)
+    a = m.model_alloc(2 * MB)
+    m.model_fail_from(1)                               # no memory for the wait of a free either
+    m.model_free(a)
+    assert m.model_live_bytes() == 0 and m.model_last_error() == 0
+
+
+def test_no_memory_for_the_strips(m):
+    """Analysis without room for the strip-ordered copy keeps the row-wise
+    schedules, and the next launch sees no error; an error of the runtime is
+    not taken for that."""
+    T = W.laplacian_triangle((128, 128))
+    m.model_strip_bytes(64 * MB)
+    m.model_fail_from(32 * MB)
+    h = Model(m, T)
+    assert h.st == 0 and m.model_last_error() == 0
+    m.log()
+    assert h.solve() == 0 and m.log()[-1] != "strips"
+    assert h.solve(t=True) == 0 and m.log()[-1] != "strips"
+    h.destroy()
+    m.model_fail_from(-1)
+    h = Model(m, T)
+    assert h.st == 0 and h.solve() == 0 and m.log()[-1] == "strips"
+    h.destroy()
+    m.model_strip_error(-8)
+    assert Model(m, T).st == -8
