@@ -1205,15 +1205,14 @@ int solve_impl(sptrsv_handle_t h, PlanState& ps, const Config& c_in, const void*
   if (is_column(c_in.algo) && !multi) return solve_column<T>(h, ps, c_in, b, x, s, ext);
   const int64_t tasks = static_cast<int64_t>(ps.strips.nstrips) * nrhs;
   if (c_in.strip && tasks > 0 && tasks < INT32_MAX / kDumpSlot && !(multi && ext.no_alloc)) {
-    // a fixed buffer too small for the published values leaves the row-wise form
+    // a fixed buffer too small for the published values, or no memory for them,
+    // leaves the row-wise (or block) form
     const int64_t need = strip_values(ps.strips, nrhs);
-    void* xp = ext.xp;
-    if (!xp) {
-      if (const int st = ensure_xp(h, need)) return st;
-      xp = h->xp;
-    }
-    if (!ext.xp || need * static_cast<int64_t>(h->vb) <= ext.xp_bytes)
-      return solve_strips<T>(h, ps, b, x, nrhs, ld, xp, s, ext);
+    const int st = ext.xp ? need * static_cast<int64_t>(h->vb) <= ext.xp_bytes ? kOk : kErrTooLarge
+                          : ensure_xp(h, need);
+    if (!st)
+      return solve_strips<T>(h, ps, b, x, nrhs, ld, ext.xp ? ext.xp : h->xp, s, ext);
+    if (st != kErrOom && st != kErrTooLarge) return st;
   }
   // several right-hand sides under a column-wise schedule: row-wise, self-scheduled
   Config c = c_in;
@@ -1283,7 +1282,10 @@ int solve_impl(sptrsv_handle_t h, PlanState& ps, const Config& c_in, const void*
   if (c.algo == SPTRSV_ALGO_BLOCK && !multi) {
     const int dir = (&ps == &h->trn) ? 1 : 0;
     BlockState& bs = h->blk[dir];
-    if (!bs.built) return ext.no_alloc ? kErrNotSupported : kErrInvalidArg;
+    if (!bs.built) {
+      if (ext.no_alloc) return kErrNotSupported;
+      if ((err = build_block(h, dir, s))) return err;
+    }
     a.plan = &bs.ps.d;
     int threads = 64;
     while (threads < bs.info.max_level && threads < 1024) threads <<= 1;
@@ -1484,12 +1486,6 @@ int solve_dispatch_ordered(sptrsv_handle_t h, bool transpose, const void* b, voi
       if (st) return st;
     }
     return kOk;
-  }
-  if (c.algo == SPTRSV_ALGO_BLOCK && nrhs == 1 && !(c.strip && ps.strips.nstrips) &&
-      !h->blk[transpose ? 1 : 0].built) {
-    if (ext.no_alloc) return kErrNotSupported;
-    const int st = build_block(h, transpose ? 1 : 0, s);
-    if (st) return st;
   }
   if (h->dtype == SPTRSV_F64) return solve_impl<double>(h, ps, c, b, x, nrhs, ld, s, ext);
   return solve_impl<float>(h, ps, c, b, x, nrhs, ld, s, ext);

@@ -127,3 +127,26 @@ def test_no_memory_for_the_strips(m):
     h.destroy()
     m.model_strip_error(-8)
     assert Model(m, T).st == -8
+
+
+def test_no_memory_for_the_strips_buffer(m):
+    """Several columns whose published values do not fit in memory, where those
+    of the row-wise solve do, are solved row-wise; with memory, in strips.  A
+    default block choice builds its plan then."""
+    T = W.laplacian_triangle((128, 128))
+    m.model_npub(16 * T.n)
+    h = Model(m, T)
+    m.log()
+    m.model_fail_from(16 * MB)
+    assert h.multi(16) == 0 and m.log()[-1] == "multi_out"
+    assert h.multi(16, t=True) == 0 and m.log()[-1] == "multi_out"
+    assert m.model_last_error() == 0
+    m.model_fail_from(-1)
+    assert h.multi(16) == 0 and m.log()[-1] == "strips"
+    h.destroy()
+
+    T = W.laplacian_triangle((40, 40))
+    h = Model(m, T)                                    # room for T's values only
+    m.model_npub(64 << 20)
+    m.model_fail_from(16 * MB)
+    assert h.solve(t=True) == 0 and m.log()[-1] == "block"
