@@ -44,7 +44,9 @@
  *     than the previous one first makes its stream wait for that event.
  *     Under graph capture nothing is recorded or waited for: the capturing
  *     stream orders the graph, and the caller orders graph launches against
- *     other work on the handle.
+ *     other work on the handle.  A buffer that a later call replaces (T^T,
+ *     more right-hand sides) stays allocated until sptrsv_destroy if a
+ *     capture of the caller's own may hold its address.
  *   - Device memory: blocks of 1 MiB and more that a call frees are kept
  *     for the next handle, at most 1 GiB over all devices; all of it goes
  *     back when an allocation fails, and a block that 64 later frees have

@@ -164,8 +164,14 @@ struct sptrsv_handle_s {
   std::shared_ptr<DevBuffer> xp_buf;   // position-ordered solution(s) of the solve kernels
   void* xp = nullptr;             // xp_buf->p
   int64_t xp_elems = 0;
+  // replaced buffers whose addresses a caller's own capture holds (freed with
+  // the handle: the library does not see such a graph end)
+  bool captured = false;          // the present buffers are in such a capture
+  std::vector<std::shared_ptr<DevBuffer>> captured_bufs;
+  bool own_capture = false;       // sptrsv_graph_capture is at work: its graph keeps xp_buf
   int live_graphs = 0;            // graphs captured from this handle, not yet destroyed
-  void* bp = nullptr;             // several right-hand sides in position order
+  std::shared_ptr<DevBuffer> bp_buf;   // several right-hand sides in position order
+  void* bp = nullptr;             // bp_buf->p
   int64_t bp_elems = 0;
   // batched handles keep the concatenated pattern and values on the device
   bool batched = false;
@@ -897,16 +903,26 @@ uint64_t tune_key(sptrsv_handle_t h) {
          (static_cast<uint64_t>(h->epl) << 32);
 }
 
+// Before a buffer is replaced: both stay if a caller's capture may use them.
+void keep_captured(sptrsv_handle_t h) {
+  if (!h->captured) return;
+  for (const auto& b : {h->xp_buf, h->bp_buf})
+    if (b) h->captured_bufs.push_back(b);
+  h->captured = false;
+}
+
 // Grows the position-ordered solution buffer to `elems` values.  Work the
 // handle issued earlier may still use the old buffer: it is waited for
 // through the handle's ordering event (not the whole device), and a graph
-// captured with the old buffer keeps it alive (see DevBuffer).
+// captured with the old buffer keeps it alive (see DevBuffer); one that the
+// caller captured leaves it to the handle to keep.
 int ensure_xp(sptrsv_handle_t h, int64_t elems) {
   if (h->xp_elems >= elems) return kOk;
   if (h->xp_buf && h->order_ev && h->order_pending) HIPCHK(hipEventSynchronize(h->order_ev));
   auto nb = std::make_shared<DevBuffer>();
   if (dev_alloc(&nb->p, elems * static_cast<int64_t>(h->vb)) != hipSuccess)
     return kErrOom;
+  keep_captured(h);
   h->xp_buf = std::move(nb);   // frees the old buffer unless a graph holds it
   h->xp = h->xp_buf->p;
   h->xp_elems = elems;
@@ -918,11 +934,15 @@ int ensure_xp(sptrsv_handle_t h, int64_t elems) {
 int ensure_multi(sptrsv_handle_t h, PlanState& ps, int64_t elems, hipStream_t s) {
   if (h->bp_elems < elems) {
     if (h->bp && h->order_ev && h->order_pending) HIPCHK(hipEventSynchronize(h->order_ev));
-    dfree(h->bp);
+    keep_captured(h);
+    h->bp_buf.reset();
     h->bp = nullptr;
     h->bp_elems = 0;
-    if (dev_alloc(&h->bp, elems * static_cast<int64_t>(h->vb)) != hipSuccess)
+    auto nb = std::make_shared<DevBuffer>();
+    if (dev_alloc(&nb->p, elems * static_cast<int64_t>(h->vb)) != hipSuccess)
       return kErrOom;
+    h->bp_buf = std::move(nb);
+    h->bp = h->bp_buf->p;
     h->bp_elems = elems;
   }
   if (!ps.d.row_pos) {
@@ -1396,6 +1416,7 @@ int solve_dispatch(sptrsv_handle_t h, bool transpose, const void* b, void* x, in
   int st = order_begin(h, s, &capturing);
   if (st) return st;
   st = solve_dispatch_ordered(h, transpose, b, x, nrhs, ld, s, ext);
+  if (capturing && !ext.xp && !h->own_capture) h->captured = true;
   const int st2 = order_end(h, s, capturing);
   return st ? st : st2;
 }
@@ -1688,7 +1709,9 @@ void destroy_handle(sptrsv_handle_t h) {
   dfree(h->scratch.arrive);
   h->xp_buf.reset();
   h->xp = nullptr;
-  dfree(h->bp);
+  h->bp_buf.reset();
+  h->bp = nullptr;
+  h->captured_bufs.clear();
   dfree(h->rp_cat);
   dfree(h->col_cat);
   dfree(h->vals_cat);
@@ -2463,7 +2486,9 @@ int sptrsv_graph_capture(sptrsv_handle_t h, const void* b, void* x, int transpos
     delete g;
     return kErrHip;
   }
+  h->own_capture = true;
   const int st = solve_dispatch(h, transpose != 0, b, x, 1, h->n, stream);
+  h->own_capture = false;
   const hipError_t e = hipStreamEndCapture(stream, &g->graph);
   if (st || e != hipSuccess) {
     if (g->graph) (void)hipGraphDestroy(g->graph);

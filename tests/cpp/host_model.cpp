@@ -32,6 +32,7 @@ std::string g_log;
 int64_t g_npub = 0;                // published values of every strip copy, 0: as many as rows
 int64_t g_strip_bytes = 1 << 16;   // size of every strip copy
 int g_strip_error = 0;             // what the construction of one reports
+void* g_xp = nullptr;              // the solution buffer filled last
 int g_handles = 0;                 // events, streams and graphs are numbers
 
 hipError_t fail(hipError_t e) { return g_last = e; }
@@ -57,6 +58,7 @@ const char* model_log() {
   g_log.clear();
   return out.c_str();
 }
+void* model_xp() { return g_xp; }
 int model_last_error() { return static_cast<int>(hipGetLastError()); }
 int64_t model_live_bytes() {
   int64_t b = 0;
@@ -234,6 +236,7 @@ template <typename T> hipError_t launch_push_gather(const DevPlan&, const DevPus
 }
 template <typename T> hipError_t launch_fill_sentinel(T* xp, int64_t count, int*, hipStream_t) {
   if (count > 0) xp[count - 1] = xp[0] = T(0);   // both ends are the buffer's own
+  g_xp = xp;
   return note("fill");
 }
 template <typename T> hipError_t launch_strip_solve(const StripSolveArgs&, hipStream_t) {

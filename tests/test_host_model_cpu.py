@@ -38,6 +38,7 @@ def m(built, tmp_path):
     for f in (lib.model_fail_from, lib.model_npub, lib.model_strip_bytes):
         f.argtypes = [I64]
     lib.model_alloc.argtypes, lib.model_alloc.restype = [I64], P
+    lib.model_xp.restype = P
     lib.model_free.argtypes = lib.model_is_live.argtypes = [P]
     lib.model_live_bytes.restype = I64
     lib.model_log.restype = ctypes.c_char_p
@@ -150,3 +151,21 @@ def test_no_memory_for_the_strips_buffer(m):
     m.model_npub(64 << 20)
     m.model_fail_from(16 * MB)
     assert h.solve(t=True) == 0 and m.log()[-1] == "block"
+
+
+@pytest.mark.parametrize("later", ["transpose", "columns"])
+def test_buffer_in_a_capture_of_the_callers_own(m, later):
+    """A buffer whose address a caller's graph holds outlives the call that
+    needs a larger one, and goes with the handle."""
+    T = W.laplacian_triangle((50, 50))
+    h = Model(m, T).set(algo=2)
+    assert h.solve() == 0
+    m.model_capture(1)
+    assert h.solve() == 0
+    m.model_capture(0)
+    held = m.model_xp()
+    m.model_npub(4 * T.n)                              # T^T publishes more
+    assert (h.solve(t=True) if later == "transpose" else h.multi(4)) == 0
+    assert m.model_xp() != held and m.model_is_live(held)
+    h.destroy()
+    assert not m.model_is_live(held) and m.model_live_bytes() == 0
