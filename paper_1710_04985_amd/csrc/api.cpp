@@ -705,7 +705,11 @@ bool strip_rule(sptrsv_handle_t h) {
 //  * rows longer than 64 entries take 32-byte slots for the solution
 //    (power-law 1M rows: 604 us against 709 packed).
 Config resolve(sptrsv_handle_t h) {
-  if (h->tuned) return h->tuned_cfg;
+  if (h->tuned) {
+    Config c = h->tuned_cfg;
+    c.strip = c.strip && strip_rule(h);   // options set since, another handle's choice
+    return c;
+  }
   Config c{h->algo, h->group, h->epl, h->sync, h->rpl, h->grid, h->assign};
   c.poll = h->poll;
   c.stride = h->xp_stride;
@@ -757,7 +761,11 @@ int publish_early(const PlanState& ps, const Config& c) {
 // then holds 64/nrhs rows, so a level has many more chunks to spread).
 Config resolve_multi(sptrsv_handle_t h, int nrhs) {
   auto it = h->tuned_multi.find(nrhs);
-  if (it != h->tuned_multi.end()) return it->second;
+  if (it != h->tuned_multi.end()) {
+    Config c = it->second;
+    c.strip = c.strip && strip_rule(h);   // options set since
+    return c;
+  }
   Config c = resolve(h);
   // the block schedule solves one right-hand side; a default choice of it
   // becomes the self-scheduled solve here
@@ -900,7 +908,8 @@ int build_strip_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t 
 uint64_t tune_key(sptrsv_handle_t h) {
   return h->hash ^ (h->dtype == SPTRSV_F32 ? 0x9e3779b97f4a7c15ull : 0) ^
          (static_cast<uint64_t>(h->algo) << 56) ^ (static_cast<uint64_t>(h->group) << 48) ^
-         (static_cast<uint64_t>(h->epl) << 32);
+         (static_cast<uint64_t>(h->epl) << 32) ^
+         (static_cast<uint64_t>(strip_rule(h)) << 46);   // whether strips were a candidate
 }
 
 // Before a buffer is replaced: both stay if a caller's capture may use them.
@@ -2275,7 +2284,7 @@ int sptrsv_tune_multi(sptrsv_handle_t h, int32_t nrhs, int32_t ld, const void* B
   std::vector<Config> cand;
   const bool self_ok = h->algo == SPTRSV_ALGO_AUTO || h->algo == SPTRSV_ALGO_SELF ||
                        is_column(h->algo);
-  if (self_ok && strip_rule(h)) {
+  if (self_ok && strip_rule(h) && h->mrows == 0) {
     Config c{SPTRSV_ALGO_SELF, 0, 4, SPTRSV_SYNC_VALUE, 1, 0, SPTRSV_ASSIGN_TICKET};
     c.strip = 1;
     cand.push_back(c);

@@ -131,7 +131,8 @@ hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) {
-  *ms = 1.0f;
+  // strips are the fastest schedule here
+  *ms = g_log.size() >= 6 && g_log.compare(g_log.size() - 6, 6, "strips") == 0 ? 0.5f : 1.0f;
   return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }

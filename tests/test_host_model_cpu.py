@@ -79,6 +79,18 @@ class Model:
         return self.m.sptrsv_solve_multi(self.h, I32(nrhs), I32(self.n), self.p(self.b),
                                          self.p(self.x), int(t), None)
 
+    def tune(self, nrhs=1):
+        y = np.zeros(self.n * nrhs)
+        if nrhs > 1:
+            return self.m.sptrsv_tune_multi(self.h, I32(nrhs), I32(self.n), self.p(self.b), self.p(y), None)
+        return self.m.sptrsv_tune(self.h, self.p(self.b), self.p(y), None)
+
+    def form(self, nrhs=1, t=False):
+        """The launch that a solve comes down to."""
+        self.m.log()
+        assert (self.multi(nrhs, t) if nrhs > 1 else self.solve(t)) == 0
+        return [w for w in self.m.log() if w not in ("fill", "multi_in", "multi_out")][-1]
+
     def destroy(self):
         assert self.m.sptrsv_destroy(self.h) == 0
 
@@ -169,3 +181,24 @@ def test_buffer_in_a_capture_of_the_callers_own(m, later):
     assert m.model_xp() != held and m.model_is_live(held)
     h.destroy()
     assert not m.model_is_live(held) and m.model_live_bytes() == 0
+
+
+@pytest.mark.parametrize("order", [(64, 256), (256, 64)])
+def test_tuned_choice_of_another_workgroup_size(m, order):
+    """A choice kept for a pattern is one of a handle with the same candidates."""
+    T = W.laplacian_triangle((60, 50))
+    for wg in order:
+        h = Model(m, T).set(algo=2, wg=wg)
+        assert h.tune() == 0
+        assert (h.form() == "strips") == (wg == 64)
+        if wg == 64:
+            assert h.set(wg=128).form() != "strips"     # set after the tuning
+
+
+def test_tuned_columns_respect_the_rows_option(m):
+    T = W.laplacian_triangle((60, 50))
+    h = Model(m, T).set(algo=2, multi_rows=2)
+    assert h.tune(4) == 0 and h.form(4) != "strips"
+    h.set(multi_rows=0)
+    assert h.tune(4) == 0 and h.form(4) == "strips"
+    assert h.set(wg=128).form(4) != "strips"
