@@ -308,12 +308,11 @@ def main():
 
     infoL = hL.info()
     schedule = {k: infoL[k] for k in SCHED_KEYS}
-    if infoL["sync"] == sp.SYNC_FLAG:
+    strips = hL.strips()
+    if strips["strips"]:
+        kernel_name = "k_strip<double, %(slots)d, %(sums)d, %(depth)d>" % strips
+    elif infoL["sync"] == sp.SYNC_FLAG:
         kernel_name = "k_self_flag<double>"
-    elif infoL["grid"] == 0 and infoL["poll"] == 1 and infoL["xp_stride"] == 1:
-        # the row-wise choices of the tuner set a grid; the strips, and a
-        # handle without any option, do not
-        kernel_name = "k_strip<double, 3, 1, 16>"
     elif infoL["assign"] in (sp.ASSIGN_STATIC, sp.ASSIGN_XCD):
         kernel_name = "k_self_static<double, %d, false>" % infoL["xp_stride"]
     else:

@@ -116,7 +116,8 @@ typedef enum {
                                workgroup size was set: no resident grid is needed, and
                                sptrsv_get_schedule and sptrsv_get_info keep naming the
                                row-wise (or block) schedule that takes over where the
-                               strips' buffer does not fit.  No rule changes the result
+                               strips' buffer does not fit (sptrsv_get_strips tells
+                               which form a solve takes).  No rule changes the result
                                bits. */
     SPTRSV_ALGO_LEVEL = 1,  /* level-scheduled: one launch per level (Sec. 4.1) */
     SPTRSV_ALGO_SELF = 2,   /* self-scheduled: one persistent launch (Sec. 4.2) */
@@ -444,6 +445,16 @@ int sptrsv_get_schedule(sptrsv_handle_t h, int32_t *algo, int32_t *group,
 /* SPTRSV_OPT_XP_STRIDE of the schedule the next solve uses (the
  * autotuner's choice if one is current, else the option). */
 int sptrsv_get_xp_stride(sptrsv_handle_t h, int32_t *stride);
+
+/* The strip form (see SPTRSV_ALGO_AUTO) of a solve of T (transpose = 0) or
+ * T^T with nrhs right-hand sides, under the present options: the strips it
+ * takes (0: the solve is row-wise or block, or T^T is not analysed yet), and
+ * of its kernel the entry slots of a row, the partial sums of a row, and the
+ * steps (that one included) in which a step's records are loaded.  A solve
+ * whose buffer does not fit runs row-wise all the same.  Every pointer may be
+ * NULL. */
+int sptrsv_get_strips(sptrsv_handle_t h, int transpose, int32_t nrhs, int32_t *strips,
+                      int32_t *slots, int32_t *sums, int32_t *depth);
 
 /* Copy the analysis to HOST buffers (any may be NULL): level int32[n],
  * ilev int32[nlev+1], jlev int32[n] (rows by (level, row)), depcnt int32[n]

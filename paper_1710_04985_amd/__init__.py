@@ -158,6 +158,14 @@ class _Base:
                 "rows_per_lane": rpl.value, "grid": grid.value, "assign": assign.value,
                 "poll": poll.value, "xp_stride": stride.value}
 
+    def strips(self, nrhs=1, transpose=False):
+        """Strip form of a solve under the present options: dict of "strips" (0:
+        the solve is row-wise or block, or T^T is not analysed yet), "slots",
+        "sums" and "depth" of its kernel."""
+        v = [ctypes.c_int32() for _ in range(4)]
+        check(lib.sptrsv_get_strips(self._h, int(transpose), nrhs, *[ctypes.byref(i) for i in v]))
+        return dict(zip(("strips", "slots", "sums", "depth"), (i.value for i in v)))
+
     def export_analysis(self, transpose=False):
         """(level, ilev, jlev, depcnt) as numpy int32 arrays (host copies)."""
         level = np.zeros(self.n, np.int32)

@@ -1224,6 +1224,13 @@ int solve_strips(sptrsv_handle_t h, PlanState& ps, const void* b, void* x, int n
   return kOk;
 }
 
+// Whether a solve with schedule c is one in strips, memory permitting (the
+// tasks and their dump slots are counted in 32 bits).
+bool takes_strips(const PlanState& ps, const Config& c, int nrhs) {
+  const int64_t tasks = static_cast<int64_t>(ps.strips.nstrips) * nrhs;
+  return c.strip && tasks > 0 && tasks < INT32_MAX / kDumpSlot;
+}
+
 template <typename T>
 int solve_impl(sptrsv_handle_t h, PlanState& ps, const Config& c_in, const void* b, void* x,
                int nrhs, int ld, hipStream_t s, const SolveExt& ext = SolveExt()) {
@@ -1232,8 +1239,7 @@ int solve_impl(sptrsv_handle_t h, PlanState& ps, const Config& c_in, const void*
   if (n == 0 || nrhs == 0) return kOk;
   const bool multi = nrhs > 1;
   if (is_column(c_in.algo) && !multi) return solve_column<T>(h, ps, c_in, b, x, s, ext);
-  const int64_t tasks = static_cast<int64_t>(ps.strips.nstrips) * nrhs;
-  if (c_in.strip && tasks > 0 && tasks < INT32_MAX / kDumpSlot && !(multi && ext.no_alloc)) {
+  if (takes_strips(ps, c_in, nrhs) && !(multi && ext.no_alloc)) {
     // a fixed buffer too small for the published values, or no memory for them,
     // leaves the row-wise (or block) form
     const int64_t need = strip_values(ps.strips, nrhs);
@@ -2412,6 +2418,19 @@ int sptrsv_get_schedule(sptrsv_handle_t h, int32_t* algo, int32_t* group,
 int sptrsv_get_xp_stride(sptrsv_handle_t h, int32_t* stride) {
   if (!h || !stride) return kErrInvalidArg;
   *stride = resolve(h).stride;
+  return kOk;
+}
+
+int sptrsv_get_strips(sptrsv_handle_t h, int transpose, int32_t nrhs, int32_t* strips,
+                      int32_t* slots, int32_t* sums, int32_t* depth) {
+  if (!h || nrhs < 1) return kErrInvalidArg;
+  const PlanState& ps = transpose ? h->trn : h->fwd;
+  const bool on =
+      ps.built && takes_strips(ps, nrhs > 1 ? resolve_multi(h, nrhs) : resolve(h), nrhs);
+  if (strips) *strips = on ? ps.strips.nstrips : 0;
+  if (slots) *slots = on ? ps.strips.entries : 0;
+  if (sums) *sums = on ? strip_sums(ps.strips, nrhs) : 0;
+  if (depth) *depth = on ? strip_depth(ps.strips, static_cast<int>(h->vb)) : 0;
   return kOk;
 }
 

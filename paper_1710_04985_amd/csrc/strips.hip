@@ -697,18 +697,11 @@ __global__ void __launch_bounds__(kStripThreads, 1) k_strip(SArgs<T> a) {
   }
 }
 
-// The kernel for a copy.  Several right-hand sides are computed as the
-// one-lane solve computes each (one partial sum).
+// The kernel for a copy.
 template <typename T> const void* strip_fn(const DevStrips& t, int nrhs) {
-  const int acc = nrhs > 1 ? 1 : t.acc;
-  // Long records, loaded 7 steps ahead instead of 3: faster where they come
-  // from memory, but in FP64 the extra stages sit in accumulation registers, so
-  // a step has more to do (27-point, both triangles, us at 7 / 3 steps: FP64
-  // 20^3 105 / 94, 60x50x40 (27 MB of records) 221 / 201, 200x40x100 (170 MB)
-  // 516 / 546, 128^3 769 / 824; FP32 90 / 91, 183 / 190, 400 / 479, 576 / 688).
-  const bool far = sizeof(T) == 4 || t.nrec * t.words * 256 > (64 << 20);
-#define SPTRSV_STRIP(E, A, D)                                    \
-  if (t.entries == E && acc == A && (E <= 4 || far == (D == 8))) \
+  const int acc = strip_sums(t, nrhs), depth = strip_depth(t, sizeof(T));
+#define SPTRSV_STRIP(E, A, D)                                \
+  if (t.entries == E && acc == A && depth == D)              \
   return reinterpret_cast<const void*>(k_strip<T, E, A, D>)
   SPTRSV_STRIP(2, 1, 16);
   SPTRSV_STRIP(3, 1, 16);

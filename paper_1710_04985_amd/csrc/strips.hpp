@@ -97,6 +97,22 @@ inline int64_t strip_values(const DevStrips& t, int nrhs) {
   return (t.npub + static_cast<int64_t>(kDumpSlot) * t.nstrips) * nrhs;
 }
 
+// The kernel's partial sums of a row: several right-hand sides are computed as
+// the one-lane solve computes each.
+inline int strip_sums(const DevStrips& t, int nrhs) { return nrhs > 1 ? 1 : t.acc; }
+
+// Stages of records that the kernel holds (it loads them depth - 1 steps
+// ahead), for values of vb bytes.  Long records, loaded 7 steps ahead instead
+// of 3: faster where they come from memory, but in FP64 the extra stages sit in
+// accumulation registers, so a step has more to do (27-point, both triangles,
+// us at 7 / 3 steps: FP64 20^3 105 / 94, 60x50x40 (27 MB of records) 221 / 201,
+// 200x40x100 (170 MB) 516 / 546, 128^3 769 / 824; FP32 90 / 91, 183 / 190,
+// 400 / 479, 576 / 688).
+inline int strip_depth(const DevStrips& t, int vb) {
+  if (t.entries <= 4) return 16;
+  return vb == 4 || t.nrec * t.words * 256 > (64 << 20) ? 8 : 4;
+}
+
 struct StripSolveArgs {
   const DevStrips* strips;
   DevScratch scratch;

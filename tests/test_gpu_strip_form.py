@@ -1,0 +1,71 @@
+"""Which form a solve takes, as the library reports it: strips on grids, the
+row-wise schedules elsewhere and wherever an option asks for them."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from gpuhelp import bits_equal, dev, dev_tri
+from test_gpu_strips import GRIDS, _banded, _dropped
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sp():
+    import paper_1710_04985_amd as sp
+    assert torch.cuda.is_available()
+    return sp
+
+
+@pytest.mark.parametrize("setup", ["host", "device"])
+@pytest.mark.parametrize("dims,points", GRIDS, ids=["x".join(map(str, g)) + "_%d" % p for g, p in GRIDS])
+def test_grids_take_strips(sp, dims, points, setup):
+    for upper in (False, True):
+        T = W.stencil_triangle(dims, points, upper=upper)
+        for t in (T, _dropped(T, 5)):
+            for dt in (torch.float64, torch.float32):
+                h = sp.Handle(*dev_tri(t, dt), uplo="U" if upper else "L", setup=setup).configure(algo=2)
+                assert h.strips(transpose=True)["strips"] == 0      # not analysed yet
+                h.prepare_transpose()
+                for tr in (False, True):
+                    rows = np.bincount(t.col_idx) if tr else np.diff(t.row_ptr)
+                    longest = max(rows.max() - 1, 2)
+                    for nrhs in (1, 3, 16):
+                        s = h.strips(nrhs, tr)
+                        assert s["strips"] > 0
+                        assert s["slots"] == longest if longest <= 4 else s["slots"] in (13, 15)
+                        assert s["sums"] == (4 if longest > 4 and nrhs == 1 else 1)
+                        assert s["depth"] == (16 if longest <= 4 else 8 if dt == torch.float32 else 4)
+                for o in ({"assign": 0}, {"algo": 1}, {"group": 1}, {"wg": 128}, {"poll": 0}):
+                    g = sp.Handle(*dev_tri(t, dt), uplo="U" if upper else "L", setup=setup)
+                    assert g.configure(**{"algo": 2, **o}).strips()["strips"] == 0
+
+
+def test_what_is_no_grid_stays_row_wise(sp):
+    """Bands that run across the line ends of the grid their offsets suggest,
+    an irregular triangle, and a batch with one system that is no grid."""
+    for T in (_banded(900, [1, 30]), _banded(900, [29, 30]), _banded(1000, [1, 10, 100], upper=True),
+              _banded(900, [2, 5, 7]), W.powerlaw_lower(5000, 3, window=700)):
+        h = sp.Handle(*dev_tri(T), uplo="U" if T.upper else "L").configure(algo=2)
+        h.prepare_transpose()
+        assert h.strips()["strips"] == 0 and h.strips(transpose=True)["strips"] == 0
+    grids = [W.ilu0_lower((s, t)) for s, t in ((33, 20), (64, 64), (25, 70))]
+    for tris, want in ((grids, True), (grids + [_banded(300, [2, 5, 7])], False)):
+        d = [dev_tri(t) for t in tris]
+        h = sp.BatchedHandle([a[0] for a in d], [a[1] for a in d], [a[2] for a in d]).configure(algo=2)
+        h.prepare_transpose()
+        assert (h.strips()["strips"] > 0) == want and (h.strips(transpose=True)["strips"] > 0) == want
+
+
+def test_both_depths_of_long_fp64_records(sp):
+    """Records of 13 entries a row on both sides of the size from which they
+    are loaded further ahead, against the row-wise schedule bit for bit."""
+    for side, depth in ((45, 4), (100, 8)):
+        T = W.stencil_triangle((side, side, side), 27)
+        d, b = dev_tri(T), dev(W.uniform_vector(T.n, 20))
+        h = sp.Handle(*d, setup="device")
+        assert h.strips()["depth"] == depth and h.strips(2)["depth"] == depth
+        x = h.solve(b)
+        h.status()
+        assert bits_equal(x, sp.Handle(*d, setup="device").configure(algo=2, assign=0).solve(b))

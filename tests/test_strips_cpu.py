@@ -60,3 +60,13 @@ def test_patterns_that_are_no_grid(check):
     assert check(band([2, 5, 7])) != 0
     assert check(band([1, 30])) == 4
     assert check(band([29, 30]), attempt=1) in (0, 4)
+
+
+def test_second_reading_of_a_cluster_of_two_offsets(check):
+    """Offsets 29 and 30: a grid of 29 columns whose entries reach back over
+    line ends on the first reading, one of 30 on the second; neither fits."""
+    i = np.arange(900)
+    cols = [[r - o for o in (30, 29) if r >= o] + [r] for r in i]
+    rp = np.concatenate([[0], np.cumsum([len(c) for c in cols])]).astype(np.int32)
+    T = W.Triangle(900, rp, np.concatenate(cols).astype(np.int32), np.ones(rp[-1]))
+    assert check(T) == 4 and check(T, attempt=1) == 4
