@@ -66,6 +66,7 @@ struct PlanState {
   int* a_jlev = nullptr;
   PushState push;
   DevStrips strips;               // strip-ordered copy (strips.hpp), if the rows sit on a grid
+  SolveCost strip_cost;           // and what a solve in strips costs
   void* vals_buf = nullptr;       // [noff + 2n] values: off-diagonals, diagonal, 1/diagonal
   // (group, epl, rows_fixed, rows_per_lane)
   std::map<std::tuple<int, int, int, int>, ChunkEntry> chunks;
@@ -101,7 +102,8 @@ struct Config {
   int stride = 1;  // static schedules, one right-hand side: elements between xp values
   int mrows = 0;   // static schedule, several right-hand sides: rows per lane group
                    // (1, 2, 4; 0 = by the number of right-hand sides)
-  int strip = 0;   // self-scheduled over strips where the plan has them (same bits)
+  int strip = 0;   // self-scheduled over strips where the plan has them (same bits):
+                   // 1 = if they are faster by the estimates, 2 = the tuner's choice
 };
 
 std::mutex g_tune_mu;
@@ -707,7 +709,7 @@ bool strip_rule(sptrsv_handle_t h) {
 Config resolve(sptrsv_handle_t h) {
   if (h->tuned) {
     Config c = h->tuned_cfg;
-    c.strip = c.strip && strip_rule(h);   // options set since, another handle's choice
+    if (!strip_rule(h)) c.strip = 0;   // options set since, another handle's choice
     return c;
   }
   Config c{h->algo, h->group, h->epl, h->sync, h->rpl, h->grid, h->assign};
@@ -763,7 +765,7 @@ Config resolve_multi(sptrsv_handle_t h, int nrhs) {
   auto it = h->tuned_multi.find(nrhs);
   if (it != h->tuned_multi.end()) {
     Config c = it->second;
-    c.strip = c.strip && strip_rule(h);   // options set since
+    if (!strip_rule(h)) c.strip = 0;   // options set since
     return c;
   }
   Config c = resolve(h);
@@ -773,7 +775,7 @@ Config resolve_multi(sptrsv_handle_t h, int nrhs) {
     c.algo = SPTRSV_ALGO_SELF;
   // strips take any number of columns (128^3, 16 columns: 983 us row-wise,
   // 420 us in strips); rows per lane group set explicitly ask for the row-wise form
-  c.strip = c.strip && h->mrows == 0;
+  c.strip = c.strip && h->mrows == 0;   // by the estimates, whatever one column chose
   // options left unset, by the column count (where sptrsv_tune_multi's picks
   // changed on 128^3 and ILU(0) 96^3): 2, 4, 8 wavefronts per CU from 2, 8,
   // 16 columns; XCD-regional lists up to 4 columns, round-robin beyond
@@ -867,10 +869,24 @@ std::vector<std::vector<StripGrid>> grid_guesses(sptrsv_handle_t h, bool upper) 
   return all;
 }
 
-// The strip-ordered copy of a plan (strips.hpp), if its rows sit on a grid and memory
-// allows; otherwise the plan keeps the row-wise schedules alone.  Blocking.
+// The strip-ordered copy of a plan (strips.hpp), if its rows sit on a grid, a
+// solve of one or of many columns gains by it, and memory allows; otherwise the
+// plan keeps the row-wise schedules alone.  Blocking.
 int build_strip_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t s) {
   if (h->offsets.empty() || ps.strips.nstrips) return kOk;
+  std::vector<std::vector<StripGrid>> grids;
+  std::vector<SolveCost> costs;
+  for (std::vector<StripGrid>& g : grid_guesses(h, upper)) {
+    const SolveCost c = strip_cost(g, ps.h.max_row_len, static_cast<int>(h->vb));
+    bool gain = false;
+    for (int nrhs : {1, 16})
+      gain |= strip_time(c, nrhs) <
+              row_time(ps.h.n, ps.h.noff, ps.h.nlev, ps.h.max_row_len, false, nrhs);
+    if (!gain) continue;
+    grids.push_back(std::move(g));
+    costs.push_back(c);
+  }
+  if (grids.empty()) return kOk;
   int st = kOk;
   unsigned char* lanes = nullptr;
   if (ps.h.max_row_len > kStripLaneEntries) {
@@ -884,14 +900,13 @@ int build_strip_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t 
     if (ps.d.row_pos && launch_row_pos(h->n, ps.d.pos_row, ps.d.row_pos, s) != hipSuccess)
       st = kErrHip;
   }
-  for (int attempt = 0; attempt < 2 && !st; ++attempt) {
-    std::vector<StripGrid> grids;
-    if (!infer_grids(h, upper, attempt, grids)) break;
-    st = build_strips(ps.d, grids, ps.h.max_row_len, lanes, static_cast<int>(h->vb), s, ps.strips);
+  for (size_t q = 0; q < grids.size() && !st; ++q) {
+    st = build_strips(ps.d, grids[q], ps.h.max_row_len, lanes, static_cast<int>(h->vb), s, ps.strips);
     if (st == kErrNotSupported) {
       st = kOk;
       continue;
     }
+    ps.strip_cost = costs[q];
     if (!st && (h->dtype == SPTRSV_F64 ? launch_strip_gather<double>(ps.d, ps.strips, s)
                                        : launch_strip_gather<float>(ps.d, ps.strips, s)) != hipSuccess)
       st = kErrHip;
@@ -1225,10 +1240,16 @@ int solve_strips(sptrsv_handle_t h, PlanState& ps, const void* b, void* x, int n
 }
 
 // Whether a solve with schedule c is one in strips, memory permitting (the
-// tasks and their dump slots are counted in 32 bits).
+// tasks and their dump slots are counted in 32 bits): a triangle on a grid can
+// have far fewer levels than its strips have steps, where entries are missing
+// or the rows along a line do not depend on one another.
 bool takes_strips(const PlanState& ps, const Config& c, int nrhs) {
   const int64_t tasks = static_cast<int64_t>(ps.strips.nstrips) * nrhs;
-  return c.strip && tasks > 0 && tasks < INT32_MAX / kDumpSlot;
+  return c.strip && tasks > 0 && tasks < INT32_MAX / kDumpSlot &&
+         (c.strip == 2 ||
+          strip_time(ps.strip_cost, nrhs) <
+              row_time(ps.h.n, ps.h.noff, ps.h.nlev, ps.h.max_row_len,
+                       c.algo == SPTRSV_ALGO_BLOCK && nrhs == 1, nrhs));
 }
 
 template <typename T>
@@ -2197,7 +2218,7 @@ int sptrsv_tune(sptrsv_handle_t h, const void* b, void* x, hipStream_t stream) {
         }
     if (strip_rule(h)) {
       Config c{SPTRSV_ALGO_SELF, grp, epl, SPTRSV_SYNC_VALUE, 1, 0, SPTRSV_ASSIGN_TICKET};
-      c.strip = 1;
+      c.strip = 2;
       cand.push_back(c);
     }
     for (int rpl : {1, 4})
@@ -2292,7 +2313,7 @@ int sptrsv_tune_multi(sptrsv_handle_t h, int32_t nrhs, int32_t ld, const void* B
                        is_column(h->algo);
   if (self_ok && strip_rule(h) && h->mrows == 0) {
     Config c{SPTRSV_ALGO_SELF, 0, 4, SPTRSV_SYNC_VALUE, 1, 0, SPTRSV_ASSIGN_TICKET};
-    c.strip = 1;
+    c.strip = 2;
     cand.push_back(c);
   }
   if (self_ok)

@@ -43,6 +43,8 @@ struct StripGrid {
   int stride = 1;            // row index step along the lines
   int dmax = 1;              // steps back of the farthest dependency
   int gu = 0, gv = 0;        // lines back of the farthest dependency, per lane coordinate
+  double chain = 0, work = 0;   // steps of the longest chain of strips (a hop counts
+                             // as ten), and of all strips: estimates
   int npub = 0;              // lanes that other strips read
   int nghost = 0;            // lines of other strips that a strip reads
   // ghost of a line outside the strip: ghost[(u + gu) + (v + gv) * (2^lu + gu)],
@@ -150,5 +152,18 @@ SPTRSV_HD void strip_line(const StripGrid& g, int u, int v, int* lo_out, int* hi
 // picks the strips' shape.  `attempt` 0, 1 choose between the readings of an
 // offset cluster of even width.  false: no grid.
 bool strip_infer(const std::vector<int>& offsets, int n, bool upper, int attempt, StripGrid* g);
+
+// What decides between the strip form and the row-wise schedules.
+struct SolveCost {
+  double chain = 0;          // steps of the longest chain, over all systems
+  double strips = 0, work = 0;   // strips, and their steps, of all systems
+  int words = 0;             // 32-bit words of a lane's record
+};
+SolveCost strip_cost(const std::vector<StripGrid>& grids, int max_len, int vb);
+
+// Estimated time of a solve in strips, and row by row (block: by the block
+// schedule), in us.
+double strip_time(const SolveCost& c, int nrhs);
+double row_time(int64_t n, int64_t noff, int nlev, int max_len, bool block, int nrhs);
 
 }  // namespace sptrsv

@@ -137,12 +137,17 @@ bool strip_infer(const std::vector<int>& offsets, int n, bool upper, int attempt
                               static_cast<int64_t>(g.be) * (g.nz - 1),
                           g.ny + static_cast<int64_t>(g.ga) * (g.nz - 1), g.nz};
   if (ext[0] > (1 << 30) || ext[1] > (1 << 30)) return false;
-  // Shape: every shape walks the same chain of steps (one per level), and
-  // waits one hop, worth about ten steps, per strip that the chain crosses.
-  // What differs besides is the work on lanes without a row: counted here as
-  // steps of all strips over the wavefronts that share them.  Walking along x
-  // (axis 0) reads b and writes x in order, so the others have to gain a
-  // quarter.
+  // Shape: what differs is the chain of steps, and the work on lanes without a
+  // row, counted here as steps of all strips over the wavefronts that share
+  // them.  A line is walked step by step, and a lane starts one step after its
+  // neighbour whether it needs it or not, so the chain has the steps of a line
+  // and those of a strip's lanes; lines of other strips add theirs, and a hop,
+  // worth about ten steps, per strip, only in a direction in which rows depend
+  // on one another.  So a direction without dependencies, such as the lines of
+  // a pattern with entries one plane back only, belongs across the lanes, not
+  // along the walk.  (With dependencies in every direction all shapes have the
+  // same chain, one step per level, but for the hops.)  Walking along x (axis
+  // 0) reads b and writes x in order, so the others have to gain a quarter.
   StripGrid best;
   double best_cost = 0;
   bool found = false;
@@ -160,8 +165,13 @@ bool strip_infer(const std::vector<int>& offsets, int n, bool upper, int attempt
       const double steps = static_cast<double>(nbu * nbv) *
                            static_cast<double>(len + std::min<int64_t>(eu, 1 << g.lu) +
                                                std::min<int64_t>(ev, 1 << g.lv) - 2 + g.dmax);
-      double cost = static_cast<double>(ext[0] + ext[1] + ext[2]) +
-                    10.0 * static_cast<double>(nbu + nbv - 2) + steps / 512;
+      const int64_t lanes_u = g.gu ? eu : std::min<int64_t>(eu, 1 << g.lu),
+                    lanes_v = g.gv ? ev : std::min<int64_t>(ev, 1 << g.lv);
+      g.chain = static_cast<double>((axis == 0 ? ext[0] : axis == 1 ? ext[1] : ext[2]) + lanes_u +
+                                    lanes_v) +
+                10.0 * static_cast<double>((g.gu ? nbu - 1 : 0) + (g.gv ? nbv - 1 : 0));
+      g.work = steps;
+      double cost = g.chain + steps / 512;
       if (axis != 0) cost *= 1.25;
       g.nbu = static_cast<int>(nbu);
       g.nbv = static_cast<int>(nbv);
@@ -179,6 +189,53 @@ bool strip_infer(const std::vector<int>& offsets, int n, bool upper, int attempt
   if (upper) best.stride = -best.stride;
   *out = best;
   return true;
+}
+
+SolveCost strip_cost(const std::vector<StripGrid>& grids, int max_len, int vb) {
+  SolveCost c;
+  for (const StripGrid& g : grids) {
+    if (g.n == 0) continue;
+    c.chain = std::max(c.chain, g.chain);
+    c.strips += static_cast<double>(g.nbu) * g.nbv;
+    c.work += g.work;
+  }
+  const int slots = max_len > 4 ? 15 : std::max(2, max_len);
+  c.words = (slots + 1) * (vb / 4) + (slots + 1) / 2;
+  return c;
+}
+
+// Strips: 10 us of two launches (12.4 at least, call after call); 0.088 us a step
+// of the chain (0.083 to 0.1
+// measured); and the most of 0.0135 us a task, whose tickets are claimed one
+// after another (4000 systems of 8x8, 1 / 8 columns: 64 / 385 us), 3500 steps of
+// all tasks in a us (256 systems of 144x144, 1 / 8 columns: 88 / 463), and the
+// records' bytes at 5 TB/s (columns find them in the cache: 100^3 27-point, 1 / 4
+// columns: 245 / 254).
+double strip_time(const SolveCost& c, int nrhs) {
+  const double tasks = std::max(
+      {0.0135 * c.strips * nrhs, c.work * nrhs / 3500, c.work * c.words * 256 / 5e6});
+  return std::max(12.4, 10 + 0.088 * c.chain + tasks);
+}
+
+// Row by row: a hop per level, 0.7 us (rows of several lanes 1.2; several
+// columns 0.8 and 1.6; the block schedule 0.35), and the rows' bytes where
+// levels are wide.  Measured, us, strips / row-wise, with what the two
+// functions give in brackets:
+//   128^3 7-point, 382 levels                       99 / 373  (89 / 404)
+//   128^2 5-point, half of the entries, 53 levels   33 / 52   (34 / 50)
+//   128^2 5-point, a fifth of the entries, 10       33 / 19   (34 / 19)
+//   512^2 5-point, a third of the entries, 22      107 / 44   (108 / 34)
+//   offset 16,384 only on 2 M rows, 128 levels      32 / 121  (45 / 164)
+//   16,384 rows in 64 chains, 256 levels          1369 / 177  (1458 / 192)
+//   20,000 independent rows                       1694 / 16   (1777 / 13)
+//   1000 systems of 16x16, 31 levels                33 / 46   (26 / 45)
+//   the same, eight columns                        113 / 83   (121 / 88)
+//   5 rows in a chain, against the block schedule 12.3 / 10.8 (12.4 / 10.8)
+double row_time(int64_t n, int64_t noff, int nlev, int max_len, bool block, int nrhs) {
+  if (nrhs > 1)
+    return 24 + (max_len > 4 ? 1.6 : 0.8) * nlev + 1.9e-5 * static_cast<double>(n) * nrhs;
+  if (block) return std::max(10.8, 6.5 + 0.35 * nlev);   // one launch
+  return 12 + (max_len > 4 ? 1.2 : 0.7) * nlev + 1.5e-5 * static_cast<double>(n + noff);
 }
 
 }  // namespace sptrsv

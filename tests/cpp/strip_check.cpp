@@ -129,3 +129,20 @@ extern "C" int check_levels(int n, const int* rp, const int* ci, int upper, int 
   }
   return differ;
 }
+
+// Estimated times of a solve in strips and row by row (one system repeated
+// `systems` times), and the shape: us, us, strips, axis.
+extern "C" int strip_costs(int n, const int* rp, const int* ci, int upper, int nlev, int systems,
+                           int nrhs, double* out) {
+  StripGrid g;
+  if (!infer(n, rp, ci, upper, 0, &g)) return -1;
+  int max_len = 0;
+  for (int i = 0; i < n; ++i) max_len = std::max(max_len, rp[i + 1] - rp[i] - 1);
+  const SolveCost c = strip_cost(std::vector<StripGrid>(systems, g), max_len, 8);
+  const int64_t rows = static_cast<int64_t>(n) * systems, off = static_cast<int64_t>(rp[n] - n) * systems;
+  out[0] = strip_time(c, nrhs);
+  out[1] = row_time(rows, off, nlev, max_len, false, nrhs);
+  out[2] = c.strips;
+  out[3] = g.axis;
+  return 0;
+}

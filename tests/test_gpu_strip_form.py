@@ -7,6 +7,7 @@ import torch
 import workloads as W
 from gpuhelp import bits_equal, dev, dev_tri
 from test_gpu_strips import GRIDS, _banded, _dropped
+from test_strips_cpu import band
 
 pytestmark = pytest.mark.gpu
 
@@ -69,3 +70,42 @@ def test_both_depths_of_long_fp64_records(sp):
         x = h.solve(b)
         h.status()
         assert bits_equal(x, sp.Handle(*d, setup="device").configure(algo=2, assign=0).solve(b))
+
+
+@pytest.mark.parametrize("n,offsets", [(7000, [1000]), (17321, [1000]), (100000, [5000]), (4096, [64, 1024]),
+                                       (4001, [64, 1024]), (6000, [1, 600])])
+@pytest.mark.parametrize("setup", ["host", "device"])
+def test_lines_without_coupling(sp, n, offsets, setup):
+    """Entries one line or plane back only: strips whose lanes, or which
+    themselves, do not depend on one another, against the row-wise schedule."""
+    T = band(n, offsets)
+    T.vals = np.where(T.col_idx == np.repeat(np.arange(n), np.diff(T.row_ptr)), 1.5,
+                      np.random.default_rng(3).uniform(-1, 1, T.nnz))
+    for dt in (torch.float64, torch.float32):
+        d, b = dev_tri(T, dt), dev(W.uniform_vector(n, 7), dt)
+        h = sp.Handle(*d, setup=setup).configure(algo=2)
+        h.prepare_transpose()
+        assert h.strips()["strips"] and h.strips(transpose=True)["strips"] and h.strips(3)["strips"]
+        ref = sp.Handle(*d, setup=setup).configure(algo=2, assign=0)
+        for _ in range(2):
+            assert bits_equal(h.solve(b), ref.solve(b)) and bits_equal(h.solve_t(b), ref.solve_t(b))
+        X = h.solve_multi(torch.stack([b, 2 * b, -b]))
+        assert bits_equal(X[1], ref.solve(2 * b)) and bits_equal(X[2], ref.solve(-b))
+        h.status()
+
+
+@pytest.mark.parametrize("setup", ["host", "device"])
+def test_shallow_triangles_are_solved_row_wise(sp, setup):
+    """Far fewer levels than a line of the grid has rows."""
+    chains = band(16384, [1])
+    cut = (chains.col_idx % 256 != 255) | (chains.col_idx == np.repeat(np.arange(16384), np.diff(chains.row_ptr)))
+    rp = np.concatenate([[0], np.cumsum(np.add.reduceat(cut, chains.row_ptr[:-1]))]).astype(np.int32)
+    for T in (band(20000, []), band(400000, [100000]),
+              W.Triangle(16384, rp, chains.col_idx[cut], chains.vals[cut])):
+        d, b = dev_tri(T), dev(W.uniform_vector(T.n, 7))
+        h = sp.Handle(*d, setup=setup)
+        h.prepare_transpose()
+        assert not any(h.strips(k, t)["strips"] for k in (1, 8) for t in (False, True))
+        x, one = h.solve(b), sp.Handle(*d, setup=setup).configure(algo=1, group=1)
+        h.status()
+        assert bits_equal(x, one.solve(b)) and bits_equal(h.solve_t(b), one.solve_t(b))

@@ -202,3 +202,97 @@ def test_tuned_columns_respect_the_rows_option(m):
     h.set(multi_rows=0)
     assert h.tune(4) == 0 and h.form(4) == "strips"
     assert h.set(wg=128).form(4) != "strips"
+
+
+def _rows(n, pairs):
+    """Unit-pattern triangle with the given (rows, columns) off the diagonal."""
+    i = np.arange(n, dtype=np.int64)
+    key = np.unique(np.concatenate([i * n + i] + [r * n + c for r, c in pairs]))
+    rp = np.zeros(n + 1, np.int64)
+    np.cumsum(np.bincount(key // n, minlength=n), out=rp[1:])
+    return W.Triangle(n, rp.astype(np.int32), (key % n).astype(np.int32), np.ones(key.size))
+
+
+def _chains(n, length):
+    i = np.arange(n, dtype=np.int64)
+    k = i[i % length != 0]
+    return _rows(n, [(k, k - 1)])
+
+
+def _offset(n, *offsets):
+    return _rows(n, [(np.arange(o, n, dtype=np.int64), np.arange(n - o, dtype=np.int64)) for o in offsets])
+
+
+def _half(n):
+    i = np.arange(n // 2, n, dtype=np.int64)
+    return _rows(n, [(i, i - n // 2), (i[1:], i[1:] - n // 2 - 1)])
+
+
+def _planes(side):
+    """Layers of a 3-D grid that do not depend on one another: reads as a 2-D
+    grid of side x side^2."""
+    i = np.arange(side ** 3, dtype=np.int64)
+    x, y = i % side, i // side % side
+    return _rows(side ** 3, [(i[x > 0], i[x > 0] - 1), (i[y > 0], i[y > 0] - side)])
+
+
+# wide, shallow triangles on grid-like offsets: far fewer levels than a line has rows
+SHALLOW = {"independent": _rows(20000, []), "independent_few": _rows(500, []),
+           "far_offset": _offset(400000, 100000), "chains": _chains(16384, 256),
+           "short_chains": _chains(20000, 10), "two_colours": _half(60000), "planes": _planes(64)}
+
+
+@pytest.mark.parametrize("name", SHALLOW)
+def test_shallow_triangles_are_solved_row_wise(m, name):
+    h = Model(m, SHALLOW[name])
+    for t in (False, True):
+        for nrhs in (1, 8):
+            assert h.form(nrhs, t) != "strips", (t, nrhs)
+    h.set(algo=2)
+    assert h.form() != "strips"
+
+
+def test_deep_triangles_are_solved_in_strips(m):
+    """Also where only some directions of the grid, or some entries, are there."""
+    rng = np.random.Generator(np.random.PCG64(1))
+    T = W.laplacian_triangle((96, 96))
+    rows = np.repeat(np.arange(T.n, dtype=np.int64), np.diff(T.row_ptr))
+    k = rng.random(T.nnz) < 0.5
+    for T in (W.laplacian_triangle((64, 64)), W.laplacian_triangle((20, 30, 16)), _offset(100000, 1000),
+              _offset(300000, 5000), _chains(3000, 3000), _chains(3000, 500),
+              _rows(T.n, [(rows[k], T.col_idx[k].astype(np.int64))])):
+        h = Model(m, T)
+        assert h.form() == "strips" and h.form(8) == "strips" and h.form(t=True) == "strips"
+
+
+def test_tiny_triangles_take_one_launch(m):
+    for T in (_chains(5, 5), W.laplacian_triangle((4, 4)), W.laplacian_triangle((1, 1))):
+        assert Model(m, T).form() == "block"
+    assert Model(m, W.laplacian_triangle((16, 16))).form() == "strips"
+
+
+def test_batches_of_many_small_systems(m):
+    """Strips cost a claim each, so many small systems keep the row-wise form,
+    more so with several columns."""
+    def batch(side, count):
+        return W.concat_block_diagonal([W.laplacian_triangle((side, side))] * count)
+
+    def form(side, count, nrhs):
+        T = batch(side, count)
+        n1, z1 = side * side, T.nnz // count
+        one = W.laplacian_triangle((side, side))
+        rp, ci, v = (np.ascontiguousarray(a, t) for a, t in
+                     ((one.row_ptr, np.int32), (one.col_idx, np.int32), (one.vals, np.float64)))
+        h = Model.__new__(Model)
+        h.m, h.n, h.h = m, T.n, P()
+        h.b, h.x = np.ones(T.n * 16), np.zeros(T.n * 16)
+        arr = lambda a: (P * count)(*[a.ctypes.data] * count)
+        assert m.sptrsv_analyze_batched_ex(I32(count), (I32 * count)(*[n1] * count),
+                                           (I32 * count)(*[z1] * count), arr(rp), arr(ci), arr(v), 0,
+                                           0, 0, 0, None, ctypes.byref(h.h)) == 0
+        out = h.form(nrhs)
+        h.destroy()
+        return out
+    assert form(8, 1200, 1) != "strips" and form(3, 1000, 1) != "strips"
+    assert form(16, 300, 16) != "strips"
+    assert form(32, 64, 1) == "strips" and form(32, 64, 8) == "strips"

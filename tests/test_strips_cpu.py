@@ -70,3 +70,36 @@ def test_second_reading_of_a_cluster_of_two_offsets(check):
     rp = np.concatenate([[0], np.cumsum([len(c) for c in cols])]).astype(np.int32)
     T = W.Triangle(900, rp, np.concatenate(cols).astype(np.int32), np.ones(rp[-1]))
     assert check(T) == 4 and check(T, attempt=1) == 4
+
+
+def band(n, offsets):
+    """Rows with an entry at each offset (each divides the next) unless it would
+    lie beyond the start of the row's line or plane."""
+    i = np.arange(n)
+    ends = list(offsets[1:]) + [n]
+    has = [i % e >= o for o, e in zip(offsets, ends)]
+    r = np.concatenate([i] + [i[k] for k in has])
+    c = np.concatenate([i] + [i[k] - o for k, o in zip(has, offsets)])
+    order = np.lexsort((c, r))
+    rp = np.zeros(n + 1, np.int64)
+    np.cumsum(np.bincount(r, minlength=n), out=rp[1:])
+    return W.Triangle(n, rp.astype(np.int32), c[order].astype(np.int32), np.ones(r.size))
+
+
+@pytest.mark.parametrize("n,offsets", [(7000, [1000]), (7321, [1000]), (30000, [5000]), (4096, [64, 1024]),
+                                       (4001, [64, 1024]), (6000, [1, 600]), (9000, [100])])
+def test_lines_without_coupling(check, n, offsets):
+    """Entries one line or plane back only: the walk follows them, the lines
+    that do not depend on one another lie across the lanes."""
+    T = band(n, offsets)
+    assert check(T) == 0
+    assert check.levels(T) == 0
+    assert check(_transposed(T)) == 0
+
+
+def _transposed(T):
+    rows = np.repeat(np.arange(T.n), np.diff(T.row_ptr))
+    order = np.lexsort((rows, T.col_idx))
+    rp = np.zeros(T.n + 1, np.int64)
+    np.cumsum(np.bincount(T.col_idx, minlength=T.n), out=rp[1:])
+    return W.Triangle(T.n, rp.astype(np.int32), rows[order].astype(np.int32), T.vals[order], upper=True)
