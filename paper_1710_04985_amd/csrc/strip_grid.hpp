@@ -19,6 +19,7 @@ constexpr int kStripMaxBack = 7;       // steps an entry may reach back
 constexpr int kRingCols = 128;         // its columns: lanes, ghosts, and the zero column
 constexpr int kZeroCol = 127;
 constexpr int kMaxGhosts = 63;
+constexpr int kStripMaxSteps = 1 << 17;  // steps of a strip
 constexpr int kStripMaxOffsets = 13;   // distinct offsets of a pattern (27-point stencil)
 constexpr int kStripTable = 32;        // slots of the device's offset table per system
 constexpr int kStripMaxEntries = 16;   // entry slots of a row
@@ -84,20 +85,28 @@ SPTRSV_HD StripPoint strip_point(const StripGrid& g, int r) {
                      : g.axis == 1 ? StripPoint{c1, z, c2} : StripPoint{c1, c2, z};
 }
 
-// row (relative to row0) at a point, or -1
-SPTRSV_HD int strip_row(const StripGrid& g, const StripPoint& p) {
-  const int c1 = g.axis == 0 ? p.w : p.u;
-  const int c2 = g.axis == 0 ? p.u : g.axis == 1 ? p.w : p.v;
-  int z = g.axis == 2 ? p.w : p.v;
-  int y = c2 - g.ga * z, x = c1 - g.al * y - g.be * z;
-  if (x < 0 || x >= g.nx || y < 0 || y >= g.ny || z < 0 || z >= g.nz) return -1;
+// row index (relative to row0) of a point, which may lie outside the grid: linear
+// in its coordinates; *inside: whether it lies in the grid, its last plane and
+// line taken to be whole
+SPTRSV_HD int64_t strip_index(const StripGrid& g, const StripPoint& p, bool* inside) {
+  const int64_t c1 = g.axis == 0 ? p.w : p.u;
+  const int64_t c2 = g.axis == 0 ? p.u : g.axis == 1 ? p.w : p.v;
+  int64_t z = g.axis == 2 ? p.w : p.v;
+  int64_t y = c2 - g.ga * z, x = c1 - g.al * y - g.be * z;
+  *inside = x >= 0 && x < g.nx && y >= 0 && y < g.ny && z >= 0 && z < g.nz;
   if (g.upper) {
     x = g.nx - 1 - x;
     y = g.ny - 1 - y;
     z = g.nz - 1 - z;
   }
-  const int64_t r = x + static_cast<int64_t>(g.sy) * y + static_cast<int64_t>(g.sz) * z;
-  return r < g.n ? static_cast<int>(r) : -1;
+  return x + g.sy * y + g.sz * z;
+}
+
+// row (relative to row0) at a point, or -1
+SPTRSV_HD int strip_row(const StripGrid& g, const StripPoint& p) {
+  bool inside;
+  const int64_t r = strip_index(g, p, &inside);
+  return inside && r < g.n ? static_cast<int>(r) : -1;
 }
 
 // [lo, hi) := the w in it with 0 <= k w + m < N
@@ -141,9 +150,12 @@ SPTRSV_HD void strip_line(const StripGrid& g, int u, int v, int* lo_out, int* hi
     strip_clip(-ga, v, g.ny, &lo, &hi);
     strip_clip(al * ga - be, u - al * static_cast<int64_t>(v), g.nx, &lo, &hi);
   }
-  // the last line or plane may be cut off by n
-  while (lo < hi && strip_row(g, StripPoint{u, v, static_cast<int>(lo)}) < 0) ++lo;
-  while (lo < hi && strip_row(g, StripPoint{u, v, static_cast<int>(hi - 1)}) < 0) --hi;
+  // the last line or plane may be cut off by n: the row at w is linear in it
+  if (lo < hi) {
+    bool inside;
+    const int64_t first = strip_index(g, StripPoint{u, v, static_cast<int>(lo)}, &inside);
+    strip_clip(g.stride, first - lo * g.stride, g.n, &lo, &hi);
+  }
   *lo_out = static_cast<int>(lo);
   *hi_out = static_cast<int>(hi);
 }

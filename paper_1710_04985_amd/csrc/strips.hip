@@ -781,6 +781,8 @@ int build_strips(const DevPlan& p, const std::vector<StripGrid>& grids, int max_
     gh[k].box0 = box0[k] = static_cast<int>(nboxes);
     nboxes += gh[k].n > 0 ? static_cast<int64_t>(gh[k].nbu) * gh[k].nbv : 0;
     if (nboxes > (1 << 22)) return kErrNotSupported;
+    if ((gh[k].axis == 0 ? gh[k].nx : gh[k].axis == 1 ? gh[k].ny : gh[k].nz) > kStripMaxSteps)
+      return kErrNotSupported;
   }
   box0[nsys] = static_cast<int>(nboxes);
   const int acc = lanes_lg ? 4 : 1;
@@ -862,7 +864,7 @@ int build_strips(const DevPlan& p, const std::vector<StripGrid>& grids, int max_
   }
   // lanes without a row cost memory: grids far from the strips' shape keep
   // the row-wise schedules
-  if (t.nstrips == 0 || t.nrec * 64 > 16ll * p.n + (1 << 20) || max_steps > (1 << 17))
+  if (t.nstrips == 0 || t.nrec * 64 > 16ll * p.n + (1 << 20) || max_steps > kStripMaxSteps)
     return kErrNotSupported;
   const int E = t.entries, vw = vb / 4;
   t.words = (E + 1) * vw + (E + 1) / 2;

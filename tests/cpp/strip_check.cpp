@@ -146,3 +146,32 @@ extern "C" int strip_costs(int n, const int* rp, const int* ci, int upper, int n
   out[3] = g.axis;
   return 0;
 }
+
+// Lines of the grid of the given offsets whose run of rows is not what a search
+// of every step finds, or -1: no grid.  limit > 0: only so many lines from
+// either end, without the search.
+extern "C" int check_lines(int n, const int* offsets, int count, int upper, int axis, int limit) {
+  StripGrid g;
+  if (!strip_infer(std::vector<int>(offsets, offsets + count), n, upper != 0, 0, &g)) return -1;
+  g.axis = axis;
+  g.stride = axis == 0   ? 1
+             : axis == 1 ? g.sy - g.al
+                         : g.sz - g.ga * g.sy + g.al * g.ga - g.be;
+  if (upper) g.stride = -g.stride;
+  const int e1 = g.nx + g.al * (g.ny - 1) + g.be * (g.nz - 1), e2 = g.ny + g.ga * (g.nz - 1);
+  const int eu = axis == 0 ? e2 : e1, ev = axis == 2 ? e2 : g.nz, ew = axis == 0 ? e1 : axis == 1 ? e2 : g.nz;
+  int wrong = 0;
+  for (int v = 0; v < ev; ++v)
+    for (int u = 0; u < eu; ++u) {
+      if (limit && u >= limit && u < eu - limit) continue;
+      int lo, hi;
+      strip_line(g, u, v, &lo, &hi);
+      if (limit) continue;
+      for (int w = 0; w < ew; ++w) {
+        const int r = strip_row(g, StripPoint{u, v, w});
+        wrong += (r >= 0) != (w >= lo && w < hi);
+        if (r >= 0 && w > lo) wrong += r - strip_row(g, StripPoint{u, v, w - 1}) != g.stride;
+      }
+    }
+  return wrong;
+}

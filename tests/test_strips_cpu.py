@@ -4,6 +4,7 @@ values brought in as late and as early as the kernel may."""
 import ctypes
 import os
 import subprocess
+import time
 
 import numpy as np
 import pytest
@@ -28,6 +29,7 @@ def check(tmp_path_factory):
         ci = np.ascontiguousarray(T.col_idx[:rp[-1]], np.int32)
         p = lambda a: a.ctypes.data_as(ctypes.c_void_p)
         return fn(n, p(rp), p(ci), int(T.upper), attempt)
+    run.lib = lib
     run.levels = lambda T, **o: run(T, fn=lib.check_levels, **o)
     return run
 
@@ -103,3 +105,31 @@ def _transposed(T):
     rp = np.zeros(T.n + 1, np.int64)
     np.cumsum(np.bincount(T.col_idx, minlength=T.n), out=rp[1:])
     return W.Triangle(T.n, rp.astype(np.int32), rows[order].astype(np.int32), T.vals[order], upper=True)
+
+
+STENCILS = {"5": [(0, 1, 0), (1, 0, 0)], "9": [(0, 1, 0)] + [(1, a, 0) for a in (-1, 0, 1)],
+            "7": [(0, 1, 0), (1, 0, 0), (0, 0, 1)],
+            "27": [(0, 1, 0)] + [(1, a, 0) for a in (-1, 0, 1)] +
+                  [(b, a, 1) for b in (-1, 0, 1) for a in (-1, 0, 1)]}
+
+
+@pytest.mark.parametrize("axis", [0, 1, 2])
+@pytest.mark.parametrize("upper", [False, True])
+@pytest.mark.parametrize("dims,stencil", [((9, 6, 1), "5"), ((7, 8, 1), "9"), ((5, 6, 4), "7"), ((5, 4, 6), "27")])
+def test_runs_of_cut_lines(check, dims, stencil, upper, axis):
+    """The rows on a line, in closed form, where n cuts the last line or plane
+    anywhere."""
+    sy, sz = dims[0], dims[0] * dims[1]
+    offs = np.array(sorted(b * sy + a + c * sz for b, a, c in STENCILS[stencil]), np.int32)
+    for n in range(sz * (dims[2] - 1) + 1 if dims[2] > 1 else 2 * sy + 1, sz * dims[2] + 1):
+        rc = check.lib.check_lines(n, offs.ctypes.data_as(ctypes.c_void_p), offs.size, int(upper), axis, 0)
+        assert rc == 0, n
+
+
+@pytest.mark.parametrize("upper", [False, True])
+def test_long_cut_lines_take_no_search(check, upper):
+    offs = np.array([1, 500000000], np.int32)
+    t0 = time.perf_counter()
+    for _ in range(100):
+        assert check.lib.check_lines(500000010, offs.ctypes.data_as(ctypes.c_void_p), 2, int(upper), 0, 2) == 0
+    assert time.perf_counter() - t0 < 1.0              # a search takes seconds for one
