@@ -206,17 +206,14 @@ k_strip_lanes_of(const StripGrid* __restrict__ grids, const StripBox* __restrict
   if (__any(bad) && lane == 0) atomicOr(&cnt->bad, 1);
 }
 
-// One wavefront per step of a strip: the ring addresses and value sources of
-// its rows' entries.
-__global__ void __launch_bounds__(kRecordThreads)
-k_strip_records(const int* __restrict__ off_ptr, const int* __restrict__ off_col,
-                const int* __restrict__ row_pos, const unsigned char* __restrict__ lanes_lg,
-                const StripGrid* __restrict__ grids, const StripBox* __restrict__ boxes, int vb,
-                DevStrips d, StripCount* cnt) {
-  const int p = blockIdx.x, lane = threadIdx.x & 63;
-  const int s = blockIdx.y * (kRecordThreads / 64) + (threadIdx.x >> 6);
-  const StripInfo inf = d.info[p];
-  if (s >= inf.steps) return;
+// Ring addresses and value sources of the rows of one record (step s of strip
+// p), by one wavefront.
+__device__ __forceinline__ void
+strip_record(const int* __restrict__ off_ptr, const int* __restrict__ off_col,
+             const int* __restrict__ row_pos, const unsigned char* __restrict__ lanes_lg,
+             const StripGrid* __restrict__ grids, const StripBox* __restrict__ boxes, int vb,
+             const DevStrips& d, StripCount* cnt, int p, int s, const StripInfo& inf) {
+  const int lane = threadIdx.x & 63;
   const StripBox bx = boxes[p];
   const StripGrid& g = grids[bx.sys];
   const StripLane l = d.lane[static_cast<int64_t>(p) * 64 + lane];
@@ -280,6 +277,31 @@ k_strip_records(const int* __restrict__ off_ptr, const int* __restrict__ off_col
       if (h < E) *word_at(d, rec, lane, cw + h / 2) = code[h] | (static_cast<unsigned>(code[h + 1]) << 16);
   }
   if (__any(bad) && lane == 0) atomicOr(&cnt->bad, 1);
+}
+
+// Workgroups per strip: four steps each, and all of the longest strip's at once
+// unless the strips' lengths differ so much that most workgroups would find
+// nothing to do (a batch of many small systems and one long chain); the long
+// ones' then take several turns.  (One wavefront per four records in a row,
+// its strip searched for: 128^3 set-up 1.36 ms against 1.32.)
+constexpr int kRecordWaves = kRecordThreads / 64;
+
+inline unsigned record_blocks(int64_t nrec, int nstrips, int max_steps) {
+  const int64_t all = (max_steps + kRecordWaves - 1) / kRecordWaves;
+  const int64_t fair = std::max<int64_t>(4 * nrec / nstrips / kRecordWaves + 1, 65536 / nstrips + 1);
+  return static_cast<unsigned>(std::min(all, fair));
+}
+
+__global__ void __launch_bounds__(kRecordThreads)
+k_strip_records(const int* __restrict__ off_ptr, const int* __restrict__ off_col,
+                const int* __restrict__ row_pos, const unsigned char* __restrict__ lanes_lg,
+                const StripGrid* __restrict__ grids, const StripBox* __restrict__ boxes, int vb,
+                DevStrips d, StripCount* cnt) {
+  const int p = blockIdx.x;
+  const StripInfo inf = d.info[p];
+  for (int s = blockIdx.y * kRecordWaves + (threadIdx.x >> 6); s < inf.steps;
+       s += gridDim.y * kRecordWaves)
+    strip_record(off_ptr, off_col, row_pos, lanes_lg, grids, boxes, vb, d, cnt, p, s, inf);
 }
 
 // values of the strip-ordered copy: entries a row lacks are -0, whose product
@@ -897,8 +919,8 @@ int build_strips(const DevPlan& p, const std::vector<StripGrid>& grids, int max_
     e = hipMemcpyAsync(box_strip_d, box_strip.data(), nboxes * sizeof(int), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) {
     k_strip_lanes_of<<<t.nstrips, 64, 0, s>>>(grids_d, boxes_d, box_strip_d, t, cnt);
-    constexpr int per = kRecordThreads / 64;
-    k_strip_records<<<dim3(t.nstrips, (max_steps + per - 1) / per), kRecordThreads, 0, s>>>(
+    k_strip_records<<<dim3(t.nstrips, record_blocks(t.nrec, t.nstrips, max_steps)), kRecordThreads,
+                      0, s>>>(
         p.off_ptr, p.off_col, p.row_pos, lanes_lg, grids_d, boxes_d, vb, t, cnt);
     e = hipGetLastError();
   }

@@ -109,3 +109,24 @@ def test_shallow_triangles_are_solved_row_wise(sp, setup):
         x, one = h.solve(b), sp.Handle(*d, setup=setup).configure(algo=1, group=1)
         h.status()
         assert bits_equal(x, one.solve(b)) and bits_equal(h.solve_t(b), one.solve_t(b))
+
+
+def test_set_up_of_small_systems_beside_a_long_chain(sp):
+    """5000 systems of 16x16 and a chain of 125,000 rows: the construction's work
+    follows the records, not the systems times the longest one's steps."""
+    small, chain = W.laplacian_triangle((16, 16)), W.bidiagonal_fast(125000, 2.0, 1.0)
+    ds, dc = dev_tri(small), dev_tri(chain)
+    d = [ds] * 5000 + [dc]
+    b = dev(W.uniform_vector(5000 * 256 + chain.n, 3))
+    one, long = sp.Handle(*ds).configure(algo=2, assign=0), sp.Handle(*dc).configure(algo=2, assign=0)
+    times = []
+    for _ in range(3):
+        h = sp.BatchedHandle([a[0] for a in d], [a[1] for a in d], [a[2] for a in d], setup="device")
+        assert h.strips()["strips"] == 5001
+        times.append(h.setup_info()[1])
+    x = h.solve(b)
+    h.status()
+    for k in (0, 2500, 4999):
+        assert bits_equal(x[256 * k:256 * (k + 1)], one.solve(b[256 * k:256 * (k + 1)].clone()))
+    assert bits_equal(x[5000 * 256:], long.solve(b[5000 * 256:].clone()))
+    assert min(times) < 20, times                        # measured 12; 41 before
