@@ -168,9 +168,9 @@ typedef enum {
     SPTRSV_OPT_POLL = 10,         /* how a waiting lane polls its dependencies (value sync):
                                      1 (default) = two rounds in flight over all of its
                                      slots, so a value is seen soon after it lands (static
-                                     schedules on triangles with rows of several lanes: one
-                                     value at a time, each row published when it is
-                                     ready); 0 = one
+                                     schedules on triangles with rows of several lanes that
+                                     wait for few values at once: one value at a time, each
+                                     row published when it is ready); 0 = one
                                      round at a time over the pending slots only (less
                                      polling traffic, better when most dependencies are
                                      already available) */

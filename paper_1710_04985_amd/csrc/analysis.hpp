@@ -50,6 +50,18 @@ void dependency_counts(int n, const int* row_ptr, const int* col, int* depcnt);
 void transpose_pattern(int n, const int* row_ptr, const int* col, std::vector<int>& rowT,
                        std::vector<int>& colT, std::vector<int>& srcT);
 
+// The default lane rule: entries per lane, and lanes of a row of `len`
+// off-diagonals (the least power of two, up to 64).
+constexpr int kDefaultLaneEntries = 4;
+constexpr int default_lanes(int len) {
+  int g = 1;
+  while (g < 64 && (len + g - 1) / g > kDefaultLaneEntries) g *= 2;
+  return g;
+}
+// Positions that HostPlan::near_lane is counted on: every near_step(n)-th, so
+// that it costs nothing on large triangles.
+constexpr int near_step(int n) { return n >> 16 > 1 ? n >> 16 : 1; }
+
 // Level-ordered layout of one triangle, as the solve kernels read it.
 //   pos_row[k]  row (x index) solved at position k; positions run level by
 //               level (pos_ilev), inside a level grouped by the bit length of
@@ -70,6 +82,9 @@ struct HostPlan {
   std::vector<int> pos_row, pos_ilev;
   std::vector<int> off_ptr, off_col, off_pos, off_src, diag_src;
   int max_row_len = 0;            // max off-diagonal count of a row
+  double near_lane = 0;           // entries one level up, per lane of the default lane rule:
+                                  // how much of what a row waits for comes at once (0 where
+                                  // no row takes several lanes)
 };
 
 // Builds the plan of the triangle (row_ptr, col); src maps an entry to its

@@ -344,6 +344,34 @@ __global__ void __launch_bounds__(256) k_offdiag(int n, int unit, const int* __r
   }
 }
 
+// Entries one level up, and lanes, of every `step`-th position (see near_step):
+// counts[0], counts[1].
+__global__ void __launch_bounds__(256)
+k_near(int n, int step, const int* __restrict__ pos_row, const int* __restrict__ level,
+       const int* __restrict__ off_ptr, const int* __restrict__ off_col, int* counts) {
+  __shared__ int wave[2][4];
+  int near = 0, lanes = 0;
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x * step;
+  for (int64_t k = (static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x) * step; k < n; k += stride) {
+    const int lev = level[pos_row[k]], e0 = off_ptr[k], e1 = off_ptr[k + 1];
+    for (int e = e0; e < e1; ++e) near += level[off_col[e]] == lev - 1;
+    lanes += default_lanes(e1 - e0);
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    near += __shfl_xor(near, o, 64);
+    lanes += __shfl_xor(lanes, o, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    wave[0][threadIdx.x >> 6] = near;
+    wave[1][threadIdx.x >> 6] = lanes;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    const int* w = wave[threadIdx.x];
+    atomicAdd(counts + threadIdx.x, w[0] + w[1] + w[2] + w[3]);
+  }
+}
+
 inline int blocks(int64_t work) {
   int64_t b = (work + 255) / 256;
   if (b < 1) b = 1;
@@ -552,10 +580,11 @@ int device_analysis(int n, int64_t nnz, const int* row_ptr, const int* col, bool
     }
     out.spare = at;
   }
-  // [0] flags, [1] max row length, [2] max level, [3] chunk ticket, [4] grid levels differ
-  DALLOC(tp.flags, 5);
-  const int init[5] = {0, 0, -1, 0, 0};
-  int got[5] = {0, 0, -1, 0, 1};
+  // [0] flags, [1] max row length, [2] max level, [3] chunk ticket, [4] grid levels
+  // differ, [5] and [6] k_near's counts
+  DALLOC(tp.flags, 7);
+  const int init[7] = {0, 0, -1, 0, 0, 0, 0};
+  int got[7] = {0, 0, -1, 0, 1, 0, 0};
   DCHK(hipMemcpyAsync(tp.flags, init, sizeof(init), hipMemcpyHostToDevice, s));
   k_check<<<std::min(blocks(n), kCheckBlocks), 256, 0, s>>>(n, nnz, row_ptr, col, upper, unit_diag,
                                                             out.depcnt, tp.flags, tp.flags + 1);
@@ -582,6 +611,7 @@ int device_analysis(int n, int64_t nnz, const int* row_ptr, const int* col, bool
     if (!got[4]) break;
   }
   if (got[4]) {
+    got[4] = 1;
     DCHK(hipMemcpyAsync(tp.flags + 2, init + 2, 3 * sizeof(int), hipMemcpyHostToDevice, s));
     k_fill_int<<<blocks(n), 256, 0, s>>>(out.level, n, -1);
     DCHK(hipGetLastError());
@@ -599,7 +629,7 @@ int device_analysis(int n, int64_t nnz, const int* row_ptr, const int* col, bool
     k_levels<<<grid, 64, 0, s>>>(n, row_ptr, col, upper ? 1 : 0, out.level, tp.flags,
                                  tp.flags + 2, tp.flags + 3, 1 << 24);
     DCHK(hipGetLastError());
-    DCHK(hipMemcpyAsync(got, tp.flags, sizeof(got), hipMemcpyDeviceToHost, s));
+    DCHK(hipMemcpyAsync(got, tp.flags, 3 * sizeof(int), hipMemcpyDeviceToHost, s));
     DCHK(hipStreamSynchronize(s));
     if (got[0] & kFlagTimeout) {
       free_device_analysis(out);
@@ -650,8 +680,17 @@ int device_analysis(int n, int64_t nnz, const int* row_ptr, const int* col, bool
   DCHK(hipMemcpyAsync(out.ilev.data(), ilev, (static_cast<size_t>(nlev) + 1) * sizeof(int),
                       hipMemcpyDeviceToHost, s));
   DCHK(hipMemcpyAsync(&noff, out.off_ptr + n, sizeof(int), hipMemcpyDeviceToHost, s));
+  // (a grid without gaps has few entries one level up: 3 of the 27-point stencil's 13)
+  const bool near = max_len > kDefaultLaneEntries && got[4];
+  if (near) {
+    k_near<<<std::min(blocks(n / near_step(n) + 1), 256), 256, 0, s>>>(
+        n, near_step(n), out.pos_row, out.level, out.off_ptr, out.off_col, tp.flags + 5);
+    DCHK(hipGetLastError());
+    DCHK(hipMemcpyAsync(got, tp.flags, sizeof(got), hipMemcpyDeviceToHost, s));
+  }
   DCHK(hipStreamSynchronize(s));
   out.noff = noff;
+  if (near) out.near_lane = static_cast<double>(got[5]) / got[6];
   return kOk;
 }
 

@@ -663,10 +663,6 @@ ChunkEntry* get_col_chunks(PlanState& ps, int group, int epl, int ncols, const C
 int ensure_xp(sptrsv_handle_t h, int64_t elems);
 int strip_occupancy(sptrsv_handle_t h, const PlanState& ps, int nrhs);
 
-// Entries per lane of the default lane rule, the one the strip-ordered copy is built
-// for.
-constexpr int kStripLaneEntries = 4;
-
 // Option bits of set_mask: options set explicitly, which the pattern-based
 // defaults of resolve() leave alone.
 constexpr unsigned kSetGrid = 1, kSetAssign = 2, kSetStride = 4;
@@ -687,7 +683,7 @@ int widest_level(sptrsv_handle_t h) {
 // solve: it computes the sums of the default lane rule, with one-wavefront
 // workgroups.
 bool strip_rule(sptrsv_handle_t h) {
-  return h->fwd.strips.nstrips > 0 && h->group == 0 && h->epl == kStripLaneEntries && h->wg == 64 &&
+  return h->fwd.strips.nstrips > 0 && h->group == 0 && h->epl == kDefaultLaneEntries && h->wg == 64 &&
          (h->algo == SPTRSV_ALGO_AUTO || h->algo == SPTRSV_ALGO_SELF);
 }
 
@@ -745,16 +741,26 @@ Config resolve(sptrsv_handle_t h) {
   return c;
 }
 
-// Whether the static schedules publish each row of a chunk as soon as it is
-// ready: with overlapped polling, in triangles whose longer rows take several
-// lanes.  There most dependencies are ready before a chunk is reached and the
-// last ones come one at a time (row-wise, us per solve, whole chunks against
-// row by row: power-law 1M rows 738 / 604, its transpose in FP32 of 777,777
-// rows 602 / 444, 128^3 27-point 2198 / 1220); with rows of at most four
-// entries most of a lane's are missing together, and asking for all of them
-// at once is faster (128^3 7-point 375 / 694, 256 2-D ILU(0) factors 571 / 727).
-int publish_early(const PlanState& ps, const Config& c) {
-  return c.poll != 0 && c.group != 1 && ps.h.max_row_len > 4 ? 1 : 0;
+// Whether a static schedule over `waves` wavefronts and `chunks` chunks publishes
+// each row of a chunk as soon as it is ready: with overlapped polling, in
+// triangles whose longer rows take several lanes, where most dependencies are
+// ready before a chunk is reached and the last ones come one at a time (row-wise,
+// us per solve, whole chunks against row by row: power-law 1M rows 738 / 604, its
+// transpose in FP32 of 777,777 rows 602 / 444, 128^3 27-point 2198 / 1220; a third
+// to a half of an entry per lane one level up, 27-point three quarters).  Where a
+// lane's entries are missing together, asking for all of them at once is faster:
+// always in rows of at most four entries (128^3 7-point 375 / 694, 256 2-D ILU(0)
+// factors 571 / 727), and by how many entries of a lane are one level up
+// otherwise.  Layers of 5,000 rows, 1, 2, 4 such entries per lane, rows of 8 in
+// two lanes: 303 / 326, 335 / 453, 378 / 740; rows of 16 in four: 567 / 548,
+// 608 / 675, 613 / 841.  Twice the wavefronts (layers of 10,000) wait less each:
+// 1, 2, 3, 4 per lane 268 / 211, 319 / 283, 347 / 368, 370 / 449; so do
+// wavefronts with several chunks a level (rows of 40 in sixteen lanes, 2.5 per
+// lane: 1494 / 1414).
+int publish_early(sptrsv_handle_t h, const PlanState& ps, const Config& c, int waves, int chunks) {
+  if (c.poll == 0 || c.group == 1 || ps.h.max_row_len <= kDefaultLaneEntries) return 0;
+  const bool more = waves >= 2 * h->num_cu || chunks > 2ll * waves * ps.h.nlev;
+  return ps.h.near_lane <= (more ? 2.5 : 1.0) ? 1 : 0;
 }
 
 // Schedule of a solve with nrhs > 1 right-hand sides: sptrsv_tune_multi's
@@ -889,9 +895,9 @@ int build_strip_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t 
   if (grids.empty()) return kOk;
   int st = kOk;
   unsigned char* lanes = nullptr;
-  if (ps.h.max_row_len > kStripLaneEntries) {
+  if (ps.h.max_row_len > kDefaultLaneEntries) {
     // rows of several lanes: their sums are split the same way here
-    ChunkEntry* ch = get_chunks(h, ps, 0, kStripLaneEntries, 0, 1, &st);
+    ChunkEntry* ch = get_chunks(h, ps, 0, kDefaultLaneEntries, 0, 1, &st);
     if (ch) lanes = dalloc<unsigned char>(static_cast<size_t>(h->n), &st);
     if (lanes && launch_strip_lanes(ch->d, lanes, s) != hipSuccess) st = kErrHip;
   }
@@ -1328,7 +1334,6 @@ int solve_impl(sptrsv_handle_t h, PlanState& ps, const Config& c_in, const void*
   a.ld = ld;
   a.spin_limit = h->spin_limit;
   a.poll = c.poll;
-  a.early = publish_early(ps, c);
   a.xp_stride = stride;
   a.res_limit = h->res_limit;
   a.coop = h->coop;
@@ -1405,6 +1410,7 @@ int solve_impl(sptrsv_handle_t h, PlanState& ps, const Config& c_in, const void*
   a.grid = persistent_grid(h, use_static ? multi_kind(multi ? mrows : 0) : 0, c.grid,
                            ch->d.count);
   if (use_static) {
+    a.early = publish_early(h, ps, c, a.grid * (h->wg / 64), ch->d.count);
     const WaveLists* wl = static_lists(h, *ch, c, &err, multi ? mrows : 0);
     if (!wl) return err;
     a.wave_ptr = wl->ptr;
@@ -1492,7 +1498,6 @@ int solve_columns(sptrsv_handle_t h, PlanState& ps, const Config& c_in, const vo
   a.ld = ld;
   a.spin_limit = h->spin_limit;
   a.poll = c.poll;
-  a.early = publish_early(ps, c);
   a.xp_stride = c.stride;
   a.xp_col = col_elems;
   a.res_limit = h->res_limit;
@@ -1501,6 +1506,7 @@ int solve_columns(sptrsv_handle_t h, PlanState& ps, const Config& c_in, const vo
   a.grid = persistent_grid(h, 3, c.grid, ch->d.count);
   const int W = a.grid * (h->wg / 64);
   const int wpb = h->wg / 64;
+  a.early = publish_early(h, ps, c, W, ch->d.count);
   const WaveLists* wl = get_wave_lists(
       *ch, W, (c.assign == SPTRSV_ASSIGN_XCD && W % (8 * wpb) == 0) ? 8 : 1, wpb, &err);
   if (!wl) return err;
@@ -1652,6 +1658,7 @@ void install_device_plan(sptrsv_handle_t h, PlanState& ps, DeviceAnalysis& da, b
   p.ilev = std::move(da.ilev);
   p.pos_ilev = p.ilev;
   p.max_row_len = da.max_row_len;
+  p.near_lane = da.near_lane;
   DevPlan& d = ps.d;
   d = DevPlan();
   d.n = h->n;

@@ -263,8 +263,8 @@ template <typename T> hipError_t launch_self_value(const SolveArgs&, hipStream_t
 template <typename T> hipError_t launch_self_flag(const SolveArgs&, hipStream_t) {
   return note("flag");
 }
-template <typename T> hipError_t launch_self_static(const SolveArgs&, hipStream_t) {
-  return note("static");
+template <typename T> hipError_t launch_self_static(const SolveArgs& a, hipStream_t) {
+  return note(a.nrhs == 1 && a.early ? "static_by_row" : "static");
 }
 template <typename T>
 hipError_t launch_block(const SolveArgs&, const int*, const int*, const int*, int, int, int,

@@ -296,3 +296,29 @@ def test_batches_of_many_small_systems(m):
     assert form(8, 1200, 1) != "strips" and form(3, 1000, 1) != "strips"
     assert form(16, 300, 16) != "strips"
     assert form(32, 64, 1) == "strips" and form(32, 64, 8) == "strips"
+
+
+def _layers(n, layers, near, far):
+    """Rows with `near` entries in the layer above and `far` in those three and
+    more up, at random."""
+    w = n // layers
+    rng = np.random.Generator(np.random.PCG64(2))
+    i = np.arange(w, n, dtype=np.int64)
+    pairs = [(i, (i // w - 1) * w + rng.integers(0, w, i.size)) for _ in range(near)]
+    k = i[i >= 4 * w]
+    pairs += [(k, (k // w - 3) * w - 1 - rng.integers(0, w, k.size)) for _ in range(far)]
+    return _rows(n, pairs)
+
+
+def test_rows_published_one_by_one_where_they_wait_for_little(m):
+    """The static row-wise schedule publishes by row where few entries of a lane
+    are one level up, and by chunk where most are."""
+    for T, want in ((_layers(20000, 20, 8, 0), "static"), (_layers(20000, 20, 16, 0), "static"),
+                    (_layers(20000, 20, 1, 7), "static_by_row"), (_layers(30000, 20, 2, 14), "static_by_row"),
+                    (_layers(100000, 11, 4, 4), "static_by_row"),     # two wavefronts per CU
+                    (W.powerlaw_lower(20000, 3, window=2000), "static_by_row"),
+                    (W.stencil_triangle((20, 20, 20), 27), "static_by_row"),
+                    (W.laplacian_triangle((30, 30, 30)), "static")):
+        h = Model(m, T).set(algo=2, assign=0)
+        assert h.form() == want
+        assert h.set(poll=0).form() == "static"
