@@ -67,6 +67,8 @@ struct PlanState {
   PushState push;
   DevStrips strips;               // strip-ordered copy (strips.hpp), if the rows sit on a grid
   SolveCost strip_cost;           // and what a solve in strips costs
+  bool strips_stale = false;      // its values are older than the plan's
+  bool strips_captured = false;   // some graph solves in strips: they must be current
   void* vals_buf = nullptr;       // [noff + 2n] values: off-diagonals, diagonal, 1/diagonal
   // (group, epl, rows_fixed, rows_per_lane)
   std::map<std::tuple<int, int, int, int>, ChunkEntry> chunks;
@@ -324,6 +326,7 @@ void free_plan(PlanState& ps) {
   ps.mem = DevBlock();
   free_push(ps.push);
   free_strips(ps.strips);
+  ps.strips_stale = ps.strips_captured = false;
   ps.d = DevPlan();
   ps.vals_buf = nullptr;
   ps.a_level = ps.a_depcnt = ps.a_jlev = nullptr;
@@ -661,6 +664,7 @@ ChunkEntry* get_col_chunks(PlanState& ps, int group, int epl, int ncols, const C
 }
 
 int ensure_xp(sptrsv_handle_t h, int64_t elems);
+int gather_strips(sptrsv_handle_t h, const PlanState& ps, hipStream_t s);
 int strip_occupancy(sptrsv_handle_t h, const PlanState& ps, int nrhs);
 
 // Option bits of set_mask: options set explicitly, which the pattern-based
@@ -739,6 +743,19 @@ Config resolve(sptrsv_handle_t h) {
   if (!(h->set_mask & kSetStride) && long_rows) c.stride = 32 / h->vb;
   c.strip = strip_rule(h) && !h->set_mask && c.poll == 1 && c.rpl == 1;
   return c;
+}
+
+// Whether a solve with schedule c is one in strips, memory permitting (the
+// tasks and their dump slots are counted in 32 bits): a triangle on a grid can
+// have far fewer levels than its strips have steps, where entries are missing
+// or the rows along a line do not depend on one another.
+bool takes_strips(const PlanState& ps, const Config& c, int nrhs) {
+  const int64_t tasks = static_cast<int64_t>(ps.strips.nstrips) * nrhs;
+  return c.strip && tasks > 0 && tasks < INT32_MAX / kDumpSlot &&
+         (c.strip == 2 ||
+          strip_time(ps.strip_cost, nrhs) <
+              row_time(ps.h.n, ps.h.noff, ps.h.nlev, ps.h.max_row_len,
+                       c.algo == SPTRSV_ALGO_BLOCK && nrhs == 1, nrhs));
 }
 
 // Whether a static schedule over `waves` wavefronts and `chunks` chunks publishes
@@ -913,9 +930,7 @@ int build_strip_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t 
       continue;
     }
     ps.strip_cost = costs[q];
-    if (!st && (h->dtype == SPTRSV_F64 ? launch_strip_gather<double>(ps.d, ps.strips, s)
-                                       : launch_strip_gather<float>(ps.d, ps.strips, s)) != hipSuccess)
-      st = kErrHip;
+    if (!st) st = gather_strips(h, ps, s);
     if (!st) st = ensure_xp(h, std::max<int64_t>(h->n, strip_values(ps.strips, 1)));
     if (!st && hipStreamSynchronize(s) != hipSuccess) st = kErrHip;
     if (!st) (void)strip_occupancy(h, ps, 1);
@@ -1146,13 +1161,24 @@ int regather_push(sptrsv_handle_t h, hipStream_t s) {
   return kOk;
 }
 
-// Re-gathers the strip-ordered copies after a value update.
-int regather_strips(sptrsv_handle_t h, hipStream_t s) {
+int gather_strips(sptrsv_handle_t h, const PlanState& ps, hipStream_t s) {
+  const hipError_t e = h->dtype == SPTRSV_F64 ? launch_strip_gather<double>(ps.d, ps.strips, s)
+                                              : launch_strip_gather<float>(ps.d, ps.strips, s);
+  return e == hipSuccess ? kOk : kErrHip;
+}
+
+// Re-gathers the strip-ordered copies after a value update; where a solve of one
+// column takes another form, not before a solve needs them.
+int regather_strips(sptrsv_handle_t h, hipStream_t s, bool capturing) {
+  const Config c = resolve(h);
   for (PlanState* ps : {&h->fwd, &h->trn}) {
     if (!ps->strips.nstrips) continue;
-    const hipError_t e = h->dtype == SPTRSV_F64 ? launch_strip_gather<double>(ps->d, ps->strips, s)
-                                                : launch_strip_gather<float>(ps->d, ps->strips, s);
-    if (e != hipSuccess) return kErrHip;
+    if (takes_strips(*ps, c, 1) || capturing || ps->strips_captured) {
+      if (const int st = gather_strips(h, *ps, s)) return st;
+      if (!capturing) ps->strips_stale = false;   // else whenever the graph runs
+    } else {
+      ps->strips_stale = true;
+    }
   }
   return kOk;
 }
@@ -1224,6 +1250,14 @@ int solve_column(sptrsv_handle_t h, PlanState& ps, const Config& c, const void* 
 template <typename T>
 int solve_strips(sptrsv_handle_t h, PlanState& ps, const void* b, void* x, int nrhs, int ld,
                  void* xp, hipStream_t s, const SolveExt& ext) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess) return kErrHip;
+  const bool capturing = cap != hipStreamCaptureStatusNone;
+  ps.strips_captured |= capturing;
+  if (ps.strips_stale) {
+    if (const int st = gather_strips(h, ps, s)) return st;
+    ps.strips_stale = capturing;
+  }
   StripSolveArgs a;
   a.strips = &ps.strips;
   a.scratch = h->scratch;
@@ -1243,19 +1277,6 @@ int solve_strips(sptrsv_handle_t h, PlanState& ps, const void* b, void* x, int n
   if (launch_strip_solve<T>(a, s) != hipSuccess) return kErrHip;
   timing_end(s, stop);
   return kOk;
-}
-
-// Whether a solve with schedule c is one in strips, memory permitting (the
-// tasks and their dump slots are counted in 32 bits): a triangle on a grid can
-// have far fewer levels than its strips have steps, where entries are missing
-// or the rows along a line do not depend on one another.
-bool takes_strips(const PlanState& ps, const Config& c, int nrhs) {
-  const int64_t tasks = static_cast<int64_t>(ps.strips.nstrips) * nrhs;
-  return c.strip && tasks > 0 && tasks < INT32_MAX / kDumpSlot &&
-         (c.strip == 2 ||
-          strip_time(ps.strip_cost, nrhs) <
-              row_time(ps.h.n, ps.h.noff, ps.h.nlev, ps.h.max_row_len,
-                       c.algo == SPTRSV_ALGO_BLOCK && nrhs == 1, nrhs));
 }
 
 template <typename T>
@@ -1998,7 +2019,7 @@ int sptrsv_update_values(sptrsv_handle_t h, const void* vals, hipStream_t stream
   if (!st && h->blk[0].built) st = gather(h, h->blk[0].ps, h->fwd.vals_buf, stream);
   if (!st && h->blk[1].built) st = gather(h, h->blk[1].ps, h->trn.vals_buf, stream);
   if (!st) st = regather_push(h, stream);
-  if (!st) st = regather_strips(h, stream);
+  if (!st) st = regather_strips(h, stream, capturing);
   h->last_stream = stream;
   const int st2 = order_end(h, stream, capturing);
   return st ? st : st2;
@@ -2025,7 +2046,7 @@ int sptrsv_update_values_batched(sptrsv_handle_t h, const void* const* vals, hip
   if (!st && h->blk[0].built) st = gather(h, h->blk[0].ps, h->fwd.vals_buf, stream);
   if (!st && h->blk[1].built) st = gather(h, h->blk[1].ps, h->trn.vals_buf, stream);
   if (!st) st = regather_push(h, stream);
-  if (!st) st = regather_strips(h, stream);
+  if (!st) st = regather_strips(h, stream, capturing);
   h->last_stream = stream;
   const int st2 = order_end(h, stream, capturing);
   return st ? st : st2;

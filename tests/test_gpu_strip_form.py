@@ -130,3 +130,39 @@ def test_set_up_of_small_systems_beside_a_long_chain(sp):
         assert bits_equal(x[256 * k:256 * (k + 1)], one.solve(b[256 * k:256 * (k + 1)].clone()))
     assert bits_equal(x[5000 * 256:], long.solve(b[5000 * 256:].clone()))
     assert min(times) < 20, times                        # measured 12; 41 before
+
+
+def test_values_updated_while_another_form_is_chosen(sp):
+    """A solve in strips after updates that ran under another form, eagerly and
+    from a graph, reads the newest values."""
+    T = W.laplacian_triangle((31, 17, 12))
+    d, b = dev_tri(T), dev(W.uniform_vector(T.n, 9))
+    h, ref = sp.Handle(*d), sp.Handle(*d).configure(algo=2, assign=0)
+    h.prepare_transpose()
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        y = torch.empty_like(b)
+        for k in range(3):
+            v = d[2] * (1.0 + 0.25 * k)
+            h.configure(algo=1)
+            h.update_values(v)
+            ref.update_values(v)
+            assert bits_equal(h.solve(b), ref.solve(b))
+            h.configure(algo=0)
+            assert h.strips()["strips"] and h.strips(transpose=True)["strips"]
+            assert bits_equal(h.solve_t(b), ref.solve_t(b)) and bits_equal(h.solve(b), ref.solve(b))
+        h.configure(algo=1)
+        h.update_values(d[2])
+        h.configure(algo=0)
+        g = h.capture(b, y, stream=s)                    # captured while the copy is old
+        for k in range(3):
+            v = d[2] * (2.0 + k)
+            h.configure(algo=1)
+            h.update_values(v)
+            ref.update_values(v)
+            g.launch(s)
+            s.synchronize()
+            assert bits_equal(y, ref.solve(b))
+            h.configure(algo=0)
+            assert bits_equal(h.solve(b), ref.solve(b))
+        h.status()

@@ -79,6 +79,12 @@ class Model:
         return self.m.sptrsv_solve_multi(self.h, I32(nrhs), I32(self.n), self.p(self.b),
                                          self.p(self.x), int(t), None)
 
+    def update(self):
+        """The launches of a value update."""
+        self.m.log()
+        assert self.m.sptrsv_update_values(self.h, self.p(self.v), None) == 0
+        return self.m.log()
+
     def tune(self, nrhs=1):
         y = np.zeros(self.n * nrhs)
         if nrhs > 1:
@@ -322,3 +328,40 @@ def test_rows_published_one_by_one_where_they_wait_for_little(m):
         h = Model(m, T).set(algo=2, assign=0)
         assert h.form() == want
         assert h.set(poll=0).form() == "static"
+
+
+def test_value_updates_follow_the_form_that_is_used(m):
+    """New values go to the strip-ordered copies where solves read them: at
+    once, or with the first solve that needs them; a captured solve or update
+    always finds them current."""
+    T = W.laplacian_triangle((64, 64))
+    h = Model(m, T)
+    assert h.solve(t=True) == 0
+    assert h.update()[-2:] == ["strip_gather", "strip_gather"]
+    h.set(algo=1)
+    assert "strip_gather" not in h.update()
+    h.set(algo=0)
+    m.log()
+    assert h.solve() == 0 and m.log() == ["strip_gather", "fill", "strips"]
+    assert h.solve() == 0 and m.log() == ["fill", "strips"]
+    assert h.solve(t=True) == 0 and m.log() == ["strip_gather", "fill", "strips"]
+    h.set(algo=1)
+    assert "strip_gather" not in h.update()
+    m.model_capture(1)
+    assert h.update().count("strip_gather") == 2       # the graph's
+    m.model_capture(0)
+    h.set(algo=0)
+    m.log()
+    assert h.solve() == 0 and m.log()[0] == "strip_gather"      # the graph has not run
+    h.set(algo=1)
+    assert "strip_gather" not in h.update()
+    h.set(algo=0)
+    m.log()
+    m.model_capture(1)
+    assert h.solve() == 0 and m.log()[0] == "strip_gather"
+    m.model_capture(0)
+    h.set(algo=1)
+    assert h.update().count("strip_gather") == 1       # that graph's copy stays current
+    h.set(algo=0)
+    m.log()
+    assert h.solve() == 0 and m.log() == ["fill", "strips"]
