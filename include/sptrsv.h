@@ -49,8 +49,11 @@
  *     capture of the caller's own may hold its address.
  *   - Device memory: blocks of 1 MiB and more that a call frees are kept
  *     for the next handle, at most 1 GiB over all devices; all of it goes
- *     back when an allocation fails, and a block that 64 later frees have
- *     passed over goes back by itself.
+ *     back when an allocation of the library fails and by
+ *     sptrsv_release_memory, and a block that 64 later frees have passed
+ *     over goes back by itself.  Other allocators of the process do not reach
+ *     it: call sptrsv_release_memory where they run out.  Before
+ *     hipDeviceReset, destroy the handles and call it too.
  *   - n = 0 is valid and every solve on it is a no-op.
  *   - Dependencies are taken from the pattern (Sec. 4.4): an explicitly
  *     stored zero off-diagonal still counts as a dependency.
@@ -482,6 +485,11 @@ const char *sptrsv_status_string(int status);
  * finished.  Returns SPTRSV_ERR_BUSY, and frees nothing, while graphs
  * captured from the handle are alive: their kernels use its buffers. */
 int sptrsv_destroy(sptrsv_handle_t h);
+
+/* Gives the device memory kept from destroyed handles back to the driver (see
+ * "Device memory" above).  Handles in use are not touched.  Waits for the
+ * devices that hold it.  Any thread. */
+int sptrsv_release_memory(void);
 
 /* ---------------------------------------------------------------------- */
 /* HIP graph of one solve (or transposed solve) on fixed b/x pointers:

@@ -21,7 +21,7 @@ import torch
 from . import _lib as L
 from ._lib import SpTRSVError, check, lib
 
-__all__ = ["Handle", "BatchedHandle", "SpTRSVFunction", "sptrsv", "SpTRSVError",
+__all__ = ["Handle", "BatchedHandle", "SpTRSVFunction", "sptrsv", "SpTRSVError", "release_memory",
            "ALGO_AUTO", "ALGO_LEVEL", "ALGO_SELF", "SYNC_VALUE", "SYNC_FLAG"]
 
 ALGO_AUTO, ALGO_LEVEL, ALGO_SELF, ALGO_BLOCK, ALGO_COLUMN_LEVEL, ALGO_COLUMN_SELF = 0, 1, 2, 3, 4, 5
@@ -256,6 +256,12 @@ def probe_hop(same_xcd=False, iters=2000):
     ns = ctypes.c_double()
     check(lib.sptrsv_probe_hop(int(bool(same_xcd)), int(iters), ctypes.byref(ns)))
     return ns.value
+
+
+def release_memory():
+    """Gives the device memory kept from destroyed handles (at most 1 GiB) back to
+    the driver, for other allocators of the process."""
+    check(lib.sptrsv_release_memory())
 
 
 class Handle(_Base):

@@ -74,6 +74,7 @@ SIGNATURES = {
     "sptrsv_kernel_time": (_int, [_v, ctypes.POINTER(ctypes.c_double), _pi64, _int]),
     "sptrsv_status_string": (ctypes.c_char_p, [_int]),
     "sptrsv_destroy": (_int, [_v]),
+    "sptrsv_release_memory": (_int, []),
     "sptrsv_graph_capture": (_int, [_v, _v, _v, _int, _v, _pv]),
     "sptrsv_graph_launch": (_int, [_v, _v]),
     "sptrsv_graph_destroy": (_int, [_v]),

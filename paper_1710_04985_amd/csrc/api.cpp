@@ -2546,6 +2546,11 @@ int sptrsv_destroy(sptrsv_handle_t h) {
   return kOk;
 }
 
+int sptrsv_release_memory(void) {
+  dev_release();
+  return kOk;
+}
+
 int sptrsv_graph_capture(sptrsv_handle_t h, const void* b, void* x, int transpose,
                          hipStream_t stream, sptrsv_graph_t* out) {
   if (!h || !out || !stream) return kErrInvalidArg;

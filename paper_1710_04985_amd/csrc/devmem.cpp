@@ -4,8 +4,8 @@
 // one back (128^3 7-point: blocks of 131 and 267 MB).
 //
 // The store is bounded (kKeepBytes over all devices; the block freed longest
-// ago goes first), gives everything back when an allocation fails, and gives
-// back a block that kKeepFrees later ones have passed over.  A block enters it
+// ago goes first), gives everything back when an allocation fails or the caller
+// asks for it, and gives back a block that kKeepFrees later ones have passed over.  A block enters it
 // only when its device is idle, so the next owner may use it on any stream.
 #include "devmem.hpp"
 
@@ -13,6 +13,7 @@
 #include <list>
 #include <map>
 #include <mutex>
+#include <vector>
 
 namespace sptrsv {
 namespace {
@@ -37,20 +38,34 @@ hipError_t settled(hipError_t e) {
 }
 
 struct Store {
-  std::mutex mu;
+  std::mutex mu;                             // the lists; not held over calls that may wait
+  std::mutex emptying;                       // held while blocks go back for want of memory
   std::map<void*, Block> live;               // large blocks in use
   std::list<Block> kept;                     // oldest first
   int64_t kept_bytes = 0, frees = 0;
 
-  // Hands back the oldest blocks until `bytes` remain, and those passed over.
-  void trim(int64_t bytes) {
+  // Takes out the oldest blocks until `bytes` remain, and those passed over.
+  std::vector<void*> trim(int64_t bytes) {
+    std::vector<void*> out;
     while (!kept.empty() && (kept_bytes > bytes || frees - kept.front().freed > kKeepFrees)) {
-      (void)settled(hipFree(kept.front().p));
+      out.push_back(kept.front().p);
       kept_bytes -= kept.front().bytes;
       kept.pop_front();
     }
+    return out;
+  }
+
+  std::vector<void*> trim_all() {
+    std::lock_guard<std::mutex> lock(mu);
+    return trim(0);
   }
 };
+
+// A free waits for the block's device, for as long as its work takes: other
+// threads' allocations are not to wait with it.
+void give_back(const std::vector<void*>& blocks) {
+  for (void* p : blocks) (void)settled(hipFree(p));
+}
 
 // Waits for all work on the current device.  By a free, which does so, and not
 // by hipDeviceSynchronize: that breaks the graph capture of another stream also
@@ -68,43 +83,63 @@ Store& store() {
 
 }  // namespace
 
+namespace {
+
+// hipMalloc; without memory for it, again after the store has been emptied
+// (also by another thread, which may still be at it).
+hipError_t device_malloc(void** p, int64_t bytes) {
+  const hipError_t e = settled(hipMalloc(p, static_cast<size_t>(bytes)));
+  if (e != hipErrorOutOfMemory) return e;
+  Store& s = store();
+  std::lock_guard<std::mutex> one(s.emptying);
+  give_back(s.trim_all());
+  return settled(hipMalloc(p, static_cast<size_t>(bytes)));
+}
+
+// Whether a kept block is still an allocation of its own: a reset of its device
+// takes it away.
+bool still_there(const Block& b) {
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  return settled(hipMemGetAddressRange(&base, &size, b.p)) == hipSuccess && base == b.p &&
+         static_cast<int64_t>(size) >= b.bytes;
+}
+
+}  // namespace
+
 hipError_t dev_alloc(void** p, int64_t bytes) {
   *p = nullptr;
   if (bytes < 1) bytes = 1;
-  if (bytes < kLarge) {
-    const hipError_t e = settled(hipMalloc(p, static_cast<size_t>(bytes)));
-    if (e == hipSuccess) return e;
-    Store& s = store();
-    std::lock_guard<std::mutex> lock(s.mu);
-    if (s.kept.empty()) return e;
-    s.trim(0);
-    return settled(hipMalloc(p, static_cast<size_t>(bytes)));
-  }
+  if (bytes < kLarge) return device_malloc(p, bytes);
   int device = 0;
   if (const hipError_t e = settled(hipGetDevice(&device))) return e;
   constexpr int64_t kUnit = 2 << 20;
   bytes = (bytes + kUnit - 1) / kUnit * kUnit;
   Store& s = store();
-  std::lock_guard<std::mutex> lock(s.mu);
-  // the smallest block that fits, if at most a quarter of it would lie idle
-  auto best = s.kept.end();
-  for (auto it = s.kept.begin(); it != s.kept.end(); ++it)
-    if (it->device == device && it->bytes >= bytes && it->bytes - bytes <= it->bytes / 4 &&
-        (best == s.kept.end() || it->bytes < best->bytes))
-      best = it;
-  if (best != s.kept.end()) {
-    *p = best->p;
-    s.kept_bytes -= best->bytes;
-    s.live[best->p] = *best;
-    s.kept.erase(best);
-    return hipSuccess;
+  {
+    std::lock_guard<std::mutex> lock(s.mu);
+    for (;;) {
+      // the smallest block that fits, if at most a quarter of it would lie idle
+      auto best = s.kept.end();
+      for (auto it = s.kept.begin(); it != s.kept.end(); ++it)
+        if (it->device == device && it->bytes >= bytes && it->bytes - bytes <= it->bytes / 4 &&
+            (best == s.kept.end() || it->bytes < best->bytes))
+          best = it;
+      if (best == s.kept.end()) break;
+      const Block b = *best;
+      s.kept_bytes -= b.bytes;
+      s.kept.erase(best);
+      if (!still_there(b)) continue;
+      *p = b.p;
+      s.live[b.p] = b;
+      return hipSuccess;
+    }
   }
-  hipError_t e = settled(hipMalloc(p, static_cast<size_t>(bytes)));
-  if (e != hipSuccess && !s.kept.empty()) {
-    s.trim(0);
-    e = settled(hipMalloc(p, static_cast<size_t>(bytes)));
+  const hipError_t e = device_malloc(p, bytes);
+  if (e == hipSuccess) {
+    std::lock_guard<std::mutex> lock(s.mu);
+    s.live[*p] = Block{*p, bytes, device, 0};
   }
-  if (e == hipSuccess) s.live[*p] = Block{*p, bytes, device, 0};
   return e;
 }
 
@@ -132,11 +167,17 @@ void dev_free(void* p) {
     (void)settled(hipFree(p));
     return;
   }
-  std::lock_guard<std::mutex> lock(s.mu);
-  b.freed = ++s.frees;
-  s.kept.push_back(b);
-  s.kept_bytes += b.bytes;
-  s.trim(kKeepBytes);
+  std::vector<void*> back;
+  {
+    std::lock_guard<std::mutex> lock(s.mu);
+    b.freed = ++s.frees;
+    s.kept.push_back(b);
+    s.kept_bytes += b.bytes;
+    back = s.trim(kKeepBytes);
+  }
+  give_back(back);
 }
+
+void dev_release() { give_back(store().trim_all()); }
 
 }  // namespace sptrsv

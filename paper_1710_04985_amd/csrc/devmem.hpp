@@ -16,4 +16,7 @@ hipError_t dev_alloc(void** p, int64_t bytes);
 // hipFree waits).  Large blocks go to the store.  Safe from any thread.
 void dev_free(void* p);
 
+// Gives back all that the store keeps.  Safe from any thread.
+void dev_release();
+
 }  // namespace sptrsv

@@ -5,8 +5,10 @@
 // leaves allocated and what error it leaves behind.
 #include <hip/hip_runtime_api.h>
 
+#include <chrono>
 #include <cstdlib>
 #include <cstring>
+#include <future>
 #include <map>
 #include <set>
 #include <string>
@@ -33,6 +35,9 @@ int64_t g_npub = 0;                // published values of every strip copy, 0: a
 int64_t g_strip_bytes = 1 << 16;   // size of every strip copy
 int g_strip_error = 0;             // what the construction of one reports
 void* g_xp = nullptr;              // the solution buffer filled last
+int g_probe_free = 0;              // the next free tries an allocation of another thread:
+                                   // 2 it went through meanwhile, 3 it had to wait
+std::future<void> g_other;
 int g_handles = 0;                 // events, streams and graphs are numbers
 
 hipError_t fail(hipError_t e) { return g_last = e; }
@@ -75,6 +80,15 @@ void* model_alloc(int64_t bytes) {
   return dev_alloc(&p, bytes) == hipSuccess ? p : nullptr;
 }
 void model_free(void* p) { dev_free(p); }
+void model_reset() {                // what a device reset leaves of the allocations
+  for (auto& kv : g_live) std::free(kv.first);
+  g_live.clear();
+}
+void model_probe_free() { g_probe_free = 1; }
+int model_probed() {
+  if (g_other.valid()) g_other.get();
+  return g_probe_free;
+}
 
 // -------------------------------------------------------------- the runtime
 hipError_t hipMalloc(void** p, size_t bytes) {
@@ -89,12 +103,26 @@ hipError_t hipMalloc(void** p, size_t bytes) {
 }
 hipError_t hipFree(void* p) {
   if (!p) return hipSuccess;
+  if (g_probe_free == 1 && g_live.count(p) && g_live[p] > 1000) {
+    g_probe_free = 0;
+    g_other = std::async(std::launch::async, [] { dev_free(model_alloc(1 << 20)); });
+    g_probe_free = g_other.wait_for(std::chrono::seconds(2)) == std::future_status::ready ? 2 : 3;
+  }
   if (g_capturing) return fail(hipErrorStreamCaptureUnsupported);
   auto it = g_live.find(p);
   if (it == g_live.end()) return fail(hipErrorInvalidValue);
   g_live.erase(it);
   std::free(p);
   return hipSuccess;
+}
+hipError_t hipMemGetAddressRange(hipDeviceptr_t* base, size_t* size, hipDeviceptr_t p) {
+  for (auto& kv : g_live)
+    if (p >= kv.first && p < static_cast<char*>(kv.first) + kv.second) {
+      *base = kv.first;
+      *size = kv.second;
+      return hipSuccess;
+    }
+  return fail(hipErrorNotFound);
 }
 hipError_t hipGetLastError() {
   const hipError_t e = g_last;

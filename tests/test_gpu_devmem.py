@@ -81,3 +81,19 @@ def test_handle_destroyed_beside_a_relaxed_capture(sp):
         g.replay()
         assert torch.equal(e, a * 2 + 1)
     assert bits_equal(sp.Handle(*d).solve(b), want)
+
+
+def test_kept_memory_is_given_back_on_request(sp):
+    d = dev_tri(W.laplacian_triangle((90, 90, 90)))
+    b = torch.ones(d[0].numel() - 1, dtype=torch.float64, device="cuda")
+    sp.release_memory()
+    torch.cuda.synchronize()
+    free0 = torch.cuda.mem_get_info()[0]
+    h = sp.Handle(*d, setup="device")
+    x = h.solve(b)
+    del h
+    torch.cuda.synchronize()
+    kept = free0 - torch.cuda.mem_get_info()[0]
+    sp.release_memory()
+    assert kept > (50 << 20) and free0 - torch.cuda.mem_get_info()[0] < (32 << 20)
+    assert bits_equal(sp.Handle(*d, setup="device").solve(b), x)

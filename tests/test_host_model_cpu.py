@@ -365,3 +365,50 @@ def test_value_updates_follow_the_form_that_is_used(m):
     h.set(algo=0)
     m.log()
     assert h.solve() == 0 and m.log() == ["fill", "strips"]
+
+
+def test_kept_memory_is_given_back_on_request(m):
+    h = Model(m, W.laplacian_triangle((300, 300)))
+    assert h.st == 0
+    h.destroy()
+    assert m.model_live_bytes() > 0
+    assert m.sptrsv_release_memory() == 0 and m.model_live_bytes() == 0
+    assert m.sptrsv_release_memory() == 0
+    a = m.model_alloc(3 * MB)                          # what is in use stays
+    m.model_free(m.model_alloc(5 * MB))
+    assert m.sptrsv_release_memory() == 0 and m.model_live_bytes() == 4 * MB and m.model_is_live(a)
+
+
+def test_blocks_that_a_reset_took_are_not_handed_out(m):
+    for _ in range(3):
+        m.model_free(m.model_alloc(6 * MB))
+    m.model_reset()
+    a = m.model_alloc(6 * MB)
+    assert a and m.model_is_live(a) and m.model_last_error() == 0
+
+
+def test_allocations_of_a_capture_keep_the_store(m):
+    """A refused allocation under capture is no lack of memory: nothing is taken
+    out of the store that could not be freed."""
+    m.model_free(m.model_alloc(4 * MB))
+    m.model_capture(1)
+    assert not m.model_alloc(64 * MB)
+    m.model_capture(0)
+    assert m.sptrsv_release_memory() == 0 and m.model_live_bytes() == 0
+
+
+@pytest.mark.parametrize("by", ["bound", "want", "request"])
+def test_other_threads_allocate_while_blocks_go_back(m, by):
+    """Freeing a block waits for its device; another thread's allocation does
+    not wait with it."""
+    blocks = [m.model_alloc(700 * MB), m.model_alloc(600 * MB)]
+    m.model_free(blocks[0])
+    m.model_probe_free()
+    if by == "bound":
+        m.model_free(blocks[1])
+    elif by == "want":
+        m.model_fail_next(1)
+        assert m.model_alloc(900 * MB)
+    else:
+        assert m.sptrsv_release_memory() == 0
+    assert m.model_probed() == 2
