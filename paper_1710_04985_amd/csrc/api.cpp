@@ -457,7 +457,9 @@ int read_status(sptrsv_handle_t h, hipStream_t s, bool clear) {
 void install_device_plan(sptrsv_handle_t h, PlanState& ps, DeviceAnalysis& da, bool upper);
 int64_t values_bytes(sptrsv_handle_t h);
 std::vector<std::vector<StripGrid>> grid_guesses(sptrsv_handle_t h, bool upper);
-int build_strip_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t s);
+bool levels_by_grid(const std::vector<StripGrid>& grids);
+int build_strip_state(sptrsv_handle_t h, PlanState& ps, std::vector<std::vector<StripGrid>> guesses,
+                      hipStream_t s);
 
 // Builds the analysis of T^T: rows of T^T are the columns of T; each value is
 // taken from the forward plan's value buffer (so the caller's vals need not
@@ -469,10 +471,13 @@ int build_transpose(sptrsv_handle_t h, hipStream_t s) {
   const int n = h->n;
   if (h->rp_dev && n > 0) {
     int *rT = nullptr, *cT = nullptr, *sT = nullptr;
+    std::vector<std::vector<StripGrid>> guesses = grid_guesses(h, !h->upper);
+    const std::vector<std::vector<StripGrid>> none;
     int st = device_transpose(n, h->nnz, h->rp_dev, h->col_dev, s, &rT, &cT, &sT);
     DeviceAnalysis da;
     if (!st) st = device_analysis(n, h->nnz, rT, cT, !h->upper, h->unit, h->num_cu,
-                                   grid_guesses(h, !h->upper), values_bytes(h), s, da);
+                                  guesses.empty() || levels_by_grid(guesses[0]) ? guesses : none,
+                                  values_bytes(h), s, da);
     if (!st)
       st = device_value_sources(n, h->fwd.d.noff, h->fwd.d.off_src, h->fwd.d.diag_src, h->nnz, sT,
                                 da, s);
@@ -482,7 +487,7 @@ int build_transpose(sptrsv_handle_t h, hipStream_t s) {
       st = gather(h, h->trn, h->fwd.vals_buf, s);
     }
     if (!st && hipStreamSynchronize(s) != hipSuccess) st = kErrHip;
-    if (!st) st = build_strip_state(h, h->trn, !h->upper, s);
+    if (!st) st = build_strip_state(h, h->trn, std::move(guesses), s);
     if (st) {
       free_device_analysis(da);
       free_plan(h->trn);
@@ -504,7 +509,7 @@ int build_transpose(sptrsv_handle_t h, hipStream_t s) {
   int st = upload_plan(h->trn, h->vb, s);
   if (!st) st = gather(h, h->trn, h->fwd.vals_buf, s);
   if (!st && hipStreamSynchronize(s) != hipSuccess) st = kErrHip;
-  if (!st) st = build_strip_state(h, h->trn, !h->upper, s);
+  if (!st) st = build_strip_state(h, h->trn, grid_guesses(h, !h->upper), s);
   if (st) free_plan(h->trn);   // a later call starts over instead of using half a plan
   return st;
 }
@@ -821,10 +826,25 @@ bool multi_by_columns(const PlanState& ps, const Config& c) {
           c.algo == SPTRSV_ALGO_BLOCK);
 }
 
+// Distinct offsets of one system's rows r0 .. r1 - 1, ascending; false: too many.
+bool row_offsets(const int* rp, const int* col, int r0, int r1, std::vector<int>& o) {
+  for (int i = r0; i < r1; ++i)
+    for (int e = rp[i]; e < rp[i + 1]; ++e) {
+      const int d = std::abs(col[e] - i);
+      if (d == 0) continue;
+      const auto at = std::lower_bound(o.begin(), o.end(), d);
+      if (at != o.end() && *at == d) continue;
+      if (o.size() == kStripMaxOffsets) return false;
+      o.insert(at, d);
+    }
+  return true;
+}
+
 // Distinct offsets of the pattern, system by system (h->offsets; left empty
-// when some system has more than a grid's stencil would).  row_ptr, col: the
-// pattern in device memory.  Blocking; without the memory for it the strip
-// form is left unused.
+// when some system has more than a grid's stencil would, or when the systems
+// are so many and so small that a solve in strips cannot pay whatever they look
+// like).  row_ptr, col: the pattern in device memory.  Blocking; without the
+// memory for it the strip form is left unused.
 int find_offsets(sptrsv_handle_t h, const int* row_ptr, const int* col, hipStream_t s) {
   h->offsets.clear();
   if (h->n == 0) return kOk;
@@ -834,6 +854,27 @@ int find_offsets(sptrsv_handle_t h, const int* row_ptr, const int* col, hipStrea
   else
     row0.push_back(h->n);
   const int nsys = static_cast<int>(row0.size()) - 1;
+  SolveCost least;               // a claim per system; at most a level per row of the largest
+  int most = 0;
+  for (int k = 0; k < nsys; ++k) {
+    least.strips += row0[k + 1] > row0[k];
+    most = std::max(most, row0[k + 1] - row0[k]);
+  }
+  bool gain = false;
+  for (int nrhs : {1, 16})
+    gain |= strip_time(least, nrhs) < row_time(h->n, h->nnz, most, INT32_MAX, false, nrhs);
+  if (!gain) return kOk;
+  // a pattern at hand on the host is read there while it is small (a round trip
+  // to the device takes about 60 us)
+  if (!h->rp_h.empty() && h->nnz <= (1 << 15)) {
+    h->offsets.resize(nsys);
+    for (int k = 0; k < nsys; ++k)
+      if (!row_offsets(h->rp_h.data(), h->col_h.data(), row0[k], row0[k + 1], h->offsets[k])) {
+        h->offsets.clear();
+        break;
+      }
+    return kOk;
+  }
   const int words = nsys * (kStripTable + 1) + nsys + 1;   // tables, full flags, row0
   int err = kOk;
   int* buf = dalloc<int>(words, &err);
@@ -864,42 +905,64 @@ int find_offsets(sptrsv_handle_t h, const int* row_ptr, const int* col, hipStrea
   return err;
 }
 
-// Reading `attempt` (0, 1) of the offsets as grids, one per system; false: none.
-bool infer_grids(sptrsv_handle_t h, bool upper, int attempt, std::vector<StripGrid>& grids) {
-  const int nsys = static_cast<int>(h->offsets.size());
-  grids.assign(nsys, StripGrid());
-  int at = 0;
-  bool any = nsys > 0 && attempt == 0;
-  for (int k = 0; k < nsys; ++k) {
-    const int nk = h->batched ? h->sys_n[k] : h->n;
-    if (nk > 0) {
-      // systems with one reading keep it on the second attempt
-      if (strip_infer(h->offsets[k], nk, upper, attempt, &grids[k])) any = true;
-      else if (!attempt || !strip_infer(h->offsets[k], nk, upper, 0, &grids[k])) return false;
-    }
-    grids[k].row0 = at;
-    at += nk;
-  }
-  return any;
-}
-
+// Readings of the offsets as grids, one per system each: at most two.
 std::vector<std::vector<StripGrid>> grid_guesses(sptrsv_handle_t h, bool upper) {
   std::vector<std::vector<StripGrid>> all;
-  for (int attempt = 0; attempt < 2; ++attempt) {
-    std::vector<StripGrid> g;
-    if (infer_grids(h, upper, attempt, g)) all.push_back(std::move(g));
+  const int nsys = static_cast<int>(h->offsets.size());
+  auto rows = [&](int k) { return h->batched ? h->sys_n[k] : h->n; };
+  // systems often repeat: kinds by size and offsets
+  auto less = [&](int x, int y) {
+    return rows(x) != rows(y) ? rows(x) < rows(y) : h->offsets[x] < h->offsets[y];
+  };
+  std::map<int, int, decltype(less)> kinds(less);
+  std::vector<int> kind(nsys, -1), of;
+  for (int k = 0; k < nsys; ++k) {
+    if (rows(k) == 0) continue;
+    const auto at = kinds.try_emplace(k, static_cast<int>(of.size()));
+    if (at.second) of.push_back(k);
+    kind[k] = at.first->second;
+  }
+  std::vector<StripGrid> first(of.size());
+  for (int attempt = 0; attempt < 2 && nsys > 0; ++attempt) {
+    std::vector<StripGrid> g(of.size());
+    bool any = attempt == 0;
+    for (size_t q = 0; q < of.size(); ++q) {
+      if (strip_infer(h->offsets[of[q]], rows(of[q]), upper, attempt, &g[q])) any = true;
+      else if (attempt) g[q] = first[q];   // one reading only
+      else return all;
+    }
+    if (!any) break;
+    std::vector<StripGrid> grids(nsys);
+    int at = 0;
+    for (int k = 0; k < nsys; ++k) {
+      if (kind[k] >= 0) grids[k] = g[kind[k]];
+      grids[k].row0 = at;
+      at += rows(k);
+    }
+    all.push_back(std::move(grids));
+    first = std::move(g);
   }
   return all;
 }
 
-// The strip-ordered copy of a plan (strips.hpp), if its rows sit on a grid, a
-// solve of one or of many columns gains by it, and memory allows; otherwise the
+// Whether finding the levels by the grids pays: the grids of many systems take
+// longer to send over (0.2 us each) than the sweep over few levels (5 us each).
+bool levels_by_grid(const std::vector<StripGrid>& grids) {
+  int64_t levels = 0;
+  for (const StripGrid& g : grids)
+    levels = std::max<int64_t>(levels, 1 + g.wx * (g.nx - 1ll) + g.wy * (g.ny - 1ll) + g.wz * (g.nz - 1ll));
+  return 0.2 * static_cast<double>(grids.size()) < 5.0 * static_cast<double>(levels);
+}
+
+// The strip-ordered copy of a plan (strips.hpp), if its rows sit on a grid (of the
+// guesses), a solve of one or of many columns gains by it, and memory allows; otherwise the
 // plan keeps the row-wise schedules alone.  Blocking.
-int build_strip_state(sptrsv_handle_t h, PlanState& ps, bool upper, hipStream_t s) {
-  if (h->offsets.empty() || ps.strips.nstrips) return kOk;
+int build_strip_state(sptrsv_handle_t h, PlanState& ps, std::vector<std::vector<StripGrid>> guesses,
+                      hipStream_t s) {
+  if (ps.strips.nstrips) return kOk;
   std::vector<std::vector<StripGrid>> grids;
   std::vector<SolveCost> costs;
-  for (std::vector<StripGrid>& g : grid_guesses(h, upper)) {
+  for (std::vector<StripGrid>& g : guesses) {
     const SolveCost c = strip_cost(g, ps.h.max_row_len, static_cast<int>(h->vb));
     bool gain = false;
     for (int nrhs : {1, 16})
@@ -1653,7 +1716,7 @@ int analyze_from_host(sptrsv_handle_t h, const int* row_ptr, const int* col_idx,
   if ((st = upload_plan(h->fwd, h->vb, s))) return st;
   if ((st = gather(h, h->fwd, vals, s))) return st;
   if ((st = find_offsets(h, row_ptr, col_idx, s))) return st;
-  if ((st = build_strip_state(h, h->fwd, h->upper, s))) return st;
+  if ((st = build_strip_state(h, h->fwd, grid_guesses(h, h->upper), s))) return st;
   if ((st = ensure_xp(h, h->n))) return st;
   return read_status(h, s, true);
 }
@@ -1718,10 +1781,12 @@ int analyze_on_device(sptrsv_handle_t h, const int* row_ptr, const int* col_idx,
     h->num_cu = ncu;
   if (const int fs = find_offsets(h, row_ptr, col_idx, s)) return fs;
   DeviceAnalysis da;
+  std::vector<std::vector<StripGrid>> guesses = grid_guesses(h, h->upper);
+  const std::vector<std::vector<StripGrid>> none;
   // behind the values: the flags of the flag schedules and the pattern
   const int64_t vb = values_bytes(h), nb = block_bytes((static_cast<int64_t>(h->n) + 1) * 4);
   int st = device_analysis(h->n, h->nnz, row_ptr, col_idx, h->upper, h->unit, h->num_cu,
-                           grid_guesses(h, h->upper),
+                           guesses.empty() || levels_by_grid(guesses[0]) ? guesses : none,
                            vb + nb + (copy_pattern ? nb + block_bytes(h->nnz * 4) : 0), s, da);
   if (st) return st;
   char* spare = da.spare + vb;
@@ -1744,7 +1809,7 @@ int analyze_on_device(sptrsv_handle_t h, const int* row_ptr, const int* col_idx,
   }
   if ((st = init_handle_common(h, s))) return st;
   if ((st = gather(h, h->fwd, vals, s))) return st;
-  if ((st = build_strip_state(h, h->fwd, h->upper, s))) return st;
+  if ((st = build_strip_state(h, h->fwd, std::move(guesses), s))) return st;
   if ((st = ensure_xp(h, h->n))) return st;
   return read_status(h, s, true);
 }

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstring>
 #include <type_traits>
 
 #include "analysis.hpp"
@@ -46,15 +47,21 @@ __device__ __forceinline__ bool table_add(int* table, int d, bool agent) {
 
 // Each workgroup collects the offsets of a contiguous run of rows in LDS,
 // system by system, and then adds the few distinct ones to the system's
-// table, so that global atomics do not grow with the entries.
-constexpr int kOffsetRows = 4096;
+// table, so that global atomics do not grow with the entries.  Systems of one
+// run follow one another, about 2 us each, so runs are shorter where there are
+// many (4000 systems of 4 rows, whole set-up: 4.7 ms at 4096 rows a run, 0.5 before
+// there were strips).
+inline int offset_rows(int n, int nsys) {
+  const int fair = n / 1024 > 64 ? n / 1024 : 64;
+  return nsys == 1 || fair > 4096 ? 4096 : fair;
+}
 
 __global__ void __launch_bounds__(256)
 k_strip_offsets(int n, int64_t nnz, const int* __restrict__ rp, const int* __restrict__ col, int nsys,
-               const int* __restrict__ row0, int* table, int* full) {
+               const int* __restrict__ row0, int rows, int* table, int* full) {
   __shared__ int tab[kStripTable];
   __shared__ int over;
-  const int r0 = blockIdx.x * kOffsetRows, r1 = min(n, r0 + kOffsetRows);
+  const int r0 = blockIdx.x * rows, r1 = min(n, r0 + rows);
   int s = system_of(row0, nsys, r0);
   for (int a = r0; a < r1; ++s) {
     const int b = min(r1, row0[s + 1]);
@@ -766,8 +773,9 @@ struct DevFree {
 hipError_t launch_strip_offsets(int n, int64_t nnz, const int* row_ptr, const int* col, int nsys,
                                 const int* sys_row0, int* table, int* full, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  k_strip_offsets<<<blocks(n, kOffsetRows), 256, 0, s>>>(n, nnz, row_ptr, col, nsys, sys_row0,
-                                                         table, full);
+  const int rows = offset_rows(n, nsys);
+  k_strip_offsets<<<blocks(n, rows), 256, 0, s>>>(n, nnz, row_ptr, col, nsys, sys_row0, rows, table,
+                                                  full);
   return hipGetLastError();
 }
 
@@ -808,34 +816,46 @@ int build_strips(const DevPlan& p, const std::vector<StripGrid>& grids, int max_
   }
   box0[nsys] = static_cast<int>(nboxes);
   const int acc = lanes_lg ? 4 : 1;
+  // One block: uploaded [grids, box0, cnt], downloaded [cnt, box], uploaded again
+  // [boxes, box_strip] (allocations, frees and copies are what the set-up of a
+  // small triangle takes: 10 to 20 us each in a busy process).
+  auto up = [](int64_t b) { return (b + 255) / 256 * 256; };
+  const int64_t b_grids = up(nsys * static_cast<int64_t>(sizeof(StripGrid))), b_box0 = up((nsys + 1) * 4ll),
+                b_cnt = up(sizeof(StripCount)), b_box = up(nboxes * static_cast<int64_t>(sizeof(int2))),
+                b_boxes = up(nboxes * static_cast<int64_t>(sizeof(StripBox))), b_strip = up(nboxes * 4);
   DevFree f;
-  StripGrid* grids_d = nullptr;
-  int *box0_d = nullptr, *box_strip_d = nullptr;
-  int2* box_d = nullptr;
-  StripBox* boxes_d = nullptr;
-  StripCount* cnt = nullptr;
-  if (!f.get(&grids_d, nsys) || !f.get(&box0_d, nsys + 1) || !f.get(&box_d, nboxes) ||
-      !f.get(&box_strip_d, nboxes) || !f.get(&boxes_d, nboxes) || !f.get(&cnt, 1))
-    return kErrOom;
+  char* work = nullptr;
+  if (!f.get(&work, b_grids + b_box0 + b_cnt + b_box + b_boxes + b_strip)) return kErrOom;
+  StripGrid* const grids_d = reinterpret_cast<StripGrid*>(work);
+  int* const box0_d = reinterpret_cast<int*>(work + b_grids);
+  StripCount* const cnt = reinterpret_cast<StripCount*>(work + b_grids + b_box0);
+  int2* const box_d = reinterpret_cast<int2*>(work + b_grids + b_box0 + b_cnt);
+  char* const boxes_at = work + b_grids + b_box0 + b_cnt + b_box;
+  StripBox* const boxes_d = reinterpret_cast<StripBox*>(boxes_at);
+  int* const box_strip_d = reinterpret_cast<int*>(boxes_at + b_boxes);
   StripCount c{0, 0, 0};
   if (!lanes_lg) c.slots = max_len;   // an entry, a slot
-  std::vector<int2> box(nboxes);
+  std::vector<char> host(b_grids + b_box0 + b_cnt);
+  std::memcpy(host.data(), gh.data(), nsys * sizeof(StripGrid));
+  std::memcpy(host.data() + b_grids, box0.data(), (nsys + 1) * sizeof(int));
+  std::memcpy(host.data() + b_grids + b_box0, &c, sizeof(c));
 #define TCHK(expr)                            \
   do {                                        \
     if ((expr) != hipSuccess) return kErrHip; \
   } while (0)
-  TCHK(hipMemcpyAsync(grids_d, gh.data(), nsys * sizeof(StripGrid), hipMemcpyHostToDevice, s));
-  TCHK(hipMemcpyAsync(box0_d, box0.data(), (nsys + 1) * sizeof(int), hipMemcpyHostToDevice, s));
-  TCHK(hipMemcpyAsync(cnt, &c, sizeof(c), hipMemcpyHostToDevice, s));
+  TCHK(hipMemcpyAsync(work, host.data(), host.size(), hipMemcpyHostToDevice, s));
   if (lanes_lg) {
     k_strip_slots<<<std::min(blocks(p.n, 256), 1024), 256, 0, s>>>(p.n, p.off_ptr, lanes_lg, cnt);
     TCHK(hipGetLastError());
   }
   k_strip_boxes<<<static_cast<int>(nboxes), 64, 0, s>>>(grids_d, nsys, box0_d, box_d, cnt);
   TCHK(hipGetLastError());
-  TCHK(hipMemcpyAsync(box.data(), box_d, nboxes * sizeof(int2), hipMemcpyDeviceToHost, s));
-  TCHK(hipMemcpyAsync(&c, cnt, sizeof(c), hipMemcpyDeviceToHost, s));
+  std::vector<char> found(b_cnt + nboxes * sizeof(int2));
+  TCHK(hipMemcpyAsync(found.data(), cnt, found.size(), hipMemcpyDeviceToHost, s));
   TCHK(hipStreamSynchronize(s));
+  std::memcpy(&c, found.data(), sizeof(c));
+  std::vector<int2> box(nboxes);
+  std::memcpy(box.data(), found.data() + b_cnt, nboxes * sizeof(int2));
   DevStrips t;
   t.acc = acc;
   t.entries = acc == 1 ? std::max(2, c.slots) : c.slots <= 13 ? 13 : 15;
@@ -891,7 +911,6 @@ int build_strips(const DevPlan& p, const std::vector<StripGrid>& grids, int max_
   const int E = t.entries, vw = vb / 4;
   t.words = (E + 1) * vw + (E + 1) / 2;
   const int nq = t.words / 4, nt = t.words % 4;
-  auto up = [](int64_t b) { return (b + 255) / 256 * 256; };
   const int64_t b_quad = up(t.nrec * nq * 1024), b_tail = up(t.nrec * nt * 256),
                 b_src = up(t.nrec * E * 256), b_dsrc = up(t.nrec * 256),
                 b_lane = up(t.nstrips * 64ll * sizeof(StripLane)),
@@ -912,11 +931,11 @@ int build_strips(const DevPlan& p, const std::vector<StripGrid>& grids, int max_
   t.info = reinterpret_cast<StripInfo*>(take(b_info));
   hipError_t e = hipMemcpyAsync(t.info, info.data(), info.size() * sizeof(StripInfo),
                                 hipMemcpyHostToDevice, s);
+  std::vector<char> order_h(b_boxes + nboxes * sizeof(int));
+  std::memcpy(order_h.data(), boxes.data(), boxes.size() * sizeof(StripBox));
+  std::memcpy(order_h.data() + b_boxes, box_strip.data(), nboxes * sizeof(int));
   if (e == hipSuccess)
-    e = hipMemcpyAsync(boxes_d, boxes.data(), boxes.size() * sizeof(StripBox),
-                       hipMemcpyHostToDevice, s);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(box_strip_d, box_strip.data(), nboxes * sizeof(int), hipMemcpyHostToDevice, s);
+    e = hipMemcpyAsync(boxes_at, order_h.data(), order_h.size(), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) {
     k_strip_lanes_of<<<t.nstrips, 64, 0, s>>>(grids_d, boxes_d, box_strip_d, t, cnt);
     k_strip_records<<<dim3(t.nstrips, record_blocks(t.nrec, t.nstrips, max_steps)), kRecordThreads,

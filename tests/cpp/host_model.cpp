@@ -218,6 +218,7 @@ hipError_t launch_strip_lanes(const DevChunks&, unsigned char*, hipStream_t) {
 
 hipError_t launch_strip_offsets(int, int64_t, const int* rp, const int* col, int nsys,
                                 const int* row0, int* table, int* full, hipStream_t) {
+  (void)note("offsets");
   for (int s = 0; s < nsys; ++s) {
     std::set<int> d;
     for (int i = row0[s]; i < row0[s + 1]; ++i)

@@ -283,8 +283,9 @@ def test_batches_of_many_small_systems(m):
     def batch(side, count):
         return W.concat_block_diagonal([W.laplacian_triangle((side, side))] * count)
 
-    def form(side, count, nrhs):
+    def form(side, count, nrhs, offsets=True):
         T = batch(side, count)
+        m.log()
         n1, z1 = side * side, T.nnz // count
         one = W.laplacian_triangle((side, side))
         rp, ci, v = (np.ascontiguousarray(a, t) for a, t in
@@ -296,10 +297,13 @@ def test_batches_of_many_small_systems(m):
         assert m.sptrsv_analyze_batched_ex(I32(count), (I32 * count)(*[n1] * count),
                                            (I32 * count)(*[z1] * count), arr(rp), arr(ci), arr(v), 0,
                                            0, 0, 0, None, ctypes.byref(h.h)) == 0
+        assert ("offsets" in m.log()) == offsets
         out = h.form(nrhs)
         h.destroy()
         return out
-    assert form(8, 1200, 1) != "strips" and form(3, 1000, 1) != "strips"
+    assert form(8, 4000, 1) != "strips"
+    # so many, so small: whatever they look like
+    assert form(2, 4000, 1, offsets=False) != "strips" and form(3, 1500, 1, offsets=False) != "strips"
     assert form(16, 300, 16) != "strips"
     assert form(32, 64, 1) == "strips" and form(32, 64, 8) == "strips"
 
@@ -412,3 +416,12 @@ def test_other_threads_allocate_while_blocks_go_back(m, by):
     else:
         assert m.sptrsv_release_memory() == 0
     assert m.model_probed() == 2
+
+
+def test_small_host_patterns_are_read_on_the_host(m):
+    for T, want in ((W.laplacian_triangle((60, 60)), True), (W.powerlaw_lower(2000, 3, window=300), False),
+                    (W.laplacian_triangle((200, 200)), None)):
+        m.log()
+        h = Model(m, T)
+        assert h.st == 0 and ("offsets" in m.log()) == (want is None)
+        assert (h.form() == "strips") == (want is not False)
