@@ -2544,7 +2544,7 @@ int sptrsv_get_strips(sptrsv_handle_t h, int transpose, int32_t nrhs, int32_t* s
   if (strips) *strips = on ? ps.strips.nstrips : 0;
   if (slots) *slots = on ? ps.strips.entries : 0;
   if (sums) *sums = on ? strip_sums(ps.strips, nrhs) : 0;
-  if (depth) *depth = on ? strip_depth(ps.strips, static_cast<int>(h->vb)) : 0;
+  if (depth) *depth = on ? strip_depth(ps.strips, static_cast<int>(h->vb), nrhs) : 0;
   return kOk;
 }
 

@@ -728,7 +728,7 @@ __global__ void __launch_bounds__(kStripThreads, 1) k_strip(SArgs<T> a) {
 
 // The kernel for a copy.
 template <typename T> const void* strip_fn(const DevStrips& t, int nrhs) {
-  const int acc = strip_sums(t, nrhs), depth = strip_depth(t, sizeof(T));
+  const int acc = strip_sums(t, nrhs), depth = strip_depth(t, sizeof(T), nrhs);
 #define SPTRSV_STRIP(E, A, D)                                \
   if (t.entries == E && acc == A && depth == D)              \
   return reinterpret_cast<const void*>(k_strip<T, E, A, D>)

@@ -104,13 +104,16 @@ inline int strip_sums(const DevStrips& t, int nrhs) { return nrhs > 1 ? 1 : t.ac
 // Stages of records that the kernel holds (it loads them depth - 1 steps
 // ahead), for values of vb bytes.  Long records, loaded 7 steps ahead instead
 // of 3: faster where they come from memory, but in FP64 the extra stages sit in
-// accumulation registers, so a step has more to do (27-point, both triangles,
-// us at 7 / 3 steps: FP64 20^3 105 / 94, 60x50x40 (27 MB of records) 221 / 201,
-// 200x40x100 (170 MB) 516 / 546, 128^3 769 / 824; FP32 90 / 91, 183 / 190,
-// 400 / 479, 576 / 688).
-inline int strip_depth(const DevStrips& t, int vb) {
+// accumulation registers, so a step has more to do.  27-point, FP64, us per
+// solve at 7 / 3 steps, two triangles in turn (which push each other out of the
+// 256 MB cache from 128 MB each on): 68^3 (87 MB of records) 164 / 153, 80^3 (123)
+// 194 / 185, 82^3 (135) 208 / 209, 85^3 (152) 223 / 229, 95^3 (197) 267 / 282;
+// one triangle alone 95^3 234 / 224.  Several columns reach memory sooner: four, in
+// turn, 68^3 156 / 156, 76^3 (107 MB) 177 / 178, 80^3 191 / 196.  FP32, both
+// triangles: 20^3 90 / 91, 60x50x40 183 / 190, 128^3 576 / 688.
+inline int strip_depth(const DevStrips& t, int vb, int nrhs) {
   if (t.entries <= 4) return 16;
-  return vb == 4 || t.nrec * t.words * 256 > (64 << 20) ? 8 : 4;
+  return vb == 4 || t.nrec * t.words * 256 > (nrhs > 1 ? 100 << 20 : 128 << 20) ? 8 : 4;
 }
 
 struct StripSolveArgs {

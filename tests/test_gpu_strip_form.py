@@ -62,11 +62,11 @@ def test_what_is_no_grid_stays_row_wise(sp):
 def test_both_depths_of_long_fp64_records(sp):
     """Records of 13 entries a row on both sides of the size from which they
     are loaded further ahead, against the row-wise schedule bit for bit."""
-    for side, depth in ((45, 4), (100, 8)):
+    for side, depth, several in ((45, 4, 4), (72, 4, 4), (80, 4, 8), (90, 8, 8)):
         T = W.stencil_triangle((side, side, side), 27)
         d, b = dev_tri(T), dev(W.uniform_vector(T.n, 20))
         h = sp.Handle(*d, setup="device")
-        assert h.strips()["depth"] == depth and h.strips(2)["depth"] == depth
+        assert h.strips()["depth"] == depth and h.strips(2)["depth"] == several
         x = h.solve(b)
         h.status()
         assert bits_equal(x, sp.Handle(*d, setup="device").configure(algo=2, assign=0).solve(b))
