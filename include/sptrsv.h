@@ -47,13 +47,19 @@
  *     other work on the handle.  A buffer that a later call replaces (T^T,
  *     more right-hand sides) stays allocated until sptrsv_destroy if a
  *     capture of the caller's own may hold its address.
- *   - Device memory: blocks of 1 MiB and more that a call frees are kept
- *     for the next handle, at most 1 GiB over all devices; all of it goes
- *     back when an allocation of the library fails and by
- *     sptrsv_release_memory, and a block that 64 later frees have passed
- *     over goes back by itself.  Other allocators of the process do not reach
- *     it: call sptrsv_release_memory where they run out.  Before
- *     hipDeviceReset, destroy the handles and call it too.
+ *   - Device memory: beside its plan, a triangle that can be solved in
+ *     strips (see SPTRSV_ALGO_AUTO) has a strip-ordered copy, made by the
+ *     analysis whatever the options say later: 56 bytes a row for the 7-point
+ *     stencil in FP64, 224 for 13 entries a row, times 1.1 to 2.6 for lanes
+ *     without a row on grids of some 50 lines a side and more, up to 16 on
+ *     thinner ones.  Without the memory for it the copy is left out.
+ *     Blocks of 1 MiB and more that a call frees are kept for the next
+ *     handle, at most 1 GiB over all devices; all of it goes back when an
+ *     allocation of the library fails and by sptrsv_release_memory, and a
+ *     block that 64 later frees have passed over goes back by itself.  Other
+ *     allocators of the process do not reach it: call sptrsv_release_memory
+ *     where they run out.  Before hipDeviceReset, destroy the handles and
+ *     call it too.
  *   - n = 0 is valid and every solve on it is a no-op.
  *   - Dependencies are taken from the pattern (Sec. 4.4): an explicitly
  *     stored zero off-diagonal still counts as a dependency.

@@ -905,8 +905,9 @@ int build_strips(const DevPlan& p, const std::vector<StripGrid>& grids, int max_
     max_steps = std::max(max_steps, steps);
   }
   // lanes without a row cost memory: grids far from the strips' shape keep
-  // the row-wise schedules
-  if (t.nstrips == 0 || t.nrec * 64 > 16ll * p.n + (1 << 20) || max_steps > kStripMaxSteps)
+  // the row-wise schedules (batches of 16x16 grids, eight lanes a row, are
+  // still faster in strips); the gather has a thread per lane
+  if (t.nstrips == 0 || t.nrec * 64 > 16ll * p.n + (1 << 20) || t.nrec * 64 > UINT32_MAX || max_steps > kStripMaxSteps)
     return kErrNotSupported;
   const int E = t.entries, vw = vb / 4;
   t.words = (E + 1) * vw + (E + 1) / 2;
