@@ -535,10 +535,10 @@ __device__ __forceinline__ void publish_when_ready(const T* xq, int xs, const in
   if (live && first) *xo = xi;
 }
 
-template <typename T, int kStride, bool kCols>
-__global__ void __launch_bounds__(256)
-k_self_static(KArgs<T> a, const int* __restrict__ cstart, const int* __restrict__ cmeta,
-              const int* __restrict__ wptr, const int* __restrict__ wlist) {
+template <typename T, int kStride, bool kCols, bool kByRow>
+__device__ __forceinline__ void
+static_schedule(const KArgs<T>& a, const int* __restrict__ cstart, const int* __restrict__ cmeta,
+                const int* __restrict__ wptr, const int* __restrict__ wlist) {
   const int lane = threadIdx.x & 63;
   if (!grid_resident(a.arrive, a.res_limit, a.status)) return;
   const int w = wave_uniform(static_cast<int>((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
@@ -627,7 +627,10 @@ k_self_static(KArgs<T> a, const int* __restrict__ cstart, const int* __restrict_
       const int64_t qo = kCols ? static_cast<int64_t>(sd.q) : 0;
       T* const slot = a.xp + qo * a.xp_col + static_cast<int64_t>(sd.k >= 0 ? sd.k : 0) * xs;
       T* const xo = a.x + qo * a.ld + sd.i;
-      if (a.early && !__any(sd.k >= 0 && sd.e + 4 * G < sd.e1)) {
+      // (a.early is set wherever kByRow is: read here it keeps the compiler from
+      // working ahead on both sides, 115 registers instead of 133 and 589 us
+      // instead of 598 on the power-law triangle)
+      if (kByRow && a.early && !__any(sd.k >= 0 && sd.e + 4 * G < sd.e1)) {
         publish_when_ready<T>(xq, xs, sd.j, sd.v, xv, sd.bi, sd.d, sd.lg, sd.k >= 0, lane, slot, xo,
                               a.spin_limit, a.status);
       } else {
@@ -657,6 +660,23 @@ k_self_static(KArgs<T> a, const int* __restrict__ cstart, const int* __restrict_
     sc = nc;
     sb = nb;
   }
+}
+
+// Publishing by chunk and by row are kernels of their own: together, the
+// registers of the second slowed the first (128^3 7-point 374 -> 407 us, 1024^2
+// 5-point 1555 -> 1716, layers of 5,000 rows of three entries 338 -> 352).
+template <typename T, int kStride, bool kCols>
+__global__ void __launch_bounds__(256)
+k_self_static(KArgs<T> a, const int* __restrict__ cstart, const int* __restrict__ cmeta,
+              const int* __restrict__ wptr, const int* __restrict__ wlist) {
+  static_schedule<T, kStride, kCols, false>(a, cstart, cmeta, wptr, wlist);
+}
+
+template <typename T, int kStride, bool kCols>
+__global__ void __launch_bounds__(256)
+k_self_rows(KArgs<T> a, const int* __restrict__ cstart, const int* __restrict__ cmeta,
+            const int* __restrict__ wptr, const int* __restrict__ wlist) {
+  static_schedule<T, kStride, kCols, true>(a, cstart, cmeta, wptr, wlist);
 }
 
 // ------------------------- self, value sync, static pipeline, several RHS
@@ -1426,12 +1446,17 @@ template <typename T> hipError_t launch_self_value(const SolveArgs& sa, hipStrea
 }
 
 // the static single-RHS kernel for a slot width (kCols: column-batched table)
-template <typename T, bool kCols> const void* static_fn(int stride) {
-  return stride == 16  ? reinterpret_cast<const void*>(k_self_static<T, 16, kCols>)
-         : stride == 8 ? reinterpret_cast<const void*>(k_self_static<T, 8, kCols>)
-         : stride == 4 ? reinterpret_cast<const void*>(k_self_static<T, 4, kCols>)
-         : stride == 2 ? reinterpret_cast<const void*>(k_self_static<T, 2, kCols>)
-                       : reinterpret_cast<const void*>(k_self_static<T, 1, kCols>);
+template <typename T, bool kCols, int kStride> const void* static_fn_of(bool by_row) {
+  return by_row ? reinterpret_cast<const void*>(k_self_rows<T, kStride, kCols>)
+                : reinterpret_cast<const void*>(k_self_static<T, kStride, kCols>);
+}
+
+template <typename T, bool kCols> const void* static_fn(int stride, bool by_row) {
+  return stride == 16  ? static_fn_of<T, kCols, 16>(by_row)
+         : stride == 8 ? static_fn_of<T, kCols, 8>(by_row)
+         : stride == 4 ? static_fn_of<T, kCols, 4>(by_row)
+         : stride == 2 ? static_fn_of<T, kCols, 2>(by_row)
+                       : static_fn_of<T, kCols, 1>(by_row);
 }
 
 template <typename T> hipError_t launch_self_static(const SolveArgs& sa, hipStream_t s) {
@@ -1448,7 +1473,8 @@ template <typename T> hipError_t launch_self_static(const SolveArgs& sa, hipStre
          : sa.mrows == 2 ? reinterpret_cast<const void*>(k_self_multi<T, 2>)
                          : reinterpret_cast<const void*>(k_self_multi<T, 1>);
   else
-    fn = sa.chunks->col ? static_fn<T, true>(sa.xp_stride) : static_fn<T, false>(sa.xp_stride);
+    fn = sa.chunks->col ? static_fn<T, true>(sa.xp_stride, sa.early != 0)
+                        : static_fn<T, false>(sa.xp_stride, sa.early != 0);
   // the grid's residency is checked by its own wavefronts (grid_resident); a
   // cooperative launch guarantees it up front at a cost of about 16 us
   if (sa.coop) return hipLaunchCooperativeKernel(fn, dim3(sa.grid), dim3(sa.wg), args, 0, s);
@@ -1514,8 +1540,9 @@ template <typename T> int self_flag_blocks_per_cu(int wg) { return occupancy(k_s
 template <typename T> int self_static_blocks_per_cu(int wg) {
   int m = 1 << 30;
   for (int stride : {1, 2, 4, 8, 16})
-    for (const void* fn : {static_fn<T, false>(stride), static_fn<T, true>(stride)})
-      m = std::min(m, occupancy(fn, wg));
+    for (bool by_row : {false, true})
+      for (const void* fn : {static_fn<T, false>(stride, by_row), static_fn<T, true>(stride, by_row)})
+        m = std::min(m, occupancy(fn, wg));
   return m;
 }
 template <typename T> int self_multi_blocks_per_cu(int wg, int rows) {
