@@ -314,7 +314,7 @@ def main():
     elif infoL["sync"] == sp.SYNC_FLAG:
         kernel_name = "k_self_flag<double>"
     elif infoL["assign"] in (sp.ASSIGN_STATIC, sp.ASSIGN_XCD):
-        kernel_name = "k_self_static<double, %d, false>" % infoL["xp_stride"]
+        kernel_name = "k_self_static<double, %d, false, false>" % infoL["xp_stride"]
     else:
         kernel_name = "k_self_value<double, false>"
     lbL = lb_bytes(TL.n, TL.nnz)

@@ -535,10 +535,13 @@ __device__ __forceinline__ void publish_when_ready(const T* xq, int xs, const in
   if (live && first) *xo = xi;
 }
 
+// kByRow: with publish_when_ready.  Publishing by chunk is a kernel of its own:
+// the registers of the other form slowed it (128^3 7-point 374 -> 407 us, 1024^2
+// 5-point 1555 -> 1716, layers of 5,000 rows of three entries 338 -> 352).
 template <typename T, int kStride, bool kCols, bool kByRow>
-__device__ __forceinline__ void
-static_schedule(const KArgs<T>& a, const int* __restrict__ cstart, const int* __restrict__ cmeta,
-                const int* __restrict__ wptr, const int* __restrict__ wlist) {
+__global__ void __launch_bounds__(256)
+k_self_static(KArgs<T> a, const int* __restrict__ cstart, const int* __restrict__ cmeta,
+              const int* __restrict__ wptr, const int* __restrict__ wlist) {
   const int lane = threadIdx.x & 63;
   if (!grid_resident(a.arrive, a.res_limit, a.status)) return;
   const int w = wave_uniform(static_cast<int>((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
@@ -660,23 +663,6 @@ static_schedule(const KArgs<T>& a, const int* __restrict__ cstart, const int* __
     sc = nc;
     sb = nb;
   }
-}
-
-// Publishing by chunk and by row are kernels of their own: together, the
-// registers of the second slowed the first (128^3 7-point 374 -> 407 us, 1024^2
-// 5-point 1555 -> 1716, layers of 5,000 rows of three entries 338 -> 352).
-template <typename T, int kStride, bool kCols>
-__global__ void __launch_bounds__(256)
-k_self_static(KArgs<T> a, const int* __restrict__ cstart, const int* __restrict__ cmeta,
-              const int* __restrict__ wptr, const int* __restrict__ wlist) {
-  static_schedule<T, kStride, kCols, false>(a, cstart, cmeta, wptr, wlist);
-}
-
-template <typename T, int kStride, bool kCols>
-__global__ void __launch_bounds__(256)
-k_self_rows(KArgs<T> a, const int* __restrict__ cstart, const int* __restrict__ cmeta,
-            const int* __restrict__ wptr, const int* __restrict__ wlist) {
-  static_schedule<T, kStride, kCols, true>(a, cstart, cmeta, wptr, wlist);
 }
 
 // ------------------------- self, value sync, static pipeline, several RHS
@@ -1447,8 +1433,8 @@ template <typename T> hipError_t launch_self_value(const SolveArgs& sa, hipStrea
 
 // the static single-RHS kernel for a slot width (kCols: column-batched table)
 template <typename T, bool kCols, int kStride> const void* static_fn_of(bool by_row) {
-  return by_row ? reinterpret_cast<const void*>(k_self_rows<T, kStride, kCols>)
-                : reinterpret_cast<const void*>(k_self_static<T, kStride, kCols>);
+  return by_row ? reinterpret_cast<const void*>(k_self_static<T, kStride, kCols, true>)
+                : reinterpret_cast<const void*>(k_self_static<T, kStride, kCols, false>);
 }
 
 template <typename T, bool kCols> const void* static_fn(int stride, bool by_row) {

@@ -59,7 +59,7 @@ struct SolveArgs {
   int nrhs = 1;
   int ld = 0;
   int spin_limit = 1 << 22;
-  int early = 0;     // static schedules, one right-hand side: rows are published one by one (k_self_rows)
+  int early = 0;     // static schedules, one right-hand side: rows are published one by one
   int poll = 1;      // waits: 1 = two overlapped rounds over all slots, 0 = pending only
   int xp_stride = 1; // static schedules, one right-hand side: elements between xp values
   int64_t xp_col = 0;   // column-batched static solves: elements between the columns of xp
