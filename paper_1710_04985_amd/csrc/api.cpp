@@ -1309,7 +1309,7 @@ int solve_column(sptrsv_handle_t h, PlanState& ps, const Config& c, const void* 
 }
 
 // Strip-wise self-scheduled solve.  Strips are claimed from a ticket, so the
-// grid may fill the GPU.
+// grid may fill the GPU, and needs no cooperative launch whatever the option says.
 template <typename T>
 int solve_strips(sptrsv_handle_t h, PlanState& ps, const void* b, void* x, int nrhs, int ld,
                  void* xp, hipStream_t s, const SolveExt& ext) {
@@ -1330,7 +1330,6 @@ int solve_strips(sptrsv_handle_t h, PlanState& ps, const void* b, void* x, int n
   a.nrhs = nrhs;
   a.ld = ld;
   a.spin_limit = h->spin_limit;
-  a.coop = h->coop;
   const int64_t tasks = static_cast<int64_t>(ps.strips.nstrips) * nrhs;
   a.grid = static_cast<int>(std::min<int64_t>(strip_occupancy(h, ps, nrhs) * h->num_cu, tasks));
   if (launch_fill_sentinel<T>(static_cast<T*>(xp), ps.strips.npub * nrhs, h->scratch.arrive, s) != hipSuccess)

@@ -976,7 +976,6 @@ template <typename T> hipError_t launch_strip_solve(const StripSolveArgs& sa, hi
   const void* fn = strip_fn<T>(t, sa.nrhs);
   if (!fn) return hipErrorInvalidValue;
   void* args[] = {&a};
-  if (sa.coop) return hipLaunchCooperativeKernel(fn, dim3(sa.grid), dim3(kStripThreads), args, 0, s);
   return hipLaunchKernel(fn, dim3(sa.grid), dim3(kStripThreads), args, 0, s);
 }
 

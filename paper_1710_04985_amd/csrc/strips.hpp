@@ -125,7 +125,6 @@ struct StripSolveArgs {
   int nrhs = 1;
   int64_t ld = 0;    // elements between the columns of b and x
   int spin_limit = 1 << 22;
-  int coop = 0;
   int grid = 1;      // four-wavefront workgroups
 };
 template <typename T> hipError_t launch_strip_solve(const StripSolveArgs& a, hipStream_t s);

@@ -166,3 +166,27 @@ def test_values_updated_while_another_form_is_chosen(sp):
             h.configure(algo=0)
             assert bits_equal(h.solve(b), ref.solve(b))
         h.status()
+
+
+def test_cooperative_option_costs_strips_nothing(sp):
+    """Strips need no co-residency, so the option leaves their launch alone (a
+    cooperative one took 125 us instead of 21)."""
+    T = W.laplacian_triangle((64, 64))
+    d, b = dev_tri(T), dev(W.uniform_vector(T.n, 3))
+
+    def us(**o):
+        h = sp.Handle(*d).configure(**o)
+        assert h.strips()["strips"]
+        best = 1e9
+        for _ in range(5):
+            t0, t1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            h.solve(b)
+            t0.record()
+            for _ in range(40):
+                h.solve(b)
+            t1.record()
+            t1.synchronize()
+            best = min(best, t0.elapsed_time(t1) / 40 * 1e3)
+        h.status()
+        return best
+    assert us(cooperative=1) < 2 * us()
