@@ -58,9 +58,9 @@ constexpr int default_lanes(int len) {
   while (g < 64 && (len + g - 1) / g > kDefaultLaneEntries) g *= 2;
   return g;
 }
-// Positions that HostPlan::near_lane is counted on: every near_step(n)-th, so
-// that it costs nothing on large triangles.
-constexpr int near_step(int n) { return n >> 16 > 1 ? n >> 16 : 1; }
+// Positions that HostPlan::near_row is counted on: every near_step(n)-th, some
+// 8192 to 16384 in all, so that it costs nothing on large triangles.
+constexpr int near_step(int n) { return n >> 13 > 1 ? n >> 13 : 1; }
 
 // Level-ordered layout of one triangle, as the solve kernels read it.
 //   pos_row[k]  row (x index) solved at position k; positions run level by
@@ -82,9 +82,9 @@ struct HostPlan {
   std::vector<int> pos_row, pos_ilev;
   std::vector<int> off_ptr, off_col, off_pos, off_src, diag_src;
   int max_row_len = 0;            // max off-diagonal count of a row
-  double near_lane = 0;           // entries one level up, per lane of the default lane rule:
-                                  // how much of what a row waits for comes at once (0 where
-                                  // no row takes several lanes)
+  double near_row = 0;            // entries one level up, per row: how much of what a row
+  double near_lane = 0;           // waits for comes at once; the same per lane of the default
+                                  // lane rule (0 where no row takes several lanes)
 };
 
 // Builds the plan of the triangle (row_ptr, col); src maps an entry to its

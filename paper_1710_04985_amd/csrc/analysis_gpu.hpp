@@ -33,7 +33,7 @@ struct DeviceAnalysis {
   int nlev = 0;
   int64_t noff = 0;
   int max_row_len = 0;
-  double near_lane = 0;     // as in HostPlan
+  double near_row = 0, near_lane = 0;   // as in HostPlan
   int* level = nullptr;     // [n]
   int* depcnt = nullptr;    // [n]
   int* jlev = nullptr;      // [n] rows by (level, row)

@@ -765,24 +765,28 @@ bool takes_strips(const PlanState& ps, const Config& c, int nrhs) {
 
 // Whether a static schedule over `waves` wavefronts and `chunks` chunks publishes
 // each row of a chunk as soon as it is ready: with overlapped polling, in
-// triangles whose longer rows take several lanes, where most dependencies are
-// ready before a chunk is reached and the last ones come one at a time (row-wise,
-// us per solve, whole chunks against row by row: power-law 1M rows 738 / 604, its
-// transpose in FP32 of 777,777 rows 602 / 444, 128^3 27-point 2198 / 1220; a third
-// to a half of an entry per lane one level up, 27-point three quarters).  Where a
-// lane's entries are missing together, asking for all of them at once is faster:
-// always in rows of at most four entries (128^3 7-point 375 / 694, 256 2-D ILU(0)
-// factors 571 / 727), and by how many entries of a lane are one level up
-// otherwise.  Layers of 5,000 rows, 1, 2, 4 such entries per lane, rows of 8 in
-// two lanes: 303 / 326, 335 / 453, 378 / 740; rows of 16 in four: 567 / 548,
-// 608 / 675, 613 / 841.  Twice the wavefronts (layers of 10,000) wait less each:
-// 1, 2, 3, 4 per lane 268 / 211, 319 / 283, 347 / 368, 370 / 449; so do
-// wavefronts with several chunks a level (rows of 40 in sixteen lanes, 2.5 per
-// lane: 1494 / 1414).
+// triangles whose longer rows take several lanes, where the last of a row's
+// dependencies come one at a time.  Where several come together, asking for all
+// of them at once and publishing once is faster: always in rows of at most four
+// entries (128^3 7-point 375 us by chunk, 694 by row), and by the entries that
+// a row has one level up otherwise.  us, by chunk / by row:
+//   one: power-law 1M rows 716 / 594, its transpose in FP32 of 777,777 rows
+//     602 / 437; 2000 rows 61 / 58; rows of 8 in layers of 50, 1500, 5000:
+//     224 / 219, 272 / 250, 292 / 294
+//   two, three: rows of 8 in layers of 5000 303 / 326; 27-point 24^3 195 / 224,
+//     90^3 766 / 971 (transposed 775 / 1101); rows of 16 in layers of 1500
+//     303 / 342
+//   eight: rows of 8 in layers of 5000 378 / 740, of 16 608 / 675
+// Layers of more than 8192 rows, or several chunks a level for each wavefront,
+// are bound by what is read rather than by the wait: there by row up to 2.5 per
+// lane (layers of 10,000, rows of 8 in two lanes, 1, 2, 3, 4 per lane: 268 / 211,
+// 319 / 283, 347 / 368, 370 / 449; layers of 5000, rows of 40 in sixteen lanes,
+// 0.3 and 2.5: 1361 / 1190, 1494 / 1414).
 int publish_early(sptrsv_handle_t h, const PlanState& ps, const Config& c, int waves, int chunks) {
   if (c.poll == 0 || c.group == 1 || ps.h.max_row_len <= kDefaultLaneEntries) return 0;
-  const bool more = waves >= 2 * h->num_cu || chunks > 2ll * waves * ps.h.nlev;
-  return ps.h.near_lane <= (more ? 2.5 : 1.0) ? 1 : 0;
+  const int64_t nlev = ps.h.nlev;
+  const bool busy = h->n > 8192 * nlev || chunks > 2 * waves * nlev;
+  return ps.h.near_row <= 1.5 || (busy && ps.h.near_lane <= 2.5) ? 1 : 0;
 }
 
 // Schedule of a solve with nrhs > 1 right-hand sides: sptrsv_tune_multi's
@@ -1741,6 +1745,7 @@ void install_device_plan(sptrsv_handle_t h, PlanState& ps, DeviceAnalysis& da, b
   p.ilev = std::move(da.ilev);
   p.pos_ilev = p.ilev;
   p.max_row_len = da.max_row_len;
+  p.near_row = da.near_row;
   p.near_lane = da.near_lane;
   DevPlan& d = ps.d;
   d = DevPlan();

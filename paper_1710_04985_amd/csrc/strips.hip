@@ -47,13 +47,13 @@ __device__ __forceinline__ bool table_add(int* table, int d, bool agent) {
 
 // Each workgroup collects the offsets of a contiguous run of rows in LDS,
 // system by system, and then adds the few distinct ones to the system's
-// table, so that global atomics do not grow with the entries.  Systems of one
-// run follow one another, about 2 us each, so runs are shorter where there are
-// many (4000 systems of 4 rows, whole set-up: 4.7 ms at 4096 rows a run, 0.5 before
-// there were strips).
+// table, so that global atomics do not grow with the entries.  Runs are short
+// enough for 512 workgroups (13,824 rows of 13 entries: 70 us in runs of 4096,
+// 9 in runs of 256), and for twice as many where systems, which follow one
+// another in a run, about 2 us each, may be small (4000 systems of 4 rows, whole
+// set-up: 4.7 ms in runs of 4096, 0.5 before there were strips).
 inline int offset_rows(int n, int nsys) {
-  const int fair = n / 1024 > 64 ? n / 1024 : 64;
-  return nsys == 1 || fair > 4096 ? 4096 : fair;
+  return nsys == 1 ? std::min(std::max(n / 512, 256), 4096) : std::min(std::max(n / 1024, 64), 4096);
 }
 
 __global__ void __launch_bounds__(256)

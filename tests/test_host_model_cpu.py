@@ -324,10 +324,11 @@ def test_rows_published_one_by_one_where_they_wait_for_little(m):
     """The static row-wise schedule publishes by row where few entries of a lane
     are one level up, and by chunk where most are."""
     for T, want in ((_layers(20000, 20, 8, 0), "static"), (_layers(20000, 20, 16, 0), "static"),
-                    (_layers(20000, 20, 1, 7), "static_by_row"), (_layers(30000, 20, 2, 14), "static_by_row"),
-                    (_layers(100000, 11, 4, 4), "static_by_row"),     # two wavefronts per CU
+                    (_layers(20000, 20, 1, 7), "static_by_row"), (_layers(30000, 20, 2, 14), "static"),
+                    (_layers(100000, 11, 4, 4), "static_by_row"),     # wide layers
+                    (_layers(40000, 20, 4, 4), "static"), (_layers(40000, 20, 1, 39), "static_by_row"),
                     (W.powerlaw_lower(20000, 3, window=2000), "static_by_row"),
-                    (W.stencil_triangle((20, 20, 20), 27), "static_by_row"),
+                    (W.stencil_triangle((20, 20, 20), 27), "static"),
                     (W.laplacian_triangle((30, 30, 30)), "static")):
         h = Model(m, T).set(algo=2, assign=0)
         assert h.form() == want
