@@ -691,10 +691,11 @@ int widest_level(sptrsv_handle_t h) {
 // Whether the options leave room for the strip form of the self-scheduled
 // solve: it computes the sums of the default lane rule, with one-wavefront
 // workgroups.
-bool strip_rule(sptrsv_handle_t h) {
-  return h->fwd.strips.nstrips > 0 && h->group == 0 && h->epl == kDefaultLaneEntries && h->wg == 64 &&
+bool strip_options(sptrsv_handle_t h) {
+  return h->group == 0 && h->epl == kDefaultLaneEntries && h->wg == 64 &&
          (h->algo == SPTRSV_ALGO_AUTO || h->algo == SPTRSV_ALGO_SELF);
 }
+bool strip_rule(sptrsv_handle_t h) { return h->fwd.strips.nstrips > 0 && strip_options(h); }
 
 // The schedule a solve uses: the autotuner's choice if there is one, else the
 // options.  Options left at their defaults follow features of the pattern
@@ -750,13 +751,18 @@ Config resolve(sptrsv_handle_t h) {
   return c;
 }
 
-// Whether a solve with schedule c is one in strips, memory permitting (the
-// tasks and their dump slots are counted in 32 bits): a triangle on a grid can
-// have far fewer levels than its strips have steps, where entries are missing
-// or the rows along a line do not depend on one another.
-bool takes_strips(const PlanState& ps, const Config& c, int nrhs) {
+// Whether a solve with schedule c can be one in strips (the tasks and their dump
+// slots are counted in 32 bits), memory permitting.
+bool can_take_strips(const PlanState& ps, const Config& c, int nrhs) {
   const int64_t tasks = static_cast<int64_t>(ps.strips.nstrips) * nrhs;
-  return c.strip && tasks > 0 && tasks < INT32_MAX / kDumpSlot &&
+  return c.strip && tasks > 0 && tasks < INT32_MAX / kDumpSlot;
+}
+
+// Whether it is one: a triangle on a grid can have far fewer levels than its
+// strips have steps, where entries are missing or the rows along a line do not
+// depend on one another.
+bool takes_strips(const PlanState& ps, const Config& c, int nrhs) {
+  return can_take_strips(ps, c, nrhs) &&
          (c.strip == 2 ||
           strip_time(ps.strip_cost, nrhs) <
               row_time(ps.h.n, ps.h.noff, ps.h.nlev, ps.h.max_row_len,
@@ -1345,6 +1351,17 @@ int solve_strips(sptrsv_handle_t h, PlanState& ps, const void* b, void* x, int n
   return kOk;
 }
 
+// Whether the tables and buffers of a default row-wise (or block) solve exist.
+bool row_tables_ready(sptrsv_handle_t h, const PlanState& ps, const Config& c, int nrhs) {
+  int kl = 1;
+  while (kl < nrhs && kl < 64) kl <<= 1;
+  if (nrhs > 1)
+    return ps.chunks.count(std::make_tuple(0, 0, 64 / kl, 1)) && ps.d.row_pos &&
+           std::min(h->xp_elems, h->bp_elems) >= static_cast<int64_t>(h->n) * nrhs;
+  if (c.algo == SPTRSV_ALGO_BLOCK && !h->blk[&ps == &h->trn].built) return false;
+  return ps.chunks.count(std::make_tuple(c.group, c.epl, 0, 1)) != 0;
+}
+
 template <typename T>
 int solve_impl(sptrsv_handle_t h, PlanState& ps, const Config& c_in, const void* b, void* x,
                int nrhs, int ld, hipStream_t s, const SolveExt& ext = SolveExt()) {
@@ -1353,7 +1370,15 @@ int solve_impl(sptrsv_handle_t h, PlanState& ps, const Config& c_in, const void*
   if (n == 0 || nrhs == 0) return kOk;
   const bool multi = nrhs > 1;
   if (is_column(c_in.algo) && !multi) return solve_column<T>(h, ps, c_in, b, x, s, ext);
-  if (takes_strips(ps, c_in, nrhs) && !(multi && ext.no_alloc)) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess) return kErrHip;
+  const bool capturing = cap != hipStreamCaptureStatusNone;
+  // (under capture or without allocation, strips that are there go before tables
+  // that are not)
+  if ((takes_strips(ps, c_in, nrhs) ||
+       ((capturing || ext.no_alloc) && can_take_strips(ps, c_in, nrhs) &&
+        !row_tables_ready(h, ps, c_in, nrhs))) &&
+      !(multi && ext.no_alloc)) {
     // a fixed buffer too small for the published values, or no memory for them,
     // leaves the row-wise (or block) form
     const int64_t need = strip_values(ps.strips, nrhs);
@@ -1373,9 +1398,6 @@ int solve_impl(sptrsv_handle_t h, PlanState& ps, const Config& c_in, const void*
   while (kl < nrhs && kl < 64) kl <<= 1;
   int err = kOk;
   // static assignment keeps one row per lane (its pipeline holds one row)
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cap) != hipSuccess) return kErrHip;
-  const bool capturing = cap != hipStreamCaptureStatusNone;
   bool use_static = c.algo == SPTRSV_ALGO_SELF && (multi || c.sync == SPTRSV_SYNC_VALUE) &&
                     (c.assign == SPTRSV_ASSIGN_STATIC || c.assign == SPTRSV_ASSIGN_XCD);
   // several right-hand sides, static: each lane group owns mrows rows
@@ -2131,7 +2153,12 @@ int sptrsv_solve_transpose(sptrsv_handle_t h, const void* b, void* x, hipStream_
 
 int sptrsv_prepare_transpose(sptrsv_handle_t h, hipStream_t stream) {
   if (!h) return kErrInvalidArg;
-  return build_transpose(h, stream);
+  if (const int st = build_transpose(h, stream)) return st;
+  // strips are ready to be captured; where T^T sits on a grid and is solved
+  // otherwise, so is what it is solved with
+  const Config c = resolve(h);
+  if (h->offsets.empty() || !strip_options(h) || h->set_mask || takes_strips(h->trn, c, 1)) return kOk;
+  return prepare_schedule(h, true, c, stream);
 }
 
 int sptrsv_solve_multi(sptrsv_handle_t h, int32_t nrhs, int32_t ld, const void* B, void* X,

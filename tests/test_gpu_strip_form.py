@@ -190,3 +190,33 @@ def test_cooperative_option_costs_strips_nothing(sp):
         h.status()
         return best
     assert us(cooperative=1) < 2 * us()
+
+
+def test_first_solves_of_shallow_triangles_under_capture(sp):
+    """Captured right after the analysis (T^T: after prepare_transpose), without a
+    solve before, whatever form they take; replays beside the handle's own solves."""
+    chains = band(16384, [1])
+    rows = np.repeat(np.arange(16384), np.diff(chains.row_ptr))
+    cut = (chains.col_idx % 256 != 255) | (chains.col_idx == rows)
+    rp = np.concatenate([[0], np.cumsum(np.add.reduceat(cut, chains.row_ptr[:-1]))]).astype(np.int32)
+    for T in (W.laplacian_triangle((3, 3)), band(20000, []), W.laplacian_triangle((40, 30)),
+              W.Triangle(16384, rp, chains.col_idx[cut], chains.vals[cut])):
+        d, b = dev_tri(T), dev(W.uniform_vector(T.n, 7))
+        one = sp.Handle(*d).configure(algo=1, group=1)
+        want, want_t = one.solve(b), one.solve_t(b)
+        h = sp.Handle(*d, setup="device")
+        h.prepare_transpose()
+        y, z = torch.empty_like(b), torch.empty_like(b)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            h.solve(b, out=y)
+            h.solve_t(b, out=z)
+        for _ in range(3):
+            y.zero_()
+            z.zero_()
+            g.replay()
+            torch.cuda.synchronize()
+            assert bits_equal(y, want) and bits_equal(z, want_t)
+            assert bits_equal(h.solve(2 * b), one.solve(2 * b))
+        h.status()

@@ -426,3 +426,26 @@ def test_small_host_patterns_are_read_on_the_host(m):
         h = Model(m, T)
         assert h.st == 0 and ("offsets" in m.log()) == (want is None)
         assert (h.form() == "strips") == (want is not False)
+
+
+def test_first_solves_under_capture(m):
+    """A captured solve needs no table that is not there yet: T after the
+    analysis, T^T after sptrsv_prepare_transpose, also where T^T is not solved in
+    strips; and several columns in strips where the row-wise tables are missing."""
+    for T in (_chains(5, 5), W.laplacian_triangle((4, 4)), W.laplacian_triangle((60, 60)), SHALLOW["chains"],
+              SHALLOW["independent"], W.laplacian_triangle((20, 20, 20))):
+        h = Model(m, T)
+        assert m.sptrsv_prepare_transpose(h.h, None) == 0
+        m.model_capture(1)
+        assert h.solve() == 0 and h.solve(t=True) == 0, T.n
+        m.model_capture(0)
+        h.destroy()
+    # strips win for one column and lose for sixteen: captured, they are there
+    rng = np.random.Generator(np.random.PCG64(1))
+    T = W.laplacian_triangle((128, 128))
+    rows = np.repeat(np.arange(T.n, dtype=np.int64), np.diff(T.row_ptr))
+    k = rng.random(T.nnz) < 0.2
+    h = Model(m, _rows(T.n, [(rows[k], T.col_idx[k].astype(np.int64))]))
+    m.model_npub(100)
+    assert m.sptrsv_prepare_transpose(h.h, None) == 0
+    assert h.form() != "strips" and h.form(16) == "strips"
