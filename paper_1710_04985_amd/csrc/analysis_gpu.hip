@@ -290,8 +290,11 @@ __global__ void __launch_bounds__(256) k_keys(int n, const int* __restrict__ lev
 }
 
 // Workgroups of the kernels that add up over all rows: each ends with an atomic
-// on one word, about 10 ns apart.
-constexpr int kCheckBlocks = 1024;
+// on one word, about 10 ns apart, unless it would change nothing.  The check has
+// more of them, so that no thread has several long rows (us at 1024 / 4096 /
+// 16384: power-law 1M rows 934 / 615 / 611, 128^3 7-point 22 / 18 / 23, 27-point
+// 63 / 69 / 67).
+constexpr int kCheckBlocks = 4096, kGridLevelBlocks = 1024;
 
 // inverse permutation, row length per position, level pointers
 __global__ void __launch_bounds__(256) k_positions(int n, int nlev, const int* __restrict__ pos_row,
@@ -345,7 +348,7 @@ __global__ void __launch_bounds__(256) k_offdiag(int n, int unit, const int* __r
 }
 
 // Entries one level up, and lanes, of every `step`-th position (see near_step):
-// counts[0], counts[1].  A wavefront per position: rows are long here, some of
+// counts[0], counts[1]; counts[2]: all entries.  A wavefront per position: rows are long here, some of
 // them very (with a thread each, 50,000 rows of a power-law triangle took 0.4 ms).
 __global__ void __launch_bounds__(256)
 k_near(int n, int step, const int* __restrict__ pos_row, const int* __restrict__ level,
@@ -369,6 +372,7 @@ k_near(int n, int step, const int* __restrict__ pos_row, const int* __restrict__
     const int* w = wave[threadIdx.x];
     atomicAdd(counts + threadIdx.x, w[0] + w[1] + w[2] + w[3]);
   }
+  if (blockIdx.x == 0 && threadIdx.x == 0) counts[2] = off_ptr[n];
 }
 
 inline int blocks(int64_t work) {
@@ -580,10 +584,10 @@ int device_analysis(int n, int64_t nnz, const int* row_ptr, const int* col, bool
     out.spare = at;
   }
   // [0] flags, [1] max row length, [2] max level, [3] chunk ticket, [4] grid levels
-  // differ, [5] and [6] k_near's counts
-  DALLOC(tp.flags, 7);
-  const int init[7] = {0, 0, -1, 0, 0, 0, 0};
-  int got[7] = {0, 0, -1, 0, 1, 0, 0};
+  // differ, [5] to [7] k_near's counts
+  DALLOC(tp.flags, 8);
+  const int init[8] = {0, 0, -1, 0, 0, 0, 0, 0};
+  int got[8] = {0, 0, -1, 0, 1, 0, 0, 0};
   DCHK(hipMemcpyAsync(tp.flags, init, sizeof(init), hipMemcpyHostToDevice, s));
   k_check<<<std::min(blocks(n), kCheckBlocks), 256, 0, s>>>(n, nnz, row_ptr, col, upper, unit_diag,
                                                             out.depcnt, tp.flags, tp.flags + 1);
@@ -601,7 +605,7 @@ int device_analysis(int n, int64_t nnz, const int* row_ptr, const int* col, bool
     if (!tp.grids) DALLOC(tp.grids, static_cast<int64_t>(g.size()));
     DCHK(hipMemcpyAsync(tp.grids, g.data(), g.size() * sizeof(StripGrid), hipMemcpyHostToDevice, s));
     DCHK(hipMemcpyAsync(tp.flags + 2, init + 2, 3 * sizeof(int), hipMemcpyHostToDevice, s));
-    k_grid_levels<<<std::min(blocks(n), kCheckBlocks), 256, 0, s>>>(
+    k_grid_levels<<<std::min(blocks(n), kGridLevelBlocks), 256, 0, s>>>(
         n, row_ptr, col, tp.grids, static_cast<int>(g.size()), out.level, tp.flags + 4,
         tp.flags + 2);
     DCHK(hipGetLastError());
@@ -678,20 +682,22 @@ int device_analysis(int n, int64_t nnz, const int* row_ptr, const int* col, bool
   int noff = 0;
   DCHK(hipMemcpyAsync(out.ilev.data(), ilev, (static_cast<size_t>(nlev) + 1) * sizeof(int),
                       hipMemcpyDeviceToHost, s));
-  DCHK(hipMemcpyAsync(&noff, out.off_ptr + n, sizeof(int), hipMemcpyDeviceToHost, s));
   const bool near = max_len > kDefaultLaneEntries;
   if (near) {
-    k_near<<<512, 256, 0, s>>>(
-        n, near_step(n), out.pos_row, out.level, out.off_ptr, out.off_col, tp.flags + 5);
+    k_near<<<512, 256, 0, s>>>(n, near_step(n), out.pos_row, out.level, out.off_ptr, out.off_col,
+                               tp.flags + 5);
     DCHK(hipGetLastError());
     DCHK(hipMemcpyAsync(got, tp.flags, sizeof(got), hipMemcpyDeviceToHost, s));
+  } else {
+    DCHK(hipMemcpyAsync(&noff, out.off_ptr + n, sizeof(int), hipMemcpyDeviceToHost, s));
   }
   DCHK(hipStreamSynchronize(s));
-  out.noff = noff;
   if (near) {
+    noff = got[7];
     out.near_row = static_cast<double>(got[5]) / ((n + near_step(n) - 1) / near_step(n));
     out.near_lane = static_cast<double>(got[5]) / got[6];
   }
+  out.noff = noff;
   return kOk;
 }
 
