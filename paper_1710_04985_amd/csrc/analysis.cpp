@@ -187,7 +187,8 @@ void build_plan(int n, const int* row_ptr, const int* col, const int* src, bool 
     int64_t near = 0, lanes = 0, rows = 0;
     for (int64_t k = 0; k < n; k += near_step(n), ++rows) {
       const int lev = p.level[p.pos_row[k]];
-      for (int o = p.off_ptr[k]; o < p.off_ptr[k + 1]; ++o) near += p.level[p.off_col[o]] == lev - 1;
+      const int end = std::min(p.off_ptr[k + 1], p.off_ptr[k] + kNearEntries);
+      for (int o = p.off_ptr[k]; o < end; ++o) near += p.level[p.off_col[o]] == lev - 1;
       lanes += default_lanes(p.off_ptr[k + 1] - p.off_ptr[k]);
     }
     p.near_row = static_cast<double>(near) / static_cast<double>(rows);

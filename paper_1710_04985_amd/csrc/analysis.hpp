@@ -61,6 +61,7 @@ constexpr int default_lanes(int len) {
 // Positions that HostPlan::near_row is counted on: every near_step(n)-th, some
 // 2048 to 4096 in all, so that it costs nothing on large triangles.
 constexpr int near_step(int n) { return n >> 11 > 1 ? n >> 11 : 1; }
+constexpr int kNearEntries = 512;   // and that many entries of a row at most
 
 // Level-ordered layout of one triangle, as the solve kernels read it.
 //   pos_row[k]  row (x index) solved at position k; positions run level by

@@ -348,22 +348,29 @@ __global__ void __launch_bounds__(256) k_offdiag(int n, int unit, const int* __r
 }
 
 // Entries one level up, and lanes, of every `step`-th position (see near_step):
-// counts[0], counts[1]; counts[2]: all entries.  A wavefront per position: rows are long here, some of
-// them very (with a thread each, 50,000 rows of a power-law triangle took 0.4 ms).
+// counts[0], counts[1]; counts[2]: all entries.  Sixteen lanes per position, since
+// some rows are very long (with a thread each, 50,000 rows of a power-law triangle
+// took 0.4 ms), and few workgroups, since each ends with two atomics.
+constexpr int kNearLanes = 16;
+
 __global__ void __launch_bounds__(256)
 k_near(int n, int step, const int* __restrict__ pos_row, const int* __restrict__ level,
        const int* __restrict__ off_ptr, const int* __restrict__ off_col, int* counts) {
   __shared__ int wave[2][4];
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x % kNearLanes;
+  const int64_t k = static_cast<int64_t>(blockIdx.x * (256 / kNearLanes) + threadIdx.x / kNearLanes) * step;
   int near = 0, lanes = 0;
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * 4 * step;
-  for (int64_t k = (static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6)) * step; k < n; k += stride) {
+  if (k < n) {
     const int lev = level[pos_row[k]], e0 = off_ptr[k], e1 = off_ptr[k + 1];
-    for (int e = e0 + lane; e < e1; e += 64) near += level[off_col[e]] == lev - 1;
-    if (lane == 0) lanes += default_lanes(e1 - e0);
+    for (int e = e0 + lane; e < min(e1, e0 + kNearEntries); e += kNearLanes)
+      near += level[off_col[e]] == lev - 1;
+    if (lane == 0) lanes = default_lanes(e1 - e0);
   }
-  for (int o = 32; o > 0; o >>= 1) near += __shfl_xor(near, o, 64);
-  if (lane == 0) {
+  for (int o = 32; o > 0; o >>= 1) {
+    near += __shfl_xor(near, o, 64);
+    lanes += __shfl_xor(lanes, o, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
     wave[0][threadIdx.x >> 6] = near;
     wave[1][threadIdx.x >> 6] = lanes;
   }
@@ -684,8 +691,9 @@ int device_analysis(int n, int64_t nnz, const int* row_ptr, const int* col, bool
                       hipMemcpyDeviceToHost, s));
   const bool near = max_len > kDefaultLaneEntries;
   if (near) {
-    k_near<<<512, 256, 0, s>>>(n, near_step(n), out.pos_row, out.level, out.off_ptr, out.off_col,
-                               tp.flags + 5);
+    const int positions = (n + near_step(n) - 1) / near_step(n), per = 256 / kNearLanes;
+    k_near<<<(positions + per - 1) / per, 256, 0, s>>>(n, near_step(n), out.pos_row, out.level,
+                                                       out.off_ptr, out.off_col, tp.flags + 5);
     DCHK(hipGetLastError());
     DCHK(hipMemcpyAsync(got, tp.flags, sizeof(got), hipMemcpyDeviceToHost, s));
   } else {
