@@ -299,16 +299,21 @@ inline unsigned record_blocks(int64_t nrec, int nstrips, int max_steps) {
   return static_cast<unsigned>(std::min(all, fair));
 }
 
+// (a loop around the one turn that most triangles take cost it a sixth)
+template <bool kTurns>
 __global__ void __launch_bounds__(kRecordThreads)
 k_strip_records(const int* __restrict__ off_ptr, const int* __restrict__ off_col,
                 const int* __restrict__ row_pos, const unsigned char* __restrict__ lanes_lg,
                 const StripGrid* __restrict__ grids, const StripBox* __restrict__ boxes, int vb,
                 DevStrips d, StripCount* cnt) {
   const int p = blockIdx.x;
+  int s = blockIdx.y * kRecordWaves + (threadIdx.x >> 6);
   const StripInfo inf = d.info[p];
-  for (int s = blockIdx.y * kRecordWaves + (threadIdx.x >> 6); s < inf.steps;
-       s += gridDim.y * kRecordWaves)
+  if (s >= inf.steps) return;
+  do {
     strip_record(off_ptr, off_col, row_pos, lanes_lg, grids, boxes, vb, d, cnt, p, s, inf);
+    if constexpr (kTurns) s += gridDim.y * kRecordWaves;
+  } while (kTurns && s < inf.steps);
 }
 
 // values of the strip-ordered copy: entries a row lacks are -0, whose product
@@ -939,9 +944,11 @@ int build_strips(const DevPlan& p, const std::vector<StripGrid>& grids, int max_
     e = hipMemcpyAsync(boxes_at, order_h.data(), order_h.size(), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) {
     k_strip_lanes_of<<<t.nstrips, 64, 0, s>>>(grids_d, boxes_d, box_strip_d, t, cnt);
-    k_strip_records<<<dim3(t.nstrips, record_blocks(t.nrec, t.nstrips, max_steps)), kRecordThreads,
-                      0, s>>>(
-        p.off_ptr, p.off_col, p.row_pos, lanes_lg, grids_d, boxes_d, vb, t, cnt);
+    const unsigned y = record_blocks(t.nrec, t.nstrips, max_steps);
+    auto* const fn = y * kRecordWaves < static_cast<unsigned>(max_steps) ? k_strip_records<true>
+                                                                         : k_strip_records<false>;
+    fn<<<dim3(t.nstrips, y), kRecordThreads, 0, s>>>(p.off_ptr, p.off_col, p.row_pos, lanes_lg,
+                                                     grids_d, boxes_d, vb, t, cnt);
     e = hipGetLastError();
   }
   if (e == hipSuccess) e = hipMemcpyAsync(&c, cnt, sizeof(c), hipMemcpyDeviceToHost, s);
