@@ -119,7 +119,10 @@ typedef enum {
                                entries.  Triangles whose rows sit on regular grids
                                (found from the distinct offsets |i - j|, every entry
                                checked; each system of a batched handle its own grid)
-                               are solved in strips of 64 grid lines instead, under
+                               are solved in strips of 64 grid lines instead where that
+                               is estimated to be faster (not where levels are few and
+                               wide: independent rows, separate chains, many small
+                               systems; the columns of the call count), under
                                AUTO and SELF, as long as no lane rule, grid,
                                assignment, slot width, polling mode, rows per lane or
                                workgroup size was set: no resident grid is needed, and
