@@ -15,7 +15,8 @@
 // checked: it must lead to an earlier step of its own strip, or to a strip
 // that is earlier in the order (no coordinate ahead of its own), at a place
 // the ring holds.  Any pattern that does not pass keeps the row-wise
-// schedules.
+// schedules, and so does one whose levels are few and wide for the length of
+// its lines (strip_time against row_time, strip_grid.hpp).
 #pragma once
 
 #include <hip/hip_runtime_api.h>
